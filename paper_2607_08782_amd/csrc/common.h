@@ -155,6 +155,11 @@ int launch_grouped_ffn_combine(const void* x_perm, const int32_t* offsets, int n
                                int64_t cap_rows, const int32_t* token_row, const float* gate,
                                const void* y_shared, int64_t T, int k, void* y, void* ws,
                                hipStream_t s);
+// the fp32 products (ffn_f32.hip); h: [cap_rows][f] scratch
+int launch_ffn_f32(const float* x, const int32_t* offsets, int n_groups, const void* const* w13,
+                   const void* const* w2, int d, int f, int64_t cap_rows, float* y, float* h,
+                   const int32_t* a_rows, int products, int lead, int lead_rows, int cus,
+                   hipStream_t s);
 size_t grouped_ffn_ws_bytes(int dtype, int64_t cap_rows, int d, int f, int n_groups);
 
 // y_shared: n_shared slices of [T][d] (nullable: none)

@@ -1,0 +1,272 @@
+// fp32 grouped SwiGLU FFN over ragged groups of rows (the fp32 path of
+// moe_grouped_ffn), on v_mfma_f32_16x16x4_f32: fp32 operands, fp32
+// accumulation.
+//
+// What bounds it: the layers run in fp32 are small, so first the latency of the
+// operand loads, then the L2 reads.  Every wave therefore multiplies a 32-row
+// tile straight from global memory, with no LDS staging and no barrier in the
+// loop: in a block of 16 consecutive K a lane loads 4 consecutive K elements of
+// its row (lane q = l / 16 those from 4 q, one 16-byte load), and the j-th MFMA
+// of the block takes element j of every lane, i.e. sums K = 16 b + 4 q + j over
+// q.  A and B use the same order, so each product sums over the same K.  The
+// loads of the next two blocks are in flight while two blocks multiply.  The
+// four waves of a workgroup split K of one tile (short K chains, four times the
+// waves; partial sums added in wave order through LDS) unless there are enough
+// tiles, when they take a 2 x 2 arrangement of tiles and share operands in L1.
+// It replaced 16 x 16 output tiles staged through LDS and multiplied on the
+// vector unit: 1000 tokens, d = 256, f = 512, 8 experts, top-2: gate/up 74 -> 30
+// us, down 73 -> 19 us; 64 tokens, d = 128, f = 256: 12.7 -> 7.3 and 20.7 -> 5.9 us.
+#include "common.h"
+
+namespace moe {
+namespace {
+
+constexpr int F_THREADS = 256;
+constexpr int F_MT = 2;                  // 16-row tiles per wave
+constexpr int F_U = 2;                   // 16-wide K blocks per load batch
+
+struct F32Args {
+    const float* w[MOE_MAX_GROUPS];      // per group: [2N][K] (gate rows, up rows) or [N][K]
+    const float* x;                      // [rows][K], or the token rows of a_rows
+    const int32_t* a_rows;               // row p of the input is x[a_rows[p]]; nullptr: x[p]
+    const int32_t* offsets;              // row offsets of the groups after the first `lead`
+    float* out;                          // [rows][N]
+    int64_t K;
+    int N;
+    int n_groups, lead, lead_rows;
+};
+
+// 4 consecutive K elements from k of a row; zero from K on (VEC: K is a multiple
+// of 4 and the row 16-byte aligned).  The address is clamped, so a lane past the
+// end re-reads the row's first elements.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load_k4(const float* __restrict__ row, int64_t k, int64_t K) {
+    f32x4 v;
+    if (VEC) {
+        const bool ok = k < K;
+        v = *(const f32x4*)(row + (ok ? k : 0));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = ok ? v[j] : 0.f;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool ok = k + j < K;
+            const float e = row[ok ? k + j : 0];
+            v[j] = ok ? e : 0.f;
+        }
+    }
+    return v;
+}
+
+// NT: 16-column tiles per wave (SWIGLU: of gate and of up each).  KS: waves that
+// split K of one tile (4), or 1: the waves take 2 x 2 tiles.
+template <bool SWIGLU, bool VEC, int NT, int KS>
+__global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
+    static_assert(KS == 1 || KS == 4, "wave arrangement");
+    constexpr int WM = KS == 1 ? 2 : 1, WN = KS == 1 ? 2 : 1;
+    constexpr int TM = 16 * F_MT * WM, TN = 16 * NT * WN;
+    constexpr int NP = SWIGLU ? 2 : 1;                   // products: gate, up
+    __shared__ int s_off[MOE_MAX_GROUPS + 1], s_tstart[MOE_MAX_GROUPS + 1];
+    __shared__ f32x4 red[KS == 4 ? 4 * F_MT * NT * NP * 64 : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_groups = args.n_groups;
+    const int N = args.N;
+    const int64_t K = args.K;
+    for (int s = tid; s <= n_groups; s += F_THREADS)
+        s_off[s] = s < args.lead ? s * args.lead_rows
+                                 : args.lead * args.lead_rows + args.offsets[s - args.lead];
+    __syncthreads();
+    const int ncol = (N + TN - 1) / TN;
+    if (wave == 0) {
+        int carry = 0;
+        for (int g0 = 0; g0 < n_groups; g0 += 64) {
+            const int g = g0 + lane;
+            const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
+            const int incl = wave_incl_scan((rows + TM - 1) / TM * ncol, lane);
+            if (g < n_groups) s_tstart[g + 1] = carry + incl;
+            carry += __shfl(incl, 63, 64);
+        }
+        if (lane == 0) s_tstart[0] = 0;
+    }
+    __syncthreads();
+    const int nblk = (int)((K + 15) / 16);
+    const int ks = KS == 4 ? wave : 0;
+    const int b0 = (int)((int64_t)ks * nblk / KS), b1 = (int)((int64_t)(ks + 1) * nblk / KS);
+    const int wm = KS == 1 ? wave & 1 : 0, wn = KS == 1 ? wave >> 1 : 0;
+    const int fr = lane & 15, kq = (lane >> 4) * 4;
+
+    for (int tile = blockIdx.x; tile < s_tstart[n_groups]; tile += gridDim.x) {
+        const int g = last_le(s_tstart, n_groups, tile);
+        const int rows = s_off[g + 1] - s_off[g];
+        const int mt = (rows + TM - 1) / TM;
+        const int local = tile - s_tstart[g];
+        const int m0 = (local % mt) * TM + wm * 16 * F_MT;   // this wave's first row and column
+        const int n0 = (local / mt) * TN + wn * 16 * NT;
+        // rows past the group and columns past N re-read its last one; their sums are
+        // not stored
+        const float* ap[F_MT];
+        const float* bp[NP][NT];
+#pragma unroll
+        for (int i = 0; i < F_MT; ++i) {
+            const int p = s_off[g] + min(m0 + i * 16 + fr, rows - 1);
+            ap[i] = args.x + (int64_t)(args.a_rows ? args.a_rows[p] : p) * K;
+        }
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                bp[q][j] = args.w[g] + ((int64_t)q * N + min(n0 + j * 16 + fr, N - 1)) * K;
+
+        f32x4 acc[NP][F_MT][NT];
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+#pragma unroll
+            for (int i = 0; i < F_MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 a[2][F_U][F_MT], b[2][F_U][NP][NT];
+        // blocks at or past b1 load zeros, so the products need no branch
+        auto load = [&](int slot, int blk) {
+#pragma unroll
+            for (int u = 0; u < F_U; ++u) {
+                const int64_t k = blk + u < b1 ? (int64_t)(blk + u) * 16 + kq : K;
+#pragma unroll
+                for (int i = 0; i < F_MT; ++i) a[slot][u][i] = load_k4<VEC>(ap[i], k, K);
+#pragma unroll
+                for (int q = 0; q < NP; ++q)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) b[slot][u][q][j] = load_k4<VEC>(bp[q][j], k, K);
+            }
+        };
+        auto mma = [&](int slot) {
+#pragma unroll
+            for (int u = 0; u < F_U; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int q = 0; q < NP; ++q)
+#pragma unroll
+                        for (int i = 0; i < F_MT; ++i)
+#pragma unroll
+                            for (int j = 0; j < NT; ++j)
+                                acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                    a[slot][u][i][e], b[slot][u][q][j][e], acc[q][i][j], 0, 0, 0);
+        };
+        load(0, b0);
+        for (int blk = b0; blk < b1; blk += 2 * F_U) {
+            load(1, blk + F_U);
+            mma(0);
+            load(0, blk + 2 * F_U);
+            mma(1);
+        }
+
+        // accumulator element r of lane l: row 4 (l / 16) + r, column l % 16
+        auto store = [&](int i, int j, const f32x4& x, const f32x4& y) {
+            const int col = n0 + j * 16 + fr;
+            if (col >= N) return;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = m0 + i * 16 + (lane >> 4) * 4 + r;
+                const float v = SWIGLU ? x[r] / (1.0f + expf(-x[r])) * y[r] : x[r];
+                if (row < rows) args.out[(int64_t)(s_off[g] + row) * N + col] = v;
+            }
+        };
+        if constexpr (KS == 4) {
+            constexpr int TILES = F_MT * NT;
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+#pragma unroll
+                for (int i = 0; i < F_MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        red[((wave * NP + q) * TILES + i * NT + j) * 64 + lane] = acc[q][i][j];
+            __syncthreads();
+            if (wave < TILES) {
+                f32x4 s[NP];
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    s[q] = red[(q * TILES + wave) * 64 + lane];
+#pragma unroll
+                    for (int w = 1; w < 4; ++w) s[q] += red[((w * NP + q) * TILES + wave) * 64 + lane];
+                }
+                store(wave / NT, wave % NT, s[0], s[NP - 1]);
+            }
+            __syncthreads();                             // red is reused by the next tile
+        } else {
+#pragma unroll
+            for (int i = 0; i < F_MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) store(i, j, acc[0][i][j], acc[NP - 1][i][j]);
+        }
+    }
+}
+
+template <bool SWIGLU>
+int launch_product(const F32Args& a, int64_t cap_rows, bool vec, int cus, hipStream_t s) {
+    // tiles of a TM-row, TN-column split: at most cap_rows / TM + n_groups row tiles
+    auto tiles = [&](int TM, int TN) {
+        return (cap_rows / TM + a.n_groups) * ceil_div(a.N, TN);
+    };
+    auto grid = [&](int64_t n) { return dim3((unsigned)(n < 16 * cus ? n : 16 * cus)); };
+    // 64 x 64 tiles of whole-K waves when there are at least four of them per CU;
+    // below that K is split over the waves, and with fewer than two 32 x 32 tiles
+    // per CU the tile is 16 columns wide (twice the workgroups)
+    const int64_t t64 = tiles(64, 64), t32 = tiles(32, 32);
+    if (!vec)
+        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, false, 2, 4>), grid(t32), dim3(F_THREADS), 0, s, a);
+    else if (t64 >= 4 * cus)
+        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, true, 2, 1>), grid(t64), dim3(F_THREADS), 0, s, a);
+    else if (t32 >= 2 * cus)
+        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, true, 2, 4>), grid(t32), dim3(F_THREADS), 0, s, a);
+    else
+        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, true, 1, 4>), grid(tiles(32, 16)), dim3(F_THREADS),
+                           0, s, a);
+    return launch_status();
+}
+
+bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
+
+}  // namespace
+
+// h = SiLU(x W1^T) * (x W3^T) into ws ([cap_rows][f]), then y = h W2^T.
+int launch_ffn_f32(const float* x, const int32_t* offsets, int n_groups, const void* const* w13,
+                   const void* const* w2, int d, int f, int64_t cap_rows, float* y, float* h,
+                   const int32_t* a_rows, int products, int lead, int lead_rows, int cus,
+                   hipStream_t s) {
+    F32Args a;
+    a.offsets = offsets;
+    a.n_groups = n_groups;
+    a.lead = lead;
+    a.lead_rows = lead_rows;
+    if (products & MOE_FFN_GATE_UP) {
+        bool vec = d % 4 == 0 && aligned16(x);
+        for (int i = 0; i < MOE_MAX_GROUPS; ++i) {
+            a.w[i] = i < n_groups ? (const float*)w13[i] : nullptr;
+            vec = vec && aligned16(a.w[i]);
+        }
+        a.x = x;
+        a.a_rows = a_rows;
+        a.out = h;
+        a.K = d;
+        a.N = f;
+        const int st = launch_product<true>(a, cap_rows, vec, cus, s);
+        if (st != MOE_OK) return st;
+    }
+    if (products & MOE_FFN_DOWN) {
+        bool vec = f % 4 == 0 && aligned16(h);
+        for (int i = 0; i < MOE_MAX_GROUPS; ++i) {
+            a.w[i] = i < n_groups ? (const float*)w2[i] : nullptr;
+            vec = vec && aligned16(a.w[i]);
+        }
+        a.x = h;
+        a.a_rows = nullptr;
+        a.out = y;
+        a.K = f;
+        a.N = d;
+        const int st = launch_product<false>(a, cap_rows, vec, cus, s);
+        if (st != MOE_OK) return st;
+    }
+    return MOE_OK;
+}
+
+}  // namespace moe

@@ -105,11 +105,12 @@ class LayerShare:
         # prefill shapes, even at Mixtral's, slower at Qwen1.5's 8192), and for bf16
         # batches of at most 256 tokens, where the copy is a launch of its own for
         # little data (Qwen3-30B-A3B-shaped decode step 74.4 -> 71.3 us), unless
-        # the share fuses the combine into the FFN call, which reads the packaged rows
+        # the share fuses the combine into the FFN call, which reads the packaged rows.
+        # fp32: always (the fp32 products read every row by its own address)
         packaged_asked = gather_in_ffn is False
         if gather_in_ffn is None:
             fusable = fuse_combine is True or (fuse_combine is None and X.shape[0] <= 64 and k <= 2)
-            gather_in_ffn = X.dtype == torch.bfloat16 and (
+            gather_in_ffn = X.dtype == torch.float32 or (
                 X.shape[0] * k >= 16384 or (X.shape[0] <= 256 and not fusable))
         # shared_in_ffn: the shared experts as leading groups of the routed call (see
         # the module docstring), which reads its rows through row_token.  None: bf16
