@@ -22,20 +22,19 @@ __device__ __forceinline__ float bf16_to_f32(bf16_t h) {
     return __uint_as_float(((uint32_t)h) << 16);
 }
 
-// fp32 -> bf16, round to nearest, ties to even; NaN stays a quiet NaN.
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x0040u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
-}
-
+// fp32 -> bf16, round to nearest, ties to even (v_cvt_pk_bf16_f32); NaN stays a
+// quiet NaN.
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
+__device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)pack_bf16x2(f, f); }
+
+// a / (1 + exp(-a)) with the hardware reciprocal (within 1 ulp)
 __device__ __forceinline__ float silu(float a) {
-    return a / (1.0f + __expf(-a));
+    return a * __builtin_amdgcn_rcpf(1.0f + __expf(-a));
 }
 
 // Inclusive prefix sum across the 64 lanes of a wave.
@@ -66,25 +65,34 @@ inline int launch_status() {
     return e == hipSuccess ? MOE_OK : MOE_ERR_DEVICE;
 }
 
-// Raise kernel F's dynamic-LDS limit to `bytes` on the current device.  The
+// Raise a kernel's dynamic-LDS limit to `bytes` on the current device.  The
 // setting persists, so each device is configured once per size increase and
 // later launches skip the runtime call.  The check, the runtime call and the
 // record of the granted size happen under one lock per kernel, so concurrent
 // callers never leave a smaller limit set than the one recorded.
+struct LdsGrant {
+    static constexpr int kMaxDevices = 64;
+    std::mutex lock;
+    int granted[kMaxDevices] = {};
+};
+
+inline int allow_dynamic_lds(const void* kernel, size_t bytes, LdsGrant& g) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= LdsGrant::kMaxDevices)
+        return MOE_ERR_DEVICE;
+    std::lock_guard<std::mutex> guard(g.lock);
+    if (g.granted[dev] >= (int)bytes) return MOE_OK;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
+        hipSuccess)
+        return MOE_ERR_DEVICE;
+    g.granted[dev] = (int)bytes;
+    return MOE_OK;
+}
+
 template <auto F>
 inline int allow_dynamic_lds(size_t bytes) {
-    constexpr int kMaxDevices = 64;
-    static std::mutex lock;
-    static int granted[kMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return MOE_ERR_DEVICE;
-    std::lock_guard<std::mutex> guard(lock);
-    if (granted[dev] >= (int)bytes) return MOE_OK;
-    if (hipFuncSetAttribute((const void*)F, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)bytes) != hipSuccess)
-        return MOE_ERR_DEVICE;
-    granted[dev] = (int)bytes;
-    return MOE_OK;
+    static LdsGrant grant;
+    return allow_dynamic_lds((const void*)F, bytes, grant);
 }
 
 // ---------------------------------------------------------------------------

@@ -32,26 +32,39 @@
 namespace moe {
 namespace {
 
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 256;          // rows per tile
 constexpr int BNW = 256;         // weight rows per tile
-constexpr int BK = 64;           // K per stage
-constexpr int LDK = BK + 8;      // LDS row stride in elements (144 B: conflict-free reads)
-constexpr int TLDK = BK;         // tiled kernel: 128-byte rows, 16-byte chunks XOR-swizzled
-constexpr int WAVES_M = 4, WAVES_N = 2;
+constexpr int BK = 64;           // K granularity of a tile's range
+constexpr int LDK = BK + 8;      // streaming kernel: LDS row stride in elements (144 B)
+constexpr int WAVES_M = 2, WAVES_N = 2;
 constexpr int GEMM_THREADS = WAVES_M * WAVES_N * 64;
 constexpr int MS = BM / WAVES_M / 16;              // 16-row accumulator tiles per wave
 constexpr int NS = BNW / WAVES_N / 16;             // 16-column accumulator tiles per wave
-constexpr int NH = NS / 2;                         // column tiles per half sub-step
-constexpr int ROWS_PER_PASS = GEMM_THREADS / 8;    // rows one pass of 16-byte loads covers
-constexpr int A_PER = BM / ROWS_PER_PASS;          // 16-byte loads per thread per stage (A)
-constexpr int B_PER = BNW / ROWS_PER_PASS;         // (B)
+// ring of K stages in LDS, filled by direct loads
+constexpr int SK = 32;                             // K per stage: 64-byte LDS rows
+constexpr int ROWB = SK * 2;
+constexpr int RING = 4;
+constexpr int A_BYTES = BM * ROWB, STAGE_BYTES = (BM + BNW) * ROWB;
+constexpr int RING_BYTES = RING * STAGE_BYTES;     // 128 KB
+constexpr int A_LOADS = A_BYTES / 1024 / 4;        // 1 KB direct loads per wave per stage
+constexpr int B_LOADS = BNW * ROWB / 1024 / 4;
+constexpr int LOADS = A_LOADS + B_LOADS;
+constexpr int TILE_LIST = 256;                     // tiles of a workgroup listed at a time
 constexpr int NUM_XCD = 8;
-// instruction classes of __builtin_amdgcn_sched_group_barrier
-constexpr int SG_MFMA = 0x008, SG_VMEM_READ = 0x020, SG_DS_READ = 0x100, SG_DS_WRITE = 0x200;
 constexpr uint32_t RSRC_WORD3 = 0x00020000;        // raw buffer: 32-bit data format
 constexpr int A_OOB = 0x7fffff00;                  // offset past any descriptor: reads zero
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// wait until at most N of this wave's vector-memory operations are outstanding
+// (they complete in issue order); no memory access moves across it
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
 // First row of group g.  The first `lead` groups hold lead_rows rows each (the
 // shared experts' groups of moe_grouped_ffn_rows_shared, every token once); the
@@ -138,43 +151,6 @@ __host__ __device__ __forceinline__ SplitPlan split_plan(int total, int KT, int 
     return p;
 }
 
-// B-tile row of the jj-th 32-wide accumulator column block of wave column wn.
-// SwiGLU tiles hold 128 gate rows then the matching 128 up rows; a wave takes
-// the same columns from both halves, so gate and up meet in its registers.
-template <bool SWIGLU>
-__device__ __forceinline__ int b_sub_row(int wn, int jj) {
-    if (SWIGLU) {
-        constexpr int HW = BNW / 2 / WAVES_N;
-        return jj < NS / 2 ? wn * HW + jj * 16 : BNW / 2 + wn * HW + (jj - NS / 2) * 16;
-    }
-    return wn * (BNW / WAVES_N) + jj * 16;
-}
-
-// 4 x 4 transpose inside each aligned quad of lanes: on entry lane 4 q + e holds
-// v[r] = M[r][e] of its quad's block, on exit v[c] = M[e][c].  Two exchange
-// stages (lane distance 1, then 2) with DPP quad permutations.
-__device__ __forceinline__ float dpp_quad(float x, int ctrl_sel) {
-    const int i = __float_as_int(x);
-    return __int_as_float(ctrl_sel == 1 ? __builtin_amdgcn_mov_dpp(i, 0xB1, 0xF, 0xF, true)
-                                        : __builtin_amdgcn_mov_dpp(i, 0x4E, 0xF, 0xF, true));
-}
-
-__device__ __forceinline__ void quad_transpose(float* v, int lane) {
-    const bool o1 = (lane & 1) != 0, o2 = (lane & 2) != 0;
-#pragma unroll
-    for (int r = 0; r < 4; r += 2) {          // lanes e, e ^ 1 swap elements r ^ 1
-        const float recv = dpp_quad(o1 ? v[r] : v[r + 1], 1);
-        v[r] = o1 ? recv : v[r];
-        v[r + 1] = o1 ? v[r + 1] : recv;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {             // lanes e, e ^ 2 swap elements r ^ 2
-        const float recv = dpp_quad(o2 ? v[r] : v[r + 2], 2);
-        v[r] = o2 ? recv : v[r];
-        v[r + 2] = o2 ? v[r + 2] : recv;
-    }
-}
-
 __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
@@ -222,26 +198,63 @@ __device__ __forceinline__ void small_limits(const int* s_off, int n_groups, int
     lim_down = 4 * mt * tiles_down <= split_units ? SMALL_ROWS_MAX : 0;
 }
 
-// Persistent grouped NT GEMM.  Per tile: operands stream through per-tile
-// buffer descriptors (rows past the group's end fall outside the descriptor and
-// read as zero), are staged through registers into a double-buffered LDS
-// stage, and MFMA fragments are double-buffered per 16-wide K sub-step, so the
-// LDS reads of sub-step q+1 (including across the stage barrier) overlap the
-// MFMAs of sub-step q.
+// Persistent grouped NT GEMM: 4 waves (2 x 2), one per SIMD, each a 128 x 128
+// tile of the 256 x 256 macro tile (the fewest LDS bytes per flop that the
+// accumulators allow: 128 KB of fragment reads per 64 K against 192 KB for eight
+// 64 x 128 wave tiles).  Both operands go straight from global memory into a ring
+// of four 32-wide K stages (no staging registers, no LDS store instructions),
+// three stages in flight: a stage's loads have three stages of MFMAs to arrive.
+// One barrier per stage: at the barrier of stage t every wave holds its fragments
+// of stage t in registers, so stage t's buffer is free for stage t + 4, and stage
+// t + 1 has landed, so its fragments are read during stage t's MFMAs.  The stages
+// of a workgroup's tiles form one stream: a tile's last four stages load the next
+// tile's first four, and its first fragments are in registers before the epilogue.
+// LDS rows are 64 bytes; 16-byte chunk c of row r sits at c ^ ((r >> 1) & 3)
+// (conflict-free for the 16-row fragment reads).
+// The weights are the MFMA's A operand, the token rows its B operand, so a lane
+// holds 4 consecutive output columns of one row per accumulator tile; the weight
+// rows of a 32-row block are laid out in LDS in the order that makes two tiles'
+// columns 8 consecutive ones (w_order), stored as one 16-byte vector.
 // GATHER: row p of A is row a_rows[p] of args.a (the token rows themselves, so
 // the packaged copy of them is never materialised).
+struct TileRec {
+    int g, row0, rows_valid, n0, kt0, nsteps, u, split;   // kt0, nsteps in stages
+};
+
+// weight row, within its 32-row block, of LDS row r: MFMA tile (r >> 4) & 1, row
+// i = r & 15 holds output column 8 (i >> 2) + 4 tile + (i & 3)
+__device__ __forceinline__ int w_order(int r) {
+    return (r & ~31) + 8 * ((r >> 2) & 3) + 4 * ((r >> 4) & 1) + (r & 3);
+}
+
+// d += w x^T on v_mfma_f32_16x16x32_bf16 with d in AGPRs or in VGPRs, and the same
+// placement for a value between MFMAs (the register constraints exist in the device
+// pass only, so these and the kernel's body are compiled there alone)
+#ifdef __HIP_DEVICE_COMPILE__
+__device__ __forceinline__ void mfma_agpr(f32x4& d, const bf16x8& w, const bf16x8& x) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(w), "v"(x));
+}
+__device__ __forceinline__ void mfma_vgpr(f32x4& d, const bf16x8& w, const bf16x8& x) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(w), "v"(x));
+}
+__device__ __forceinline__ void pin_agpr(f32x4& d) { asm volatile("" : "+a"(d)); }
+__device__ __forceinline__ void pin_vgpr(f32x4& d) { asm volatile("" : "+v"(d)); }
+__device__ __forceinline__ void opaque(int& x) { asm volatile("" : "+v"(x)); }
+#endif
+
 template <bool SWIGLU, bool GATHER = false>
-__global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_kernel(GemmArgs args) {
-    __shared__ __attribute__((aligned(16))) bf16_t As[2][BM * TLDK];
-    __shared__ __attribute__((aligned(16))) bf16_t Bs[2][BNW * TLDK];
+__global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs args) {
+#ifdef __HIP_DEVICE_COMPILE__
+    extern __shared__ __attribute__((aligned(1024))) char ring[];
     __shared__ int s_off[MOE_MAX_GROUPS + 1];
     __shared__ int s_tstart[MOE_MAX_GROUPS + 1];
+    __shared__ TileRec s_tile[TILE_LIST];
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1;
     const int n_groups = args.n_groups;
-    const int BN_OUT = SWIGLU ? BNW / 2 : BNW;      // output columns per tile
+    constexpr int BN_OUT = SWIGLU ? BNW / 2 : BNW;      // output columns per tile
 
     // the down launch reads its row limit from the gate/up launch (no group can
     // exceed SMALL_ROWS when there is nowhere to keep it)
@@ -279,55 +292,65 @@ __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_kernel(GemmArgs arg
     const int uchunk = (n_units + NUM_XCD - 1) / NUM_XCD;
     const int s_begin = min(xcd * uchunk, n_units), s_end = min(s_begin + uchunk, n_units);
     const int n_head = h_end - h_begin, n_mine = n_head + (s_end - s_begin);
-    const int kc = (tid & 7) * 8;
-    const int voff = ((tid >> 3) * K + kc) * 2;
-    const int vstep = ROWS_PER_PASS * K * 2;
-
     if (widx >= n_mine) return;
+    const int n_list = (n_mine - widx + nper - 1) / nper;   // this workgroup's tiles
 
-    // Tile coordinates, uniform across the workgroup: every thread derives them
-    // from the plan in LDS, kept in scalar registers.  Whole tile, or unit
-    // u = (split tile, K chunk).
-    struct Tile {
-        int g, row0, rows_valid, n0, kt0, nsteps, u, split;
+    // Tile q of this workgroup: a whole tile, or unit u = (split tile, K chunk).
+    // Each thread works out one of the next TILE_LIST, so a tile's start costs one
+    // LDS read instead of a search over the groups.
+    auto list_tiles = [&](int q0) {
+        const int q = q0 + tid;
+        if (tid < TILE_LIST && q < n_list) {
+            const int i = widx + q * nper;
+            TileRec c;
+            const bool split = i >= n_head;
+            const int u = split ? s_begin + (i - n_head) : 0;
+            const int L = split ? plan.head + u / plan.S : h_begin + i;
+            const int S = split ? plan.S : 1;
+            const int kchunk = split ? u - (u / plan.S) * plan.S : 0;
+            const int kt0 = (int)((int64_t)kchunk * KT / S);
+            const int s = last_le(s_tstart, n_groups, L);
+            const int mt = (int)ceil_div(s_off[s + 1] - s_off[s], BM);
+            const int local = L - s_tstart[s];
+            const int nt = local / mt;
+            c.g = s;
+            c.row0 = s_off[s] + (local - nt * mt) * BM;
+            c.rows_valid = min(BM, s_off[s + 1] - c.row0);
+            c.n0 = nt * BN_OUT;
+            c.kt0 = kt0 * (BK / SK);
+            c.nsteps = ((int)((int64_t)(kchunk + 1) * KT / S) - kt0) * (BK / SK);
+            c.u = u;
+            c.split = split ? 1 : 0;
+            s_tile[tid] = c;
+        }
     };
-    auto tile_at = [&](int i) {
-        Tile c;
-        const bool split = i >= n_head;
-        const int u = split ? s_begin + (i - n_head) : 0;
-        const int L = split ? plan.head + u / plan.S : h_begin + i;
-        const int S = split ? plan.S : 1;
-        const int kchunk = split ? u - (u / plan.S) * plan.S : 0;
-        const int kt0 = (int)((int64_t)kchunk * KT / S);
-        const int s = last_le(s_tstart, n_groups, L);
-        const int rows = s_off[s + 1] - s_off[s];
-        const int mt = (int)ceil_div(rows, BM);
-        const int local = L - s_tstart[s];
-        const int nt = local / mt;
-        const int row0 = s_off[s] + (local - nt * mt) * BM;
-        c.g = __builtin_amdgcn_readfirstlane(s);
-        c.row0 = __builtin_amdgcn_readfirstlane(row0);
-        c.rows_valid = __builtin_amdgcn_readfirstlane(min(BM, s_off[s + 1] - row0));
-        c.n0 = __builtin_amdgcn_readfirstlane(nt) * BN_OUT;
-        c.kt0 = __builtin_amdgcn_readfirstlane(kt0);
-        c.nsteps = __builtin_amdgcn_readfirstlane((int)((int64_t)(kchunk + 1) * KT / S) - kt0);
-        c.u = __builtin_amdgcn_readfirstlane(u);
-        c.split = __builtin_amdgcn_readfirstlane(split ? 1 : 0);
+    auto tile_at = [&](int q) {
+        TileRec c = s_tile[q % TILE_LIST];
+        c.g = __builtin_amdgcn_readfirstlane(c.g);
+        c.row0 = __builtin_amdgcn_readfirstlane(c.row0);
+        c.rows_valid = __builtin_amdgcn_readfirstlane(c.rows_valid);
+        c.n0 = __builtin_amdgcn_readfirstlane(c.n0);
+        c.kt0 = __builtin_amdgcn_readfirstlane(c.kt0);
+        c.nsteps = __builtin_amdgcn_readfirstlane(c.nsteps);
+        c.u = __builtin_amdgcn_readfirstlane(c.u);
+        c.split = __builtin_amdgcn_readfirstlane(c.split);
         return c;
     };
-    // operand descriptors of a tile: rows past the group's end fall outside the
-    // A descriptor and read as zero; gate and up halves of a SwiGLU weight tile
+    // operand descriptors of a tile: rows past the group's end or past the output
+    // columns fall outside them (their products are not stored); gate and up halves
+    // of a SwiGLU weight tile.  live = false: empty ranges, loads without traffic
     struct Rsrc {
         __amdgpu_buffer_rsrc_t a, lo, hi;
     };
-    auto rsrc_of = [&](const Tile& c) {
+    auto rsrc_of = [&](const TileRec& c, bool live) {
         Rsrc r;
-        r.a = GATHER ? __builtin_amdgcn_make_buffer_rsrc((void*)args.a, (short)0, args.a_total * K * 2,
-                                                         RSRC_WORD3)
-                     : __builtin_amdgcn_make_buffer_rsrc((void*)(args.a + (int64_t)c.row0 * K), (short)0,
-                                                         c.rows_valid * K * 2, RSRC_WORD3);
+        r.a = GATHER ? __builtin_amdgcn_make_buffer_rsrc((void*)args.a, (short)0,
+                                                         live ? args.a_total * K * 2 : 0, RSRC_WORD3)
+                     : __builtin_amdgcn_make_buffer_rsrc((void*)(args.a + (int64_t)c.row0 * K),
+                                                         (short)0, live ? c.rows_valid * K * 2 : 0,
+                                                         RSRC_WORD3);
         const bf16_t* __restrict__ W = args.w[c.g];
-        const int bvalid = min(BN_OUT, args.N - c.n0);
+        const int bvalid = live ? min(BN_OUT, args.N - c.n0) : 0;
         const int bup = SWIGLU ? args.up_row + c.n0 : c.n0;
         r.lo = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (int64_t)c.n0 * K), (short)0,
                                                  bvalid * K * 2, RSRC_WORD3);
@@ -335,270 +358,251 @@ __global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_kernel(GemmArgs arg
                                                  bvalid * K * 2, RSRC_WORD3);
         return r;
     };
-    // per-thread A row offsets (GATHER: the token rows of the tile)
-    auto a_offsets = [&](const Tile& c, int* av) {
+    // load i of a wave fills LDS rows 64 i + 16 wave + (lane / 4) of A or B, chunk
+    // slot lane % 4
+    const int lrow = 16 * wave + (lane >> 2);
+    const int kc = (((lane & 3) ^ ((lane >> 3) & 3)) * 8);
+    const int avoff = (lrow * K + kc) * 2;
+    const int bvoff = (w_order(lrow) * K + kc) * 2;
+    const int vstep = 64 * K * 2;
+    // GATHER: the token rows of a tile's loads (-1: past the group), and their offsets
+    auto a_tokens = [&](const TileRec& c, int* tok) {
 #pragma unroll
-        for (int i = 0; i < A_PER; ++i) {
-            if constexpr (GATHER) {
-                const int rin = (tid >> 3) + ROWS_PER_PASS * i;
-                av[i] = rin < c.rows_valid ? (args.a_rows[c.row0 + rin] * K + kc) * 2 : A_OOB;
-            } else {
-                av[i] = voff + i * vstep;
-            }
+        for (int i = 0; i < A_LOADS; ++i) {
+            const int rin = lrow + 64 * i;
+            tok[i] = GATHER && rin < c.rows_valid ? args.a_rows[c.row0 + rin] : -1;
         }
     };
-
-    uint4 ra[A_PER], rb[B_PER];
-    auto gload = [&](const Rsrc& r, const int* av, int kt) {
-        const int so = kt * BK * 2;
+    auto a_offsets = [&](const int* tok, int* av) {
 #pragma unroll
-        for (int i = 0; i < A_PER; ++i) ra[i] = buffer_load16(r.a, av[i], so);
-#pragma unroll
-        for (int i = 0; i < B_PER; ++i) {
-            if (SWIGLU && i >= B_PER / 2)
-                rb[i] = buffer_load16(r.hi, voff + (i - B_PER / 2) * vstep, so);
-            else
-                rb[i] = buffer_load16(r.lo, voff + i * vstep, so);
-        }
+        for (int i = 0; i < A_LOADS; ++i)
+            av[i] = !GATHER ? avoff + i * vstep : tok[i] >= 0 ? (tok[i] * K + kc) * 2 : A_OOB;
     };
-    // 16-byte chunk c of LDS row r sits at chunk c ^ (r & 7): conflict-free for the
-    // stage stores (8 lanes per row) and for the 16-row fragment reads
-    const int sc = ((tid & 7) ^ ((tid >> 3) & 7)) * 8;
-    auto sstore = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < A_PER; ++i)
-            *(uint4*)&As[buf][((tid >> 3) + ROWS_PER_PASS * i) * TLDK + sc] = ra[i];
-#pragma unroll
-        for (int i = 0; i < B_PER; ++i)
-            *(uint4*)&Bs[buf][((tid >> 3) + ROWS_PER_PASS * i) * TLDK + sc] = rb[i];
+    // direct load i of a wave's share of stage kt (A's loads, then B's)
+    auto load1 = [&](const Rsrc& r, const int* av, int kt, int slot, int i) {
+        char* base = ring + slot * STAGE_BYTES + wave * 1024 + i * 4096;
+        if (i < A_LOADS) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r.a, (lds_void*)base, 16, av[i], kt * ROWB, 0, 0);
+        } else {
+            const int b = i - A_LOADS;
+            const bool up = SWIGLU && b >= B_LOADS / 2;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(up ? r.hi : r.lo, (lds_void*)base, 16,
+                                                     bvoff + (up ? b - B_LOADS / 2 : b) * vstep,
+                                                     kt * ROWB, 0, 0);
+        }
     };
 
     f32x4 acc[MS][NS];
-    // v_mfma_f32_16x16x32_bf16 fragments: lane l holds row l % 16 of a 16-row
-    // block and the 8 K elements 8 (l / 16) .. of a 32-wide sub-step, for A and
-    // B alike, so every product sums over the same K
+    // v_mfma_f32_16x16x32_bf16 fragments: lane l holds row l % 16 of a 16-row block
+    // and the 8 K elements 8 (l / 16) .. of the stage, for both operands alike
     const int frow = lane & 15;
-    const int fsw = lane & 7;                         // the swizzle of rows frow (+ 16 m)
-    const int fc0 = ((lane >> 4) ^ fsw) * 8, fc1 = ((4 + (lane >> 4)) ^ fsw) * 8;
-    const bf16_t* a_lds0 = &As[0][(wm * (BM / WAVES_M) + frow) * TLDK];
-    const bf16_t* b_lds0 = &Bs[0][frow * TLDK];
-    // a 32-wide sub-step q runs as two halves (column tiles 0..NH-1, NH..NS-1);
-    // the fragments of the next half are read while the current half multiplies
-    bf16x8 fa0[MS], fa1[MS], fb0[NH], fb1[NH];
-    auto read_a = [&](int buf, int q, bf16x8* fa) {
-#pragma unroll
-        for (int mi = 0; mi < MS; ++mi)
-            fa[mi] = *(const bf16x8*)(a_lds0 + buf * BM * TLDK + mi * 16 * TLDK + (q ? fc1 : fc0));
+    const int fchunk = ((lane >> 4) ^ ((frow >> 1) & 3)) * 16;
+    const int a_frag = (wm * (BM / WAVES_M) + frow) * ROWB + fchunk;
+    // SwiGLU tiles hold 128 gate rows then the matching 128 up rows; a wave takes the
+    // same columns from both halves, so gate and up meet in its registers
+    const int b_frag = A_BYTES + (wn * (SWIGLU ? BNW / 2 / WAVES_N : BNW / WAVES_N) + frow) * ROWB +
+                       fchunk;
+    auto b_tile = [](int j) { return SWIGLU && j >= NS / 2 ? BNW / 2 + (j - NS / 2) * 16 : j * 16; };
+    // MFMA u of a stage.  The accumulators of row blocks 0..6 are pinned to 224 AGPRs,
+    // those of the last block to VGPRs (filling all 256 AGPRs left the register
+    // allocator moving some in and out of VGPRs in every stage, and so did the
+    // compiler's own choice)
+    auto mfma = [&](int u, const bf16x8* fa, const bf16x8* fb) {
+        const int m = u / NS, j = u % NS;
+        if (m < MS - 1) mfma_agpr(acc[m][j], fb[j], fa[m]);
+        else mfma_vgpr(acc[m][j], fb[j], fa[m]);
     };
-    auto read_b = [&](int buf, int q, int h, bf16x8* fb) {
+    // accumulators cross between MFMAs and other instructions only behind enough idle
+    // cycles (the compiler does not see the MFMAs inside the assembly): settle() before
+    // or after all MFMAs, then use(m) where row block m is first set or read (it also
+    // keeps the compiler from copying all accumulators out at once)
+    auto settle = []() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); };
+    auto use = [&](int m) {
 #pragma unroll
-        for (int j = 0; j < NH; ++j)
-            fb[j] = *(const bf16x8*)(b_lds0 + buf * BNW * TLDK +
-                                     b_sub_row<SWIGLU>(wn, h * NH + j) * TLDK + (q ? fc1 : fc0));
+        for (int j = 0; j < NS; ++j) {
+            if (m < MS - 1) pin_agpr(acc[m][j]);
+            else pin_vgpr(acc[m][j]);
+        }
     };
-    auto mfma = [&](const bf16x8* fa, const bf16x8* fb, int h) {
+    constexpr int STORES = SWIGLU ? MS * NS / 4 : MS * NS / 2;   // 16-byte stores of an epilogue
+    unsigned c = 0;                              // stages run so far: stage slot c % RING
+    int since = 3;                               // stages since an epilogue (3: or more)
+    // one stage: multiply the fragments fa, fb (stage t), read those of stage t + 1
+    // into na, nb, load stage t + 4 (or its stand-in of the next tile)
+    auto stage = [&](const bf16x8* fa, const bf16x8* fb, bf16x8* na, bf16x8* nb, const Rsrc& r,
+                     const int* av, int kt) {
+        // stage t + 1 has landed: at most the loads of the two stages after it, and in
+        // the first stages after an epilogue its stores, are outstanding
+        if (since < 3) wait_vm<2 * LOADS + STORES>();
+        else wait_vm<2 * LOADS>();
+        // this wave's fragment reads of stage t are done
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        ++since;
+        // issue order, fixed: each of the next stage's 16 fragment reads before two
+        // MFMAs, each of the 8 loads before four
+        const int slot = c % RING;
+        ++c;
+        const char* st = ring + (c % RING) * STAGE_BYTES;
 #pragma unroll
-        for (int mi = 0; mi < MS; ++mi)
+        for (int i = 0; i < MS + NS; ++i) {
+            if (i < NS) nb[i] = *(const bf16x8*)(st + b_frag + b_tile(i) * ROWB);
+            else na[i - NS] = *(const bf16x8*)(st + a_frag + (i - NS) * 16 * ROWB);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < NH; ++j)
-                acc[mi][h * NH + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    fa[mi], fb[j], acc[mi][h * NH + j], 0, 0, 0);
+            for (int u = 2 * i; u < 2 * i + 2; ++u) mfma(u, fa, fb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            load1(r, av, kt, slot, i);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 32 + 4 * i; u < 32 + 4 * i + 4; ++u) mfma(u, fa, fb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
 
-    // The workgroup's tiles form one pipeline: while a tile's last K steps run,
-    // the next tile's first stage is loaded (in place of a repeat of the last
-    // stage) and stored to the free LDS buffer, and its second stage is in flight
-    // during the epilogue, so a tile starts without waiting for its operands.
-    // pb: the LDS buffer that holds the current tile's first stage.
-    int i = widx;
-    Tile cur = tile_at(i);
-    Rsrc rc = rsrc_of(cur);
-    int avc[A_PER];
-    a_offsets(cur, avc);
-    int pb = 0;
-    gload(rc, avc, cur.kt0);
-    sstore(0);
-    gload(rc, avc, cur.kt0 + (cur.nsteps > 1 ? 1 : 0));
+    list_tiles(0);
     __syncthreads();
+    // with fewer than four stages a tile (K = 64) cannot hold the next tile's loads:
+    // every tile then starts its own ring
+    const bool chain = KT * (BK / SK) >= RING;
+    bf16x8 fa0[MS], fa1[MS], fb0[NS], fb1[NS];
+    int q = 0;
+    TileRec cur = tile_at(0);
+    Rsrc rc = rsrc_of(cur, true);
+    int avc[A_LOADS], tok[A_LOADS];
+    a_tokens(cur, tok);
+    a_offsets(tok, avc);
+    bool start = true;
     for (;;) {
-        const int inext = i + nper;
-        const bool has_next = inext < n_mine;
-        const Tile nxt = tile_at(has_next ? inext : i);
-        const Rsrc rn = rsrc_of(nxt);
-        int avn[A_PER];
-        a_offsets(nxt, avn);
-        // what the load after this tile's last stage fetches: the next tile's
-        // first stage, or (last tile) this tile's last stage again (cached)
-        const int kt_after = has_next ? nxt.kt0 : cur.kt0 + cur.nsteps - 1;
-        const int nsteps = cur.nsteps;
-
+        if (start) {
 #pragma unroll
-        for (int mi = 0; mi < MS; ++mi)
+            for (int s = 0; s < RING; ++s)
 #pragma unroll
-            for (int jj = 0; jj < NS; ++jj)
+                for (int i = 0; i < LOADS; ++i)
+                    load1(rc, avc, cur.kt0 + min(s, cur.nsteps - 1), (c + s) % RING, i);
+            wait_vm<3 * LOADS>();
+            asm volatile("s_barrier" ::: "memory");
+            const char* st = ring + (c % RING) * STAGE_BYTES;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[mi][jj][r] = 0.f;
-
-        read_a(pb, 0, fa0);
-        read_b(pb, 0, 0, fb0);
-        // Every step but the last runs one straight path, so the MFMAs after the
-        // barrier (on fragments read before it) issue without waiting for the
-        // next stage's reads; the last step is peeled off below.
-        for (int t = 0; t + 1 < nsteps; ++t) {
-            const int buf = pb ^ (t & 1);
-            read_b(buf, 0, 1, fb1);
-            mfma(fa0, fb0, 0);
-            read_a(buf, 1, fa1);
-            read_b(buf, 1, 0, fb0);
-            mfma(fa0, fb1, 1);
-            read_b(buf, 1, 1, fb1);
-            mfma(fa1, fb0, 0);
-            sstore(buf ^ 1);
-            // issue order up to the barrier: each half's fragment reads at the head of
-            // the MFMA batch before the one that uses them, the stage stores spread
-            // over the last batch
+            for (int j = 0; j < NS; ++j) fb0[j] = *(const bf16x8*)(st + b_frag + b_tile(j) * ROWB);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, 12, 0);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, 8, 0);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(SG_DS_WRITE, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(SG_MFMA, 4, 0);
+            for (int m = 0; m < MS; ++m) fa0[m] = *(const bf16x8*)(st + a_frag + m * 16 * ROWB);
+        }
+        const int qn = q + 1;
+        const bool has_next = qn < n_list;
+        if (has_next && qn % TILE_LIST == 0) {
             __syncthreads();
-            {
-                // stage t + 2 of this tile, or what follows its last stage
-                const bool own = t + 2 < nsteps;
-                Rsrc rl;
-                rl.a = own ? rc.a : rn.a;
-                rl.lo = own ? rc.lo : rn.lo;
-                rl.hi = own ? rc.hi : rn.hi;
-                int avl[A_PER];
-#pragma unroll
-                for (int q = 0; q < A_PER; ++q) avl[q] = own ? avc[q] : avn[q];
-                gload(rl, avl, own ? cur.kt0 + t + 2 : kt_after);
-            }
-            read_a(buf ^ 1, 0, fa0);
-            read_b(buf ^ 1, 0, 0, fb0);
-            mfma(fa1, fb1, 1);
-            // after the barrier: the next stage's first fragment reads, then its
-            // global loads, each between MFMAs of the last half
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(SG_VMEM_READ, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-            }
+            list_tiles(qn);
+            __syncthreads();
         }
-        const int lbuf = pb ^ ((nsteps - 1) & 1);
-        {
-            read_b(lbuf, 0, 1, fb1);
-            mfma(fa0, fb0, 0);
-            read_a(lbuf, 1, fa1);
-            read_b(lbuf, 1, 0, fb0);
-            mfma(fa0, fb1, 1);
-            read_b(lbuf, 1, 1, fb1);
-            mfma(fa1, fb0, 0);
-            mfma(fa1, fb1, 1);
-        }
-        if (has_next) {
-            // the next tile's first stage into the LDS buffer this tile no longer
-            // reads (with a one-stage tile the registers hold this tile's stage
-            // again: load it first), its second stage into the registers
-            if (nsteps == 1) gload(rn, avn, nxt.kt0);
-            sstore(lbuf ^ 1);
-            gload(rn, avn, nxt.kt0 + (nxt.nsteps > 1 ? 1 : 0));
-        }
-        __syncthreads();
+        const TileRec nxt = has_next ? tile_at(qn) : cur;
+        a_tokens(nxt, tok);                      // used by the last stages' loads
+        const int nsteps = cur.nsteps;
+#pragma unroll
+        for (int m = 0; m < MS; ++m)
+#pragma unroll
+            for (int j = 0; j < NS; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < MS; ++m) use(m);
+        settle();
 
-        if (cur.split) {
-            // fp32 partial tile of this K chunk, laid out [row][weight row of the
-            // tile]; rows past the group fall outside the descriptor and are dropped
-            const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
-                (void*)(args.part + (int64_t)cur.u * BM * BNW), (short)0, cur.rows_valid * BNW * 4,
-                RSRC_WORD3);
-            const int lbase = ((wm * (BM / WAVES_M) + (lane >> 4) * 4) * BNW +
-                               b_sub_row<SWIGLU>(wn, 0) + (lane & 15)) * 4;
+        // the loads of stage t + 4: of this tile, or past its end of the next one
+        const Rsrc rn = rsrc_of(nxt, has_next && chain);
+        int avn[A_LOADS];
+        a_offsets(tok, avn);
+        const int kt_next = nxt.kt0 - (nsteps - RING);
+        auto step = [&](int t, const bf16x8* fa, const bf16x8* fb, bf16x8* na, bf16x8* nb) {
+            const bool own = t + RING < nsteps;
+            Rsrc r;
+            r.a = own ? rc.a : rn.a;
+            r.lo = own ? rc.lo : rn.lo;
+            r.hi = own ? rc.hi : rn.hi;
+            int av[A_LOADS];
 #pragma unroll
-            for (int mi = 0; mi < MS; ++mi)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int jj = 0; jj < NS; ++jj) {
-                        const int off = ((mi * 16 + r) * BNW + b_sub_row<SWIGLU>(0, jj)) * 4;
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[mi][jj][r]), prsrc,
-                                                              lbase, off, 0);
-                    }
-        } else {
-            // epilogue: accumulator element r of a 16x16 tile sits at row 4 (lane / 16)
-            // + r, column lane % 16; a 4 x 4 transpose inside each lane quad gives
-            // lane 4 b + e of row group a the row 4 a + e, columns 4 b .. 4 b + 3,
-            // stored as one 8-byte vector (a quarter of the store instructions of
-            // 2-byte stores, whole 32-byte row segments per lane quad) through a
-            // descriptor over the tile's rows (rows past the group are dropped)
-            const int qa = lane >> 4, qb = (lane >> 2) & 3, qe = lane & 3;
-            const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
-                (void*)(args.out + (int64_t)cur.row0 * args.ldo), (short)0,
-                cur.rows_valid * args.ldo * 2, RSRC_WORD3);
-            auto store4 = [&](const float* v, int row_in, int col) {
-                const uint2 w = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, w), orsrc,
-                                                      (row_in * args.ldo + col) * 2, 0, 0);
-            };
-#pragma unroll
-            for (int mi = 0; mi < MS; ++mi) {
-                const int row_in = wm * (BM / WAVES_M) + mi * 16 + qa * 4 + qe;
-                if (SWIGLU) {
-                    constexpr int HW = BNW / 2 / WAVES_N;
-#pragma unroll
-                    for (int j = 0; j < NS / 2; ++j) {
-                        float v[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = silu(acc[mi][j][r]) * acc[mi][NS / 2 + j][r];
-                        quad_transpose(v, lane);
-                        const int col = cur.n0 + wn * HW + j * 16 + qb * 4;
-                        if (col < args.N) store4(v, row_in, col);
-                    }
-                } else {
-#pragma unroll
-                    for (int jj = 0; jj < NS; ++jj) {
-                        float v[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = acc[mi][jj][r];
-                        quad_transpose(v, lane);
-                        const int col = cur.n0 + wn * (BNW / WAVES_N) + jj * 16 + qb * 4;
-                        if (col < args.N) store4(v, row_in, col);
-                    }
-                }
-            }
+            for (int i = 0; i < A_LOADS; ++i) av[i] = !GATHER || own ? avc[i] : avn[i];
+            stage(fa, fb, na, nb, r, av, t + (own ? cur.kt0 + RING : kt_next));
+        };
+        for (int t = 0; t < nsteps; t += 2) {
+            step(t, fa0, fb0, fa1, fb1);
+            step(t + 1, fa1, fb1, fa0, fb0);
         }
-        if (!has_next) break;
-        i = inext;
-        cur = nxt;
+        settle();
         rc = rn;
 #pragma unroll
-        for (int q = 0; q < A_PER; ++q) avc[q] = avn[q];
-        pb = lbuf ^ 1;
+        for (int i = 0; i < A_LOADS; ++i) avc[i] = avn[i];
+
+        // accumulator element r of tile (m, j) sits at output row m * 16 + lane % 16 of
+        // the wave's rows; elements 0..3 of tiles 2 p and 2 p + 1 are columns 32 p + 8
+        // (lane / 16) + 0..3 and + 4..7.  The lane's offset is made opaque per tile: the
+        // compiler otherwise keeps every store's offset live across the K loop, in scratch
+        int lrow_out = wm * (BM / WAVES_M) + frow, colq = (lane >> 4) * 8;
+        opaque(lrow_out);
+        opaque(colq);
+        if (cur.split) {
+            // fp32 partial tile of this K chunk, laid out [row][weight row of the tile]
+            // (rows past the group inside the last 16-row block hold unused sums)
+            const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(args.part + (int64_t)cur.u * BM * BNW), (short)0, BM * BNW * 4, RSRC_WORD3);
+            const int wcol = wn * (SWIGLU ? BNW / 2 / WAVES_N : BNW / WAVES_N);
+            const int vo = (lrow_out * BNW + wcol + colq) * 4;
+#pragma unroll
+            for (int m = 0; m < MS; ++m) {
+                if (wm * (BM / WAVES_M) + m * 16 >= cur.rows_valid) break;
+                use(m);
+#pragma unroll
+                for (int j = 0; j < NS; ++j)
+                    __builtin_amdgcn_raw_buffer_store_b128(
+                        __builtin_bit_cast(u32x4, acc[m][j]), prsrc,
+                        vo + (b_tile(j & ~1) + (j & 1) * 4) * 4, m * 16 * BNW * 4, 0);
+            }
+            wait_vm<0>();                        // more stores than the stage waits allow for
+        } else {
+            // rows past the group are dropped by the descriptor, and so are 32-column
+            // blocks past the output (N is a multiple of 64), by an empty one
+            const int wcol = cur.n0 + wn * (BN_OUT / WAVES_N);
+            auto orsrc = [&](int p) {
+                return __builtin_amdgcn_make_buffer_rsrc(
+                    (void*)(args.out + (int64_t)cur.row0 * args.ldo), (short)0,
+                    wcol + 32 * p < args.N ? cur.rows_valid * args.ldo * 2 : 0, RSRC_WORD3);
+            };
+            int vo = (lrow_out * args.ldo + wcol + colq) * 2;
+#pragma unroll
+            for (int m = 0; m < MS; ++m) {
+                constexpr int NP = SWIGLU ? NS / 4 : NS / 2;
+                use(m);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    float v[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int j = 2 * p + (e >> 2);
+                        if constexpr (SWIGLU) v[e] = silu(acc[m][j][e & 3]) * acc[m][NS / 2 + j][e & 3];
+                        else v[e] = acc[m][j][e & 3];
+                    }
+                    const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
+                                     pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+                    __builtin_amdgcn_raw_buffer_store_b128(w, orsrc(p), vo + 64 * p, 0, 0);
+                }
+                vo += 32 * args.ldo;
+            }
+        }
+        since = 0;
+        if (!has_next) break;
+        q = qn;
+        cur = nxt;
+        start = !chain;
+        if (start) {
+            // the ring is idle before it is refilled
+            wait_vm<0>();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            rc = rsrc_of(cur, true);
+            since = 3;
+        }
     }
+    wait_vm<0>();                                // no direct load outlives the workgroup's LDS
+#endif
 }
 
 // ---------------------------------------------------------------------------
@@ -1165,10 +1169,18 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
     a1.split_units = grid < TILE_SPLIT_UNITS ? grid : TILE_SPLIT_UNITS;
     a1.a_rows = a_rows;
     a1.a_total = (int)a_total;
-    if (up && !small && a_rows)
-        hipLaunchKernelGGL((grouped_gemm_kernel<true, true>), dim3(grid), dim3(GEMM_THREADS), 0, s, a1);
-    else if (up && !small)
-        hipLaunchKernelGGL((grouped_gemm_kernel<true, false>), dim3(grid), dim3(GEMM_THREADS), 0, s, a1);
+    // the ring is dynamic LDS above the default limit
+#define MOE_TILED(SWIGLU, GATHER, args)                                                          \
+    do {                                                                                         \
+        static LdsGrant grant;                                                                   \
+        if (allow_dynamic_lds((const void*)grouped_gemm_kernel<SWIGLU, GATHER>, RING_BYTES,      \
+                              grant) != MOE_OK)                                                  \
+            return MOE_ERR_DEVICE;                                                               \
+        hipLaunchKernelGGL((grouped_gemm_kernel<SWIGLU, GATHER>), dim3(grid),                    \
+                           dim3(GEMM_THREADS), RING_BYTES, s, args);                             \
+    } while (0)
+    if (up && !small && a_rows) MOE_TILED(true, true, a1);
+    else if (up && !small) MOE_TILED(true, false, a1);
     StreamArgs s1;
     for (int i = 0; i < MOE_MAX_GROUPS; ++i) s1.w[i] = a1.w[i];
     s1.offsets = offsets;
@@ -1210,9 +1222,8 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
     a2.split_info = tinfo ? tinfo + 1 : nullptr;
     a2.product = 1;
     a2.a_rows = nullptr;
-    if (!small)
-        hipLaunchKernelGGL((grouped_gemm_kernel<false, false>), dim3(grid), dim3(GEMM_THREADS), 0, s,
-                           a2);
+    if (!small) MOE_TILED(false, false, a2);
+#undef MOE_TILED
     StreamArgs s2 = s1;
     for (int i = 0; i < MOE_MAX_GROUPS; ++i) s2.w[i] = a2.w[i];
     s2.a = h;
