@@ -27,6 +27,8 @@
 //   epilogue stores 8 bytes per lane (four columns of one row, gathered by a
 //   4 x 4 transpose inside each lane quad).  Group sizes are read on the
 //   device; empty groups produce no tiles, so their weights are never read.
+#include <type_traits>
+
 #include "common.h"
 
 namespace moe {
@@ -172,6 +174,33 @@ __device__ __forceinline__ void tile_starts(const int* s_off, int n_groups, int 
     if (lane == 0) s_tstart[0] = 0;
 }
 
+// Tile `local` of a group of mt x n_tiles tiles: the row tiles in blocks of at most
+// 8 (of equal size, give or take one), each block running through all column tiles,
+// rows first.  The 32 tiles an XCD works on at once then span about 8 row and 4
+// column slabs of operands, whatever the group's height (rows first over a whole
+// group of 32 row tiles, they span 32 + 1: an 8192-row expert's gate/up product at
+// d = f = 2048 x 2816 fetched twice the bytes).
+struct TilePos {
+    int m, n;
+};
+
+__device__ __forceinline__ TilePos tile_pos(int local, int mt, int n_tiles) {
+    const int nb = (mt + 7) >> 3;
+    const int base = mt / nb, extra = mt - base * nb;      // the first `extra` blocks have one more
+    const int big = extra * (base + 1) * n_tiles;
+    TilePos p;
+    if (local < big) {
+        const int b = local / ((base + 1) * n_tiles), l = local - b * (base + 1) * n_tiles;
+        p.n = l / (base + 1);
+        p.m = b * (base + 1) + l - p.n * (base + 1);
+    } else {
+        const int l0 = local - big, b = l0 / (base * n_tiles), l = l0 - b * base * n_tiles;
+        p.n = l / base;
+        p.m = extra * (base + 1) + b * base + l - p.n * base;
+    }
+    return p;
+}
+
 // Row limits of the streamed groups of the two products, run by one whole wave.
 // When the groups above SMALL_ROWS rows make so few tiles (a quarter of the
 // split units or fewer) that the tiled kernel would split K over them, its
@@ -311,10 +340,10 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
             const int kt0 = (int)((int64_t)kchunk * KT / S);
             const int s = last_le(s_tstart, n_groups, L);
             const int mt = (int)ceil_div(s_off[s + 1] - s_off[s], BM);
-            const int local = L - s_tstart[s];
-            const int nt = local / mt;
+            const TilePos pos = tile_pos(L - s_tstart[s], mt, args.n_tiles);
+            const int nt = pos.n;
             c.g = s;
-            c.row0 = s_off[s] + (local - nt * mt) * BM;
+            c.row0 = s_off[s] + pos.m * BM;
             c.rows_valid = min(BM, s_off[s + 1] - c.row0);
             c.n0 = nt * BN_OUT;
             c.kt0 = kt0 * (BK / SK);
@@ -426,40 +455,49 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
     };
     constexpr int STORES = SWIGLU ? MS * NS / 4 : MS * NS / 2;   // 16-byte stores of an epilogue
     unsigned c = 0;                              // stages run so far: stage slot c % RING
-    int since = 3;                               // stages since an epilogue (3: or more)
+    struct Source {                              // what the stages of a tile load
+        Rsrc own, next;
+        int av[A_LOADS], an[A_LOADS];
+        int kt_own, kt_next, own_end;            // stage t loads own K stage kt_own + t below
+    };                                           // own_end, then next's kt_next + t
     // one stage: multiply the fragments fa, fb (stage t), read those of stage t + 1
-    // into na, nb, load stage t + 4 (or its stand-in of the next tile)
-    auto stage = [&](const bf16x8* fa, const bf16x8* fb, bf16x8* na, bf16x8* nb, const Rsrc& r,
-                     const int* av, int kt) {
-        // stage t + 1 has landed: at most the loads of the two stages after it, and in
-        // the first stages after an epilogue its stores, are outstanding
-        if (since < 3) wait_vm<2 * LOADS + STORES>();
-        else wait_vm<2 * LOADS>();
+    // into na, nb, load stage t + 4 (past the tile's end: of the next tile).  WAIT:
+    // what may be outstanding once stage t + 1 has landed: the loads of the two stages
+    // after it, and in the first three stages of a tile the last epilogue's stores
+    auto stage = [&](auto wait, int t, const bf16x8* fa, const bf16x8* fb, bf16x8* na, bf16x8* nb,
+                     const Source& src) {
+        wait_vm<decltype(wait)::value>();
         // this wave's fragment reads of stage t are done
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        ++since;
-        // issue order, fixed: each of the next stage's 16 fragment reads before two
-        // MFMAs, each of the 8 loads before four
-        const int slot = c % RING;
+        const unsigned slot = c % RING;
         ++c;
         const char* st = ring + (c % RING) * STAGE_BYTES;
+        // issue order, fixed: one fragment read of the next stage before every three
+        // MFMAs (the reads are back well before the next barrier waits for them), a
+        // load before every six, each with the selection of its descriptor
+        const bool own = t < src.own_end;
+        const int kt = t + (own ? src.kt_own : src.kt_next);
+        Rsrc r;
 #pragma unroll
         for (int i = 0; i < MS + NS; ++i) {
             if (i < NS) nb[i] = *(const bf16x8*)(st + b_frag + b_tile(i) * ROWB);
             else na[i - NS] = *(const bf16x8*)(st + a_frag + (i - NS) * 16 * ROWB);
+            if (i == 1) r.a = own ? src.own.a : src.next.a;
+            if (i == 2 * A_LOADS + 1) r.lo = own ? src.own.lo : src.next.lo;
+            if (i == 2 * A_LOADS + B_LOADS + 1) r.hi = own ? src.own.hi : src.next.hi;
+            if (i & 1) {
+                const int q = i >> 1;
+                int av[A_LOADS];
+                if (q < A_LOADS) av[q] = !GATHER || own ? src.av[q] : src.an[q];
+                load1(r, av, kt, slot, q);
+            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 2 * i; u < 2 * i + 2; ++u) mfma(u, fa, fb);
+            for (int u = 3 * i; u < 3 * i + 3; ++u) mfma(u, fa, fb);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            load1(r, av, kt, slot, i);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 32 + 4 * i; u < 32 + 4 * i + 4; ++u) mfma(u, fa, fb);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int u = 3 * (MS + NS); u < MS * NS; ++u) mfma(u, fa, fb);
     };
 
     list_tiles(0);
@@ -482,7 +520,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
 #pragma unroll
                 for (int i = 0; i < LOADS; ++i)
                     load1(rc, avc, cur.kt0 + min(s, cur.nsteps - 1), (c + s) % RING, i);
-            wait_vm<3 * LOADS>();
+            // all four have landed: the first stages' waits allow for more
+            wait_vm<0>();
             asm volatile("s_barrier" ::: "memory");
             const char* st = ring + (c % RING) * STAGE_BYTES;
 #pragma unroll
@@ -508,30 +547,31 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
         for (int m = 0; m < MS; ++m) use(m);
         settle();
 
-        // the loads of stage t + 4: of this tile, or past its end of the next one
-        const Rsrc rn = rsrc_of(nxt, has_next && chain);
-        int avn[A_LOADS];
-        a_offsets(tok, avn);
-        const int kt_next = nxt.kt0 - (nsteps - RING);
-        auto step = [&](int t, const bf16x8* fa, const bf16x8* fb, bf16x8* na, bf16x8* nb) {
-            const bool own = t + RING < nsteps;
-            Rsrc r;
-            r.a = own ? rc.a : rn.a;
-            r.lo = own ? rc.lo : rn.lo;
-            r.hi = own ? rc.hi : rn.hi;
-            int av[A_LOADS];
+        Source src;
+        src.own = rc;
+        src.next = rsrc_of(nxt, has_next && chain);
 #pragma unroll
-            for (int i = 0; i < A_LOADS; ++i) av[i] = !GATHER || own ? avc[i] : avn[i];
-            stage(fa, fb, na, nb, r, av, t + (own ? cur.kt0 + RING : kt_next));
-        };
-        for (int t = 0; t < nsteps; t += 2) {
-            step(t, fa0, fb0, fa1, fb1);
-            step(t + 1, fa1, fb1, fa0, fb0);
+        for (int i = 0; i < A_LOADS; ++i) src.av[i] = avc[i];
+        a_offsets(tok, src.an);
+        src.own_end = nsteps - RING;
+        src.kt_own = cur.kt0 + RING;
+        src.kt_next = nxt.kt0 - src.own_end;
+        constexpr std::integral_constant<int, 2 * LOADS> loads{};
+        constexpr std::integral_constant<int, 2 * LOADS + STORES> loads_stores{};
+        stage(loads_stores, 0, fa0, fb0, fa1, fb1, src);
+        stage(loads_stores, 1, fa1, fb1, fa0, fb0, src);
+        if (nsteps > 2) {
+            stage(loads_stores, 2, fa0, fb0, fa1, fb1, src);
+            stage(loads, 3, fa1, fb1, fa0, fb0, src);
+        }
+        for (int t = 4; t < nsteps; t += 2) {
+            stage(loads, t, fa0, fb0, fa1, fb1, src);
+            stage(loads, t + 1, fa1, fb1, fa0, fb0, src);
         }
         settle();
-        rc = rn;
+        rc = src.next;
 #pragma unroll
-        for (int i = 0; i < A_LOADS; ++i) avc[i] = avn[i];
+        for (int i = 0; i < A_LOADS; ++i) avc[i] = src.an[i];
 
         // accumulator element r of tile (m, j) sits at output row m * 16 + lane % 16 of
         // the wave's rows; elements 0..3 of tiles 2 p and 2 p + 1 are columns 32 p + 8
@@ -588,7 +628,6 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
                 vo += 32 * args.ldo;
             }
         }
-        since = 0;
         if (!has_next) break;
         q = qn;
         cur = nxt;
@@ -598,7 +637,6 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
             wait_vm<0>();
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             rc = rsrc_of(cur, true);
-            since = 3;
         }
     }
     wait_vm<0>();                                // no direct load outlives the workgroup's LDS
@@ -894,10 +932,9 @@ __device__ void tile_split_reduce(const GemmArgs& t, int* s_off, int* s_tstart) 
         const int row = rem / C4, j = (rem - row * C4) * 4;
         const int g = last_le(s_tstart, n_groups, L);
         const int rows = s_off[g + 1] - s_off[g];
-        const int mt = (int)ceil_div(rows, BM);
-        const int local = L - s_tstart[g];
-        const int nt = local / mt;
-        const int m0 = (local - nt * mt) * BM;
+        const TilePos pos = tile_pos(L - s_tstart[g], (int)ceil_div(rows, BM), t.n_tiles);
+        const int nt = pos.n;
+        const int m0 = pos.m * BM;
         if (m0 + row >= rows) continue;
         const int n0 = nt * BN_OUT;
         if (n0 + j >= t.N) continue;
