@@ -34,6 +34,7 @@
 namespace moe {
 namespace {
 
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 256;          // rows per tile
@@ -691,6 +692,7 @@ struct StreamArgs {
     const int* limits;                   // row limits written by the gate/up tiled launch (nullptr:
     int product;                         // lim0); this product's index, 0 gate/up, 1 down
     int lim0;                            // row limit of streamed groups when limits is nullptr
+    int zero_big;                        // strips: rows of groups above the limit get zeros
 };
 
 struct StreamPlan {
@@ -869,6 +871,171 @@ __global__ __launch_bounds__(ST_THREADS, ST_WG_PER_CU) void stream_gemm_kernel(S
         }
         __syncthreads();                             // s_item and LDS reuse by the next item
     }
+}
+
+// ---------------------------------------------------------------------------
+// Strips: the streamed groups' products where K is short (strip_product): one
+// launch, no split of K over workgroups, no partial sums and no launch to add
+// them.  A workgroup takes M rows of a group x 64 weight rows (SwiGLU: 32 gate and
+// the matching 32 up rows) over the whole of K; both operands go straight into an
+// LDS ring of R 64-wide K stages, R - 1 in flight.  What bounds it: at decode the
+// latency of the launch and of the first loads, then the weight stream; an item of
+// the split kernel reads a few K steps only and pays for the partial sums' round
+// trip and the second launch.  Waves 2 x 2, each M / 2 rows x 32 weight rows;
+// 128-byte LDS rows, 16-byte chunk c of row r at c ^ (r & 7) (conflict-free for the
+// fragment reads); weights as the MFMA's A operand, so a lane holds 4 consecutive
+// output columns of one row.  Every sum runs over K in ascending stages, whatever
+// M and R, so the choice of shape does not change the bits.
+// ---------------------------------------------------------------------------
+constexpr int SP_N = 64;                 // weight rows per tile
+constexpr int SP_THREADS = 256;
+constexpr int SP_ROWB = 128;             // LDS row bytes: 64 K
+constexpr int STRIP_MAX_K = 2048;
+
+template <bool SWIGLU, bool GATHER, int M, int R>
+__global__ __launch_bounds__(SP_THREADS, 2) void strip_gemm_kernel(StreamArgs args) {
+#ifdef __HIP_DEVICE_COMPILE__
+    extern __shared__ __attribute__((aligned(1024))) char strip_ring[];
+    __shared__ int s_off[MOE_MAX_GROUPS + 1], s_tstart[MOE_MAX_GROUPS + 1];
+    constexpr int SA = M * SP_ROWB, STAGE = SA + SP_N * SP_ROWB;
+    constexpr int NA = M / 32, NB = SP_N / 32, P = NA + NB;    // 1 KB loads per wave per stage
+    constexpr int MT = M / 32;                                 // 16-row tiles per wave
+    constexpr int OUT = SWIGLU ? SP_N / 2 : SP_N;              // output columns per tile
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1;
+    const int n_groups = args.n_groups, K = args.K;
+    const int n_out = SWIGLU ? args.N / 2 : args.N;
+    const int nt = n_out / OUT;
+    const int lim = args.limits != nullptr ? args.limits[args.product] : args.lim0;
+    for (int g = tid; g <= n_groups; g += SP_THREADS)
+        s_off[g] = group_start(args.offsets, args.lead, args.lead_rows, g);
+    __syncthreads();
+    if (wave == 0) {
+        int carry = 0;
+        for (int g0 = 0; g0 < n_groups; g0 += 64) {
+            const int g = g0 + lane;
+            const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
+            const int v = rows <= lim || args.zero_big ? (int)ceil_div(rows, M) * nt : 0;
+            const int incl = wave_incl_scan(v, lane);
+            if (g < n_groups) s_tstart[g + 1] = carry + incl;
+            carry += __shfl(incl, 63, 64);
+        }
+        if (lane == 0) s_tstart[0] = 0;
+    }
+    __syncthreads();
+    // contiguous tiles per XCD: the row tiles of a weight strip share its L2
+    const int total = s_tstart[n_groups];
+    const int per = (total + NUM_XCD - 1) / NUM_XCD;
+    const int t_begin = (blockIdx.x % NUM_XCD) * per, t_end = min(t_begin + per, total);
+    // load i of a wave fills LDS rows 32 i + 8 wave + lane / 8, chunk slot lane % 8
+    const int lrow = 8 * wave + (lane >> 3);
+    const int kc = ((lane & 7) ^ ((lane >> 3) & 7)) * 8;
+    const int wvoff = ((SWIGLU ? lrow : w_order(lrow)) * K + kc) * 2;
+    const int frow = lane & 15;
+    const int c0 = ((lane >> 4) ^ (frow & 7)) * 16, c1 = c0 ^ 64;
+    const int a_frag = (wm * (M / 2) + frow) * SP_ROWB;
+    const int b_frag = SA + (wn * (SWIGLU ? 16 : 32) + frow) * SP_ROWB;
+    constexpr int B_STEP = (SWIGLU ? 32 : 16) * SP_ROWB;       // second column tile
+
+    for (int tile = t_begin + blockIdx.x / NUM_XCD; tile < t_end; tile += gridDim.x / NUM_XCD) {
+        const int g = __builtin_amdgcn_readfirstlane(last_le(s_tstart, n_groups, tile));
+        const int start = __builtin_amdgcn_readfirstlane(s_off[g]);
+        const int rows = __builtin_amdgcn_readfirstlane(s_off[g + 1]) - start;
+        const int mt = (rows + M - 1) / M;
+        const int local = tile - __builtin_amdgcn_readfirstlane(s_tstart[g]);
+        const int m = local % mt, n0 = (local / mt) * OUT;
+        const int row0 = start + m * M, rows_valid = min(M, rows - m * M);
+        const int nst = rows <= lim ? K / 64 : 0;
+        // rows past the group read as zero or leave LDS as it is: not stored either way
+        const __amdgpu_buffer_rsrc_t ar =
+            GATHER ? __builtin_amdgcn_make_buffer_rsrc((void*)args.a, (short)0, args.a_total * K * 2,
+                                                      RSRC_WORD3)
+                   : __builtin_amdgcn_make_buffer_rsrc((void*)(args.a + (int64_t)row0 * K), (short)0,
+                                                      rows_valid * K * 2, RSRC_WORD3);
+        const bf16_t* W = args.w[g] + (int64_t)n0 * K;
+        const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)W, (short)0, (SWIGLU ? 32 : SP_N) * K * 2, RSRC_WORD3);
+        const __amdgpu_buffer_rsrc_t ur = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(W + (int64_t)(SWIGLU ? n_out : 0) * K), (short)0, (SWIGLU ? 32 : SP_N) * K * 2,
+            RSRC_WORD3);
+        int av[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int rin = lrow + 32 * i;
+            av[i] = !GATHER ? (rin * K + kc) * 2
+                    : rin < rows_valid ? (args.a_rows[row0 + rin] * K + kc) * 2 : A_OOB;
+        }
+        auto dma = [&](int s) {
+            char* base = strip_ring + (s % R) * STAGE + wave * 1024;
+            const int so = s * SP_ROWB;
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    SWIGLU && i ? ur : br, (lds_void*)(base + SA + i * 4096), 16,
+                    wvoff + (SWIGLU ? 0 : i * 64 * K), so, 0, 0);
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_void*)(base + i * 4096), 16, av[i], so,
+                                                         0, 0);
+        };
+        f32x4 acc[MT][2];
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < R - 1; ++s)
+            if (s < nst) dma(s);
+        for (int t = 0; t < nst; ++t) {
+            // stage t has landed; the R - 2 after it may still fly
+            if (nst - 1 - t >= R - 2) wait_vm<(R - 2) * P>();
+            else wait_vm<0>();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (t + R - 1 < nst) dma(t + R - 1);
+            const char* st = strip_ring + (t % R) * STAGE;
+            // row tiles past the group are left out (uniform across the wave)
+            const int live = rows_valid - wm * (M / 2);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int cq = q ? c1 : c0;
+                const bf16x8 b0 = *(const bf16x8*)(st + b_frag + cq);
+                const bf16x8 b1 = *(const bf16x8*)(st + b_frag + B_STEP + cq);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    if (i * 16 >= live) break;
+                    const bf16x8 a = *(const bf16x8*)(st + a_frag + i * 16 * SP_ROWB + cq);
+                    acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b0, a, acc[i][0], 0, 0, 0);
+                    acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a, acc[i][1], 0, 0, 0);
+                }
+            }
+        }
+        const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(args.out + (int64_t)row0 * args.ldo), (short)0, rows_valid * args.ldo * 2,
+            RSRC_WORD3);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int row_in = wm * (M / 2) + i * 16 + frow;
+            if constexpr (SWIGLU) {
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = silu(acc[i][0][r]) * acc[i][1][r];
+                const u32x2 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+                __builtin_amdgcn_raw_buffer_store_b64(
+                    w, orsrc, (row_in * args.ldo + n0 + wn * 16 + (lane >> 4) * 4) * 2, 0, 0);
+            } else {
+                const u32x4 w = {pack_bf16x2(acc[i][0][0], acc[i][0][1]),
+                                 pack_bf16x2(acc[i][0][2], acc[i][0][3]),
+                                 pack_bf16x2(acc[i][1][0], acc[i][1][1]),
+                                 pack_bf16x2(acc[i][1][2], acc[i][1][3])};
+                __builtin_amdgcn_raw_buffer_store_b128(
+                    w, orsrc, (row_in * args.ldo + n0 + wn * 32 + (lane >> 4) * 8) * 2, 0, 0);
+            }
+        }
+        // every wave is done with the ring before the next tile refills it
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+#endif
 }
 
 // Adds chunks [c, c + RU) of a partial sum to x (SWIGLU: the up half, `up`
@@ -1140,6 +1307,35 @@ size_t grouped_ffn_ws_bytes(int dtype, int64_t cap_rows, int d, int f, int n_gro
     return (size_t)(h + part + tile_part_bytes(cap_rows) + 256);
 }
 
+// Whether the streamed groups of a product run as strips: K short enough for one
+// workgroup to walk, and a call whose rows may all lie in streamed groups (which
+// also bounds the rows the fused combine keeps in the workspace).  A longer K (the
+// Mixtral-shaped layers' 4096 and 14336) leaves too few strips of too long a chain:
+// there K is split over workgroups.
+static bool strip_product(int K, int64_t cap_rows, int n_groups) {
+    return K <= STRIP_MAX_K && cap_rows <= (int64_t)SMALL_ROWS_MAX * n_groups;
+}
+
+template <bool SWIGLU, bool GATHER>
+static int launch_strips(const StreamArgs& a, int64_t max_rows, int cus, hipStream_t s) {
+    const dim3 grid((unsigned)(2 * cus / NUM_XCD * NUM_XCD)), block(SP_THREADS);
+    // groups of at most 64 rows (max_rows bounds them): half the rows per tile, one
+    // stage more in flight in the same LDS
+#define MOE_STRIPS(M, R)                                                                         \
+    do {                                                                                         \
+        static LdsGrant grant;                                                                   \
+        constexpr int lds = R * (M + SP_N) * SP_ROWB;                                            \
+        if (allow_dynamic_lds((const void*)strip_gemm_kernel<SWIGLU, GATHER, M, R>, lds,         \
+                              grant) != MOE_OK)                                                  \
+            return MOE_ERR_DEVICE;                                                               \
+        hipLaunchKernelGGL((strip_gemm_kernel<SWIGLU, GATHER, M, R>), grid, block, lds, s, a);   \
+    } while (0)
+    if (max_rows <= 64) MOE_STRIPS(64, 4);
+    else MOE_STRIPS(128, 3);
+#undef MOE_STRIPS
+    return MOE_OK;
+}
+
 int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, int n_groups,
                        const void* const* w13, const void* const* w2, int d, int f,
                        int64_t cap_rows, void* y_perm, void* ws, hipStream_t s,
@@ -1237,12 +1433,30 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
     s1.limits = a1.limits;
     s1.product = 0;
     s1.lim0 = a1.lim0;
+    s1.zero_big = 0;
+    // a group's rows: at most every token once where the row map tells their number
+    const int64_t max_rows = a_rows && a_total < cap_rows ? a_total : cap_rows;
+    // the chunk sums' launch: nothing streamed to add up when the strips did it
+    auto reduce_args = [](StreamArgs r, bool strips) {
+        if (strips) {
+            r.limits = nullptr;
+            r.lim0 = 0;
+        }
+        return r;
+    };
+    const bool strips1 = strip_product(d, cap_rows, n_groups);
     if (up) {
-        if (!large && a_rows)
+        if (!large && strips1) {
+            const int st = a_rows ? launch_strips<true, true>(s1, max_rows, cus, s)
+                                  : launch_strips<true, false>(s1, max_rows, cus, s);
+            if (st != MOE_OK) return st;
+        } else if (!large && a_rows)
             hipLaunchKernelGGL(stream_gemm_kernel<true>, dim3(sgrid), dim3(ST_THREADS), 0, s, s1);
         else if (!large)
             hipLaunchKernelGGL(stream_gemm_kernel<false>, dim3(sgrid), dim3(ST_THREADS), 0, s, s1);
-        hipLaunchKernelGGL(split_reduce_kernel<true>, dim3(rgrid), dim3(ST_THREADS), 0, s, s1, a1);
+        if (!strips1 || tpart != nullptr)
+            hipLaunchKernelGGL(split_reduce_kernel<true>, dim3(rgrid), dim3(ST_THREADS), 0, s,
+                               reduce_args(s1, strips1), a1);
     }
     if (!down) return launch_status();
 
@@ -1270,10 +1484,28 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
     s2.ldo = d;
     s2.a_rows = nullptr;
     s2.product = 1;
-    if (!large)
+    const bool strips2 = strip_product(f, cap_rows, n_groups);
+    if (strips2 && !large) {
+        if (combine != nullptr) {
+            // the fused combine's y_perm: the partial sums' place (at most 256 rows a
+            // group: 512 n d bytes of at least 2048 n d, or 2 of 32 d bytes a row), rows
+            // of groups above the limit zeroed, which leaves them out of the sum
+            s2.out = (bf16_t*)part;
+            s2.zero_big = 1;
+        }
+        const int st = launch_strips<false, false>(s2, max_rows, cus, s);
+        if (st != MOE_OK) return st;
+        if (combine != nullptr) {
+            const CombineArgs& cb = *(const CombineArgs*)combine;
+            return launch_combine(part, MOE_BF16, cb.token_row, cb.gate, cb.y_shared, 1, cb.T, d,
+                                  cb.k, cb.y, s);
+        }
+    } else if (!large)
         hipLaunchKernelGGL(stream_gemm_kernel<false>, dim3(sgrid), dim3(ST_THREADS), 0, s, s2);
     if (combine == nullptr) {
-        hipLaunchKernelGGL(split_reduce_kernel<false>, dim3(rgrid), dim3(ST_THREADS), 0, s, s2, a2);
+        if (!strips2 || tpart != nullptr)
+            hipLaunchKernelGGL(split_reduce_kernel<false>, dim3(rgrid), dim3(ST_THREADS), 0, s,
+                               reduce_args(s2, strips2), a2);
         return launch_status();
     }
     // the down product's chunk sum writes the combined output (every group streamed)
