@@ -185,6 +185,28 @@ int moe_permute_noalloc(const void* x, int dtype, const int32_t* topk_idx,
                         int64_t cap_rows, int32_t* group_offsets, int32_t* row_token,
                         float* row_gate, int32_t* token_row, int32_t* send_counts, void* stream);
 
+/*
+ * moe_route_package -- moe_route_topk, moe_expert_histogram and moe_permute of
+ * one batch in one call (Sec. II-A, II-B, VI-A): the same outputs, bit for bit,
+ * in fewer launches where the batch is short (a decode step's routing is two).
+ *
+ * x, dtype, w_router, bias, T, d, E, k, flags, logits, topk_idx, topk_gate,
+ *           ws_route, ws_route_bytes as for moe_route_topk
+ * counts, coact (nullable) as for moe_expert_histogram
+ * placement .. send_counts, ws_perm, ws_perm_bytes as for moe_permute; x_perm
+ *           NULL writes the row maps only (moe_permute with d = 0)
+ * Requirements and errors as for the three calls; with MOE_LOGITS_IN and no row
+ * copy x and w_router are not read and may be NULL.
+ */
+int moe_route_package(const void* x, int dtype, const void* w_router, const float* bias,
+                      int64_t T, int d, int E, int k, int flags, float* logits,
+                      int32_t* topk_idx, float* topk_gate, void* ws_route,
+                      size_t ws_route_bytes, int32_t* counts, int32_t* coact,
+                      const uint8_t* placement, int G, int dev, int c_max, void* x_perm,
+                      int64_t cap_rows, int32_t* group_offsets, int32_t* row_token,
+                      float* row_gate, int32_t* token_row, int32_t* send_counts, void* ws_perm,
+                      size_t ws_perm_bytes, void* stream);
+
 /* Workspace bytes moe_grouped_ffn needs. */
 size_t moe_grouped_ffn_ws_bytes(int dtype, int64_t cap_rows, int d, int f, int n_groups);
 

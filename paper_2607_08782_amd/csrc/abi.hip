@@ -11,6 +11,32 @@ using namespace moe;
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
+// Validation shared by moe_route_topk and moe_route_package.
+int route_check(const void* x, int dtype, const void* w_router, int64_t T, int d, int E, int k,
+                int flags, const float* logits, const int32_t* topk_idx, const float* topk_gate,
+                const void* ws, size_t ws_bytes) {
+    if (T < 0 || E < 1 || E > MOE_MAX_E || k < 1 || k > MOE_MAX_K || k > E) return MOE_ERR_ARG;
+    if (flags & ~(MOE_RENORM | MOE_LOGITS_IN)) return MOE_ERR_ARG;
+    if (T > (int64_t)0x7fffffff * 16) return MOE_ERR_ARG;
+    if (T > 0 && (!topk_idx || !topk_gate)) return MOE_ERR_ARG;
+    if (flags & MOE_LOGITS_IN) {
+        if (T > 0 && !logits) return MOE_ERR_ARG;
+    } else {
+        if (dtype != MOE_F32 && dtype != MOE_BF16) return MOE_ERR_ARG;
+        if (d < 1) return MOE_ERR_ARG;
+        if (T > 0 && (!x || !w_router)) return MOE_ERR_ARG;
+        if (dtype == MOE_BF16) {
+            if (d % 8) return MOE_ERR_SHAPE;
+            // the router matrix is addressed through one 32-bit buffer descriptor
+            if ((int64_t)E * d * 2 > 0x7fffffffLL) return MOE_ERR_SHAPE;
+            if (!aligned16(x) || !aligned16(w_router)) return MOE_ERR_ARG;
+        }
+    }
+    const size_t need = route_ws_bytes(dtype, T, d, E, flags);
+    if (need > 0 && (!ws || ws_bytes < need || ((uintptr_t)ws & 255u))) return MOE_ERR_SHAPE;
+    return MOE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -34,25 +60,9 @@ size_t moe_route_topk_ws_bytes(int dtype, int64_t T, int d, int E, int flags) {
 int moe_route_topk(const void* x, int dtype, const void* w_router, const float* bias, int64_t T,
                    int d, int E, int k, int flags, float* logits, int32_t* topk_idx,
                    float* topk_gate, void* ws, size_t ws_bytes, void* stream) {
-    if (T < 0 || E < 1 || E > MOE_MAX_E || k < 1 || k > MOE_MAX_K || k > E) return MOE_ERR_ARG;
-    if (flags & ~(MOE_RENORM | MOE_LOGITS_IN)) return MOE_ERR_ARG;
-    if (T > (int64_t)0x7fffffff * 16) return MOE_ERR_ARG;
-    if (T > 0 && (!topk_idx || !topk_gate)) return MOE_ERR_ARG;
-    if (flags & MOE_LOGITS_IN) {
-        if (T > 0 && !logits) return MOE_ERR_ARG;
-    } else {
-        if (dtype != MOE_F32 && dtype != MOE_BF16) return MOE_ERR_ARG;
-        if (d < 1) return MOE_ERR_ARG;
-        if (T > 0 && (!x || !w_router)) return MOE_ERR_ARG;
-        if (dtype == MOE_BF16) {
-            if (d % 8) return MOE_ERR_SHAPE;
-            // the router matrix is addressed through one 32-bit buffer descriptor
-            if ((int64_t)E * d * 2 > 0x7fffffffLL) return MOE_ERR_SHAPE;
-            if (!aligned16(x) || !aligned16(w_router)) return MOE_ERR_ARG;
-        }
-    }
-    const size_t need = route_ws_bytes(dtype, T, d, E, flags);
-    if (need > 0 && (!ws || ws_bytes < need || ((uintptr_t)ws & 255u))) return MOE_ERR_SHAPE;
+    const int st = route_check(x, dtype, w_router, T, d, E, k, flags, logits, topk_idx, topk_gate,
+                               ws, ws_bytes);
+    if (st != MOE_OK) return st;
     return launch_route_topk(x, dtype, w_router, bias, T, d, E, k, flags, logits, topk_idx,
                              topk_gate, ws, (hipStream_t)stream);
 }
@@ -132,6 +142,31 @@ int moe_permute(const void* x, int dtype, const int32_t* topk_idx, const float* 
     return launch_permute(x, dtype, topk_idx, topk_gate, counts, T, d, k, E, tab, n_local, G, dev,
                           x_perm, cap_rows, group_offsets, row_token, row_gate, token_row,
                           send_counts, ws, (hipStream_t)stream);
+}
+
+int moe_route_package(const void* x, int dtype, const void* w_router, const float* bias,
+                      int64_t T, int d, int E, int k, int flags, float* logits,
+                      int32_t* topk_idx, float* topk_gate, void* ws_route,
+                      size_t ws_route_bytes, int32_t* counts, int32_t* coact,
+                      const uint8_t* placement, int G, int dev, int c_max, void* x_perm,
+                      int64_t cap_rows, int32_t* group_offsets, int32_t* row_token,
+                      float* row_gate, int32_t* token_row, int32_t* send_counts, void* ws_perm,
+                      size_t ws_perm_bytes, void* stream) {
+    int st = route_check(x, dtype, w_router, T, d, E, k, flags, logits, topk_idx, topk_gate,
+                         ws_route, ws_route_bytes);
+    if (st != MOE_OK) return st;
+    PermuteTables tab;
+    int n_local = 0;
+    st = permute_check(x, dtype, topk_idx, topk_gate, counts, T, x_perm ? d : 0, k, E, placement, G,
+                       dev, c_max, x_perm, cap_rows, group_offsets, row_token, row_gate, token_row,
+                       tab, n_local);
+    if (st != MOE_OK) return st;
+    if (!ws_perm || ws_perm_bytes < permute_ws_bytes(T, k, E) || ((uintptr_t)ws_perm & 255u))
+        return MOE_ERR_SHAPE;
+    return launch_route_package(x, dtype, w_router, bias, T, d, E, k, flags, logits, topk_idx,
+                                topk_gate, ws_route, counts, coact, tab, n_local, G, dev, x_perm,
+                                cap_rows, group_offsets, row_token, row_gate, token_row,
+                                send_counts, ws_perm, (hipStream_t)stream);
 }
 
 int moe_permute_noalloc(const void* x, int dtype, const int32_t* topk_idx,

@@ -101,6 +101,11 @@ inline int allow_dynamic_lds(size_t bytes) {
 int launch_route_topk(const void* x, int dtype, const void* w, const float* bias, int64_t T, int d,
                       int E, int k, int flags, float* logits, int32_t* idx, float* gate, void* ws,
                       hipStream_t s);
+// bf16 scores of a short batch (route.hip): whether a batch takes them, and the launch
+// (scores + bias to out[T][E])
+bool route_short(int64_t T, int d, int E);
+int launch_scores_short(const void* x, const void* w, const float* bias, int64_t T, int d, int E,
+                        float* out, hipStream_t s);
 size_t route_ws_bytes(int dtype, int64_t T, int d, int E, int flags);
 
 int launch_quantize_e4m3(const void* x, int dtype, int64_t rows, int cols, uint8_t* q, float* scales,
@@ -141,6 +146,13 @@ int launch_permute(const void* x, int dtype, const int32_t* idx, const float* ga
                    int32_t* group_offsets, int32_t* row_token, float* row_gate, int32_t* token_row,
                    int32_t* send_counts, void* ws, hipStream_t s);
 size_t permute_ws_bytes(int64_t T, int k, int E);
+// route_topk, histogram and permute in one call (x_perm null: no row copy)
+int launch_route_package(const void* x, int dtype, const void* w, const float* bias, int64_t T,
+                         int d, int E, int k, int flags, float* logits, int32_t* idx, float* gate,
+                         void* ws_route, int32_t* counts, int32_t* coact, const PermuteTables& tab,
+                         int n_local, int G, int dev, void* x_perm, int64_t cap_rows,
+                         int32_t* group_offsets, int32_t* row_token, float* row_gate,
+                         int32_t* token_row, int32_t* send_counts, void* ws_perm, hipStream_t s);
 // Device address of the library's own permute scratch on the current device
 // (MOE_PERMUTE_NOALLOC_MAX_WS bytes, 256-byte aligned).
 int permute_scratch(void** ptr);

@@ -14,6 +14,7 @@
 //   gather   x_perm[p] = x[row_token[p]], 16-byte vector copies
 // Every step is integer arithmetic, so the result is exact and unique.
 #include "common.h"
+#include "topk.h"
 
 namespace moe {
 namespace {
@@ -251,41 +252,110 @@ __global__ __launch_bounds__(PERM_TOKENS) void perm_scatter_kernel(
 // Short batches (at most SMALL_T tokens): count, scan and scatter in one
 // workgroup, one wave per 64-token block, the same arithmetic as the three
 // kernels above (so the same unique result), one launch instead of three.
+// COUNT: the expert counts (and, with coact, the co-activation counts, E * E bins in
+// dynamic LDS) are taken here too instead of read from `counts`: one launch instead
+// of the histogram's and this one.  KM > 0 (COUNT, at most PLAN_IDS assignments): the
+// top-k (k <= KM, top-k class C) of `scores` as well, so a decode step's routing is
+// this launch after the scores.  Bound by the latency of one workgroup's chain of
+// loads and barriers; each launch saved is 4-8 us of a decode step.
 constexpr int SMALL_T = 1024;
 constexpr int SMALL_BLK = SMALL_T / PERM_TOKENS;
+constexpr int PLAN_IDS = 4096;
 
-__global__ __launch_bounds__(SMALL_T) void perm_small_kernel(
-    const int32_t* __restrict__ idx, const float* __restrict__ gate,
-    const int32_t* __restrict__ counts, int64_t T, int k, int E, SlotTable st, HostTable ht,
-    int n_local, int G, int dev, int32_t* __restrict__ group_offsets,
-    int32_t* __restrict__ row_token, float* __restrict__ row_gate, int32_t* __restrict__ token_row,
-    int32_t* __restrict__ send_counts) {
+struct SmallArgs {
+    const int32_t* idx;                  // [T][k] (KM == 0)
+    const float* gate;
+    const int32_t* counts_in;            // [E] (!COUNT)
+    int32_t* counts;                     // [E] (COUNT)
+    int32_t* coact;                      // [E][E], nullable (COUNT)
+    const float* scores;                 // [T][E], bias added (KM > 0)
+    int32_t* idx_out;                    // [T][k] (KM > 0)
+    float* gate_out;
+    int renorm;
+    int T, k, E, n_local, G, dev;
+    int32_t* group_offsets;
+    int32_t* row_token;
+    float* row_gate;
+    int32_t* token_row;
+    int32_t* send_counts;
+};
+
+template <bool COUNT, int KM = 0, int C = 0>
+__global__ __launch_bounds__(SMALL_T) void perm_small_kernel(SmallArgs a, SlotTable st,
+                                                             HostTable ht) {
     __shared__ unsigned long long bits[SMALL_BLK][MOE_MAX_GROUPS];
     __shared__ int32_t base[SMALL_BLK][MOE_MAX_GROUPS];
     __shared__ int16_t slot_lds[MOE_MAX_E];
     __shared__ uint64_t hosts_s[MOE_MAX_E];
     __shared__ int32_t cnt_s[MOE_MAX_E], send_s[MOE_MAX_G];
     __shared__ int32_t lo_s[MOE_MAX_GROUPS], size_s[MOE_MAX_GROUPS], off_s[MOE_MAX_GROUPS + 1];
+    __shared__ int32_t ids_s[KM > 0 ? PLAN_IDS : 1];
+    __shared__ float gates_s[KM > 0 ? PLAN_IDS : 1];
+    extern __shared__ __attribute__((aligned(16))) int32_t co_s[];   // [E][E] with coact
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int T = a.T, k = a.k, E = a.E, n_local = a.n_local;
     const int nblk = (int)ceil_div(T, PERM_TOKENS);
-    const int64_t t = (int64_t)wave * PERM_TOKENS + lane;
+    const int t = tid;
     int ev[MOE_MAX_K];
     float gv[MOE_MAX_K];
-    if (t < T) {
-        load_ids(idx, t, k, ev);
-        load_gates(gate, t, k, gv);
+    if (KM == 0 && t < T) {
+        load_ids(a.idx, t, k, ev);
+        load_gates(a.gate, t, k, gv);
     }
     for (int e = tid; e < E; e += SMALL_T) {
         slot_lds[e] = st.slot_of[e];
-        cnt_s[e] = counts[e];
+        cnt_s[e] = COUNT ? 0 : a.counts_in[e];
         hosts_s[e] = ht.hosts[e];
     }
     if (tid < MOE_MAX_G) send_s[tid] = 0;
     for (int i = tid; i < SMALL_BLK * MOE_MAX_GROUPS; i += SMALL_T)
         bits[i / MOE_MAX_GROUPS][i % MOE_MAX_GROUPS] = 0ull;
+    const bool coact = COUNT && a.coact != nullptr;
+    if (coact)
+        for (int i = tid; i < E * E; i += SMALL_T) co_s[i] = 0;
+    if constexpr (KM > 0) topk_tokens<KM, C, 1>(a.scores, E, T, 0, E, k, a.renorm, ids_s, gates_s);
     __syncthreads();
+    if (KM > 0 && t < T) {
+#pragma unroll
+        for (int r = 0; r < MOE_MAX_K; ++r) {
+            ev[r] = ids_s[t * k + (r < k ? r : k - 1)];
+            gv[r] = gates_s[t * k + (r < k ? r : k - 1)];
+        }
+    }
+    if (KM > 0)
+        for (int i = tid; i < T * k; i += SMALL_T) {
+            a.idx_out[i] = ids_s[i];
+            a.gate_out[i] = gates_s[i];
+        }
     set_bits(ev, t < T, k, E, slot_lds, bits[wave], lane);
-    if (send_counts) add_send_counts(cnt_s, hosts_s, E, tid, SMALL_T, send_s);
+    if (COUNT && t < T) {
+#pragma unroll
+        for (int r = 0; r < MOE_MAX_K; ++r) {
+            if (r >= k) break;
+            // out-of-range expert ids are ignored rather than counted out of bounds
+            if ((unsigned)ev[r] < (unsigned)E) atomicAdd(&cnt_s[ev[r]], 1);
+        }
+    }
+    if (coact) {
+        // thread i takes assignment (i / k, i % k) and adds its row of the token's k x k
+        // block
+        const int32_t* ids = KM > 0 ? ids_s : a.idx;
+        for (int i = tid; i < T * k; i += SMALL_T) {
+            const int tok = i / k;
+            const int e = ids[i];
+            if ((unsigned)e >= (unsigned)E) continue;
+            for (int q = 0; q < k; ++q) {
+                const int e2 = ids[tok * k + q];
+                if ((unsigned)e2 < (unsigned)E) atomicAdd(&co_s[e * E + e2], 1);
+            }
+        }
+    }
+    if (COUNT) __syncthreads();
+    if (a.send_counts) add_send_counts(cnt_s, hosts_s, E, tid, SMALL_T, send_s);
+    if (COUNT)
+        for (int e = tid; e < E; e += SMALL_T) a.counts[e] = cnt_s[e];
+    if (coact)
+        for (int i = tid; i < E * E; i += SMALL_T) a.coact[i] = co_s[i];
     __syncthreads();
     if (tid < n_local) {
         int32_t run = 0;
@@ -296,16 +366,16 @@ __global__ __launch_bounds__(SMALL_T) void perm_small_kernel(
         const int e = ht.expert_of_slot[tid];
         const uint64_t h = hosts_s[e];
         const int n = __popcll(h);
-        const int q = dev == 0 ? 0 : __popcll(h & (~0ull >> (64 - dev)));
+        const int q = a.dev == 0 ? 0 : __popcll(h & (~0ull >> (64 - a.dev)));
         const int64_t lo = replica_lo(q, cnt_s[e], n);
         lo_s[tid] = (int32_t)lo;
         size_s[tid] = (int32_t)(replica_lo(q + 1, cnt_s[e], n) - lo);
     }
-    if (send_counts && tid < G) send_counts[tid] = send_s[tid];
+    if (a.send_counts && tid < a.G) a.send_counts[tid] = send_s[tid];
     __syncthreads();
     if (wave == 0) wave_offsets(size_s, n_local, off_s, lane);
     __syncthreads();
-    for (int sl = tid; sl <= n_local; sl += SMALL_T) group_offsets[sl] = off_s[sl];
+    for (int sl = tid; sl <= n_local; sl += SMALL_T) a.group_offsets[sl] = off_s[sl];
     if (t >= T) return;
     const unsigned long long lower = (1ull << lane) - 1ull;
 #pragma unroll
@@ -319,11 +389,11 @@ __global__ __launch_bounds__(SMALL_T) void perm_small_kernel(
             const int32_t lo = lo_s[sl];
             if (rank >= lo && rank < lo + size_s[sl]) {
                 p = off_s[sl] + (rank - lo);
-                row_token[p] = (int32_t)t;
-                row_gate[p] = gv[r];
+                a.row_token[p] = t;
+                a.row_gate[p] = gv[r];
             }
         }
-        token_row[t * k + r] = p;
+        a.token_row[t * k + r] = p;
     }
 }
 
@@ -377,6 +447,40 @@ size_t permute_ws_bytes(int64_t T, int k, int E) {
     return (size_t)(nblk * slots + MOE_MAX_GROUPS) * sizeof(int32_t) + 256;
 }
 
+static void fill_tables(const PermuteTables& tabs, SlotTable& st, HostTable& ht) {
+    for (int e = 0; e < MOE_MAX_E; ++e) {
+        st.slot_of[e] = tabs.slot_of[e];
+        ht.hosts[e] = tabs.hosts[e];
+    }
+    for (int i = 0; i < MOE_MAX_GROUPS; ++i) ht.expert_of_slot[i] = tabs.expert_of_slot[i];
+}
+
+// x_perm[p] = x[row_token[p]] for the rows the maps hold (nothing when d = 0)
+static void launch_gather_rows(const void* x, int dtype, int64_t T, int d, int k, int n_local,
+                               void* x_perm, int64_t cap_rows, const int32_t* group_offsets,
+                               const int32_t* row_token, hipStream_t s) {
+    if (T <= 0 || n_local <= 0 || d <= 0) return;
+    const size_t row_bytes = (size_t)d * (dtype == MOE_BF16 ? 2 : 4);
+    int64_t max_rows = cap_rows;
+    if (max_rows > T * (int64_t)k) max_rows = T * (int64_t)k;
+    int64_t blocks = ceil_div(max_rows, 4);
+    if (blocks > 4096) blocks = 4096;
+    if (blocks < 1) blocks = 1;
+    const int32_t* total = group_offsets + n_local;
+    if (row_bytes % 16 == 0)
+        hipLaunchKernelGGL(gather_rows_kernel<uint4>, dim3((unsigned)blocks), dim3(256), 0, s,
+                           (const uint4*)x, row_token, total, (int)(row_bytes / 16),
+                           (uint4*)x_perm);
+    else if (row_bytes % 4 == 0)
+        hipLaunchKernelGGL(gather_rows_kernel<uint32_t>, dim3((unsigned)blocks), dim3(256), 0,
+                           s, (const uint32_t*)x, row_token, total, (int)(row_bytes / 4),
+                           (uint32_t*)x_perm);
+    else
+        hipLaunchKernelGGL(gather_rows_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0,
+                           s, (const uint16_t*)x, row_token, total, (int)(row_bytes / 2),
+                           (uint16_t*)x_perm);
+}
+
 int launch_permute(const void* x, int dtype, const int32_t* idx, const float* gate,
                    const int32_t* counts, int64_t T, int d, int k, int E, const PermuteTables& tabs,
                    int n_local, int G, int dev, void* x_perm, int64_t cap_rows,
@@ -387,16 +491,20 @@ int launch_permute(const void* x, int dtype, const int32_t* idx, const float* ga
     int32_t* blk = lo_ws + MOE_MAX_GROUPS;
     SlotTable st;
     HostTable ht;
-    for (int e = 0; e < MOE_MAX_E; ++e) {
-        st.slot_of[e] = tabs.slot_of[e];
-        ht.hosts[e] = tabs.hosts[e];
-    }
-    for (int i = 0; i < MOE_MAX_GROUPS; ++i) ht.expert_of_slot[i] = tabs.expert_of_slot[i];
+    fill_tables(tabs, st, ht);
 
     if (T <= SMALL_T) {
-        hipLaunchKernelGGL(perm_small_kernel, dim3(1), dim3(SMALL_T), 0, s, idx, gate, counts, T, k,
-                           E, st, ht, n_local, G, dev, group_offsets, row_token, row_gate,
-                           token_row, send_counts);
+        SmallArgs a = {};
+        a.idx = idx;
+        a.gate = gate;
+        a.counts_in = counts;
+        a.T = (int)T, a.k = k, a.E = E, a.n_local = n_local, a.G = G, a.dev = dev;
+        a.group_offsets = group_offsets;
+        a.row_token = row_token;
+        a.row_gate = row_gate;
+        a.token_row = token_row;
+        a.send_counts = send_counts;
+        hipLaunchKernelGGL(perm_small_kernel<false>, dim3(1), dim3(SMALL_T), 0, s, a, st, ht);
     } else {
         if (n_local > 0)
             hipLaunchKernelGGL(perm_count_kernel, dim3((unsigned)nblk), dim3(PERM_TOKENS), 0, s,
@@ -408,27 +516,102 @@ int launch_permute(const void* x, int dtype, const int32_t* idx, const float* ga
                            idx, gate, T, k, E, st, n_local, blk, lo_ws, group_offsets, row_token,
                            row_gate, token_row);
     }
-    if (nblk > 0 && n_local > 0 && d > 0) {
-        const size_t row_bytes = (size_t)d * (dtype == MOE_BF16 ? 2 : 4);
-        int64_t max_rows = cap_rows;
-        if (max_rows > T * (int64_t)k) max_rows = T * (int64_t)k;
-        int64_t blocks = ceil_div(max_rows, 4);
-        if (blocks > 4096) blocks = 4096;
-        if (blocks < 1) blocks = 1;
-        const int32_t* total = group_offsets + n_local;
-        if (row_bytes % 16 == 0)
-            hipLaunchKernelGGL(gather_rows_kernel<uint4>, dim3((unsigned)blocks), dim3(256), 0, s,
-                               (const uint4*)x, row_token, total, (int)(row_bytes / 16),
-                               (uint4*)x_perm);
-        else if (row_bytes % 4 == 0)
-            hipLaunchKernelGGL(gather_rows_kernel<uint32_t>, dim3((unsigned)blocks), dim3(256), 0,
-                               s, (const uint32_t*)x, row_token, total, (int)(row_bytes / 4),
-                               (uint32_t*)x_perm);
-        else
-            hipLaunchKernelGGL(gather_rows_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0,
-                               s, (const uint16_t*)x, row_token, total, (int)(row_bytes / 2),
-                               (uint16_t*)x_perm);
+    launch_gather_rows(x, dtype, T, d, k, n_local, x_perm, cap_rows, group_offsets, row_token, s);
+    return launch_status();
+}
+
+namespace {
+
+// The packaging launch with the counts, and with the top-k when scores are given;
+// KM, C as topk_group.
+template <int KM, int C>
+int launch_small_plan(const SmallArgs& a, const SlotTable& st, const HostTable& ht, hipStream_t s) {
+    const size_t lds = a.coact ? (size_t)a.E * a.E * sizeof(int32_t) : 0;
+    if (lds > 0 && allow_dynamic_lds<perm_small_kernel<true, KM, C>>(lds) != MOE_OK)
+        return MOE_ERR_DEVICE;
+    hipLaunchKernelGGL((perm_small_kernel<true, KM, C>), dim3(1), dim3(SMALL_T), lds, s, a, st, ht);
+    return launch_status();
+}
+
+template <int KM>
+int launch_small_topk(const SmallArgs& a, const SlotTable& st, const HostTable& ht, hipStream_t s) {
+    switch (topk_class(a.E)) {
+        case 0: return launch_small_plan<KM, 0>(a, st, ht, s);
+        case 1: return launch_small_plan<KM, 1>(a, st, ht, s);
+        case 2: return launch_small_plan<KM, 2>(a, st, ht, s);
+        case 3: return launch_small_plan<KM, 3>(a, st, ht, s);
+        default: return launch_small_plan<KM, 4>(a, st, ht, s);
     }
+}
+
+// Whether the packaging launch also takes the top-k: at most two passes of its 1024
+// threads (L lanes a token), and the ids within PLAN_IDS.  Measured per step against
+// the top-k launch of its own, see launch_route_package.
+bool plan_topk(int64_t T, int k, int E) {
+    const int C = topk_class(E);
+    const int L = C == 0 ? 4 : C <= 2 ? 8 : C == 3 ? 16 : 32;
+    return T * L <= 2 * SMALL_T && T * k <= PLAN_IDS;
+}
+
+}  // namespace
+
+// Routing, counts and packaging of one batch: moe_route_topk, moe_expert_histogram and
+// moe_permute, in fewer launches where the batch is short (at most SMALL_T tokens;
+// co-activation bins that fit LDS): the counts move into the packaging launch, and
+// for decode-sized bf16 batches the top-k too.
+int launch_route_package(const void* x, int dtype, const void* w, const float* bias, int64_t T,
+                         int d, int E, int k, int flags, float* logits, int32_t* idx, float* gate,
+                         void* ws_route, int32_t* counts, int32_t* coact, const PermuteTables& tabs,
+                         int n_local, int G, int dev, void* x_perm, int64_t cap_rows,
+                         int32_t* group_offsets, int32_t* row_token, float* row_gate,
+                         int32_t* token_row, int32_t* send_counts, void* ws_perm, hipStream_t s) {
+    const bool small = T > 0 && T <= SMALL_T && (!coact || E <= 128);
+    const bool given = (flags & MOE_LOGITS_IN) != 0;
+    const bool topk = small && plan_topk(T, k, E) &&
+                      (given || (dtype == MOE_BF16 && route_short(T, d, E)));
+    const int dcopy = x_perm ? d : 0;
+    int st = MOE_OK;
+    const float* scores = logits;
+    if (!topk) {
+        st = launch_route_topk(x, dtype, w, bias, T, d, E, k, flags, logits, idx, gate, ws_route, s);
+    } else if (!given) {
+        float* out = logits ? logits : (float*)ws_route;
+        scores = out;
+        st = launch_scores_short(x, w, bias, T, d, E, out, s);
+    }
+    if (st != MOE_OK) return st;
+    if (!small) {
+        st = launch_histogram(idx, T, k, E, counts, coact, s);
+        if (st != MOE_OK) return st;
+        return launch_permute(x, dtype, idx, gate, counts, T, dcopy, k, E, tabs, n_local, G, dev,
+                              x_perm, cap_rows, group_offsets, row_token, row_gate, token_row,
+                              send_counts, ws_perm, s);
+    }
+    SlotTable slots;
+    HostTable hosts;
+    fill_tables(tabs, slots, hosts);
+    SmallArgs a = {};
+    a.idx = idx;
+    a.gate = gate;
+    a.counts = counts;
+    a.coact = coact;
+    a.scores = scores;
+    a.idx_out = idx;
+    a.gate_out = gate;
+    a.renorm = (flags & MOE_RENORM) ? 1 : 0;
+    a.T = (int)T, a.k = k, a.E = E, a.n_local = n_local, a.G = G, a.dev = dev;
+    a.group_offsets = group_offsets;
+    a.row_token = row_token;
+    a.row_gate = row_gate;
+    a.token_row = token_row;
+    a.send_counts = send_counts;
+    if (!topk) st = launch_small_plan<0, 0>(a, slots, hosts, s);
+    else if (k <= 2) st = launch_small_topk<2>(a, slots, hosts, s);
+    else if (k <= 4) st = launch_small_topk<4>(a, slots, hosts, s);
+    else if (k <= 8) st = launch_small_topk<8>(a, slots, hosts, s);
+    else st = launch_small_topk<MOE_MAX_K>(a, slots, hosts, s);
+    if (st != MOE_OK) return st;
+    launch_gather_rows(x, dtype, T, dcopy, k, n_local, x_perm, cap_rows, group_offsets, row_token, s);
     return launch_status();
 }
 

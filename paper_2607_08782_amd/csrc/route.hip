@@ -6,9 +6,8 @@
 //   phase 1  scores for its tokens x all E experts into LDS
 //            bf16: MFMA 16x16x32, K split over 16 waves, fixed-order reduction
 //            (long batches over more than 32 experts use the tiled kernel of
-//            score.hip instead; short batches over more than 16 experts the
-//            per-wave partial tiles of route_wave_kernel, summed in a second
-//            launch with the top-k);
+//            score.hip instead; short batches score_small_kernel and a top-k
+//            launch);
 //            f32:  MFMA 16x16x4 (fp32 operands and sums), K split over waves;
 //            logits-in: read in place from global memory
 //   phase 2  bias added, scores written back coalesced (if requested)
@@ -20,13 +19,6 @@ namespace moe {
 namespace {
 
 constexpr int ROUTE_THREADS = TOPK_THREADS;
-constexpr int ROUTE_MAX_SPLIT = 32;    // K chunks of the split score kernel
-
-enum RouteMode { MODE_LOGITS_IN = 2, MODE_PARTIALS = 3 };
-
-}  // namespace
-int route_split(int64_t T, int d, int E);
-namespace {
 
 // bf16 gate scores on MFMA 16x16x32.  A workgroup of 16 waves owns 16*RT
 // tokens; wave w takes the K steps w, w+16, w+32, ... (32 elements each) for
@@ -48,7 +40,7 @@ template <int RT, int NTM, int KM, int C>
 __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, const float* __restrict__ bias,
     int64_t T, int d, int E, int k, int renorm, float* __restrict__ logits,
-    int32_t* __restrict__ idx, float* __restrict__ gate, int S, float* __restrict__ part) {
+    int32_t* __restrict__ idx, float* __restrict__ gate) {
     extern __shared__ __attribute__((aligned(16))) float smem[];
     constexpr int ROWS = 16 * RT;
     const int E_pad = (E + 15) & ~15;
@@ -78,12 +70,7 @@ __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
 #pragma unroll
         for (int j = 0; j < NTM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // K chunk of this workgroup (blockIdx.y of S): steps [sbeg, send), 32 elements each
-    const int nsteps_all = (d + 31) / 32;
-    const int chunk = blockIdx.y;
-    const int sbeg = (int)((int64_t)chunk * nsteps_all / S);
-    const int send = (int)((int64_t)(chunk + 1) * nsteps_all / S);
-    const int nsteps = send - sbeg;
+    const int nsteps = (d + 31) / 32;                  // 32 elements each
     if (NTM <= 4) {
         // all tiles' fragments of one K step fit in registers: keep two steps of
         // loads in flight (ring of two register sets, alternating by step parity).
@@ -91,7 +78,7 @@ __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
         // memory traffic), so the loop has no branches and the waits are exact.
         uint4 av[2][RT], bv[2][NTM];
         const int n_mine = wave < nsteps ? (nsteps - wave + RB_WAVES - 1) / RB_WAVES : 0;
-        const int s0 = sbeg + wave;
+        const int s0 = wave;
         auto load = [&](int i, uint4* a_, uint4* b_) {
             const int k0 = (s0 + i * RB_WAVES) * 32;
             const bool kin = i < n_mine && k0 + kq < d;
@@ -120,7 +107,7 @@ __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
             load(i + 3, av[1], bv[1]);
         }
     } else {
-        for (int step = sbeg + wave; step < send; step += RB_WAVES) {
+        for (int step = wave; step < nsteps; step += RB_WAVES) {
             const int k0 = step * 32;
             const bool kin = k0 + kq < d;
             bf16x8 a[RT];
@@ -181,40 +168,28 @@ __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
         Sm[r * ldS + e] = smem[o];
     }
     __syncthreads();
-    if (S == 1) {
-        // 1024 threads hold at least one lane group per token: one token per group
-        finish_tokens<KM, C, 1>(Sm, ldS, nt, t0, E, k, renorm, bias, logits, idx, gate);
-    } else {
-        // partial scores of this K chunk: part[chunk][t][e]
-        for (int c = tid; c < nt * E; c += RB_THREADS) {
-            const int r = c / E, e = c % E;
-            part[((int64_t)chunk * T + t0 + r) * E + e] = Sm[r * ldS + e];
-        }
-    }
+    // 1024 threads hold at least one lane group per token: one token per group
+    finish_tokens<KM, C, 1>(Sm, ldS, nt, t0, E, k, renorm, bias, logits, idx, gate);
 }
 
-// Partial bf16 gate scores of short batches (few token blocks, e.g. decode):
-// one wave per (16 tokens, 16 experts, K chunk) on MFMA 16x16x32, every operand
-// load of the chunk issued before the first product, and the 16 x 16 fp32
-// partial tile stored straight from the accumulators into part[chunk][t][e]
-// (no LDS, no barriers), so a batch of a few dozen tokens still spreads over
-// about a thousand waves.  Rows past the batch or past E, and K past d, read as
-// zero through the buffer descriptors.
-constexpr int RW_WAVES = 4;            // waves per workgroup
-constexpr int RW_STEPS = 8;            // 32-wide K steps of loads issued at once
+// bf16 gate scores of short batches (few token blocks, e.g. decode): one 16-wave
+// workgroup per (16 tokens, 16 experts) on MFMA 16x16x32, the waves splitting K,
+// every operand load of a wave's slice issued before its first product (up to 8
+// K steps at a time), the 16 partial tiles summed in wave order through LDS.  Rows
+// past the batch or past E, and K past d, read as zero through the buffer
+// descriptors.  Bound by load latency: the scores leave finished, where K chunks on
+// separate workgroups left up to 32 partial scores each for the top-k's launch to
+// read back.
+constexpr int SS_WAVES = 16;
+constexpr int SS_STEPS = 8;            // 32-wide K steps of loads issued at once
 
-__global__ __launch_bounds__(RW_WAVES * 64) void route_wave_kernel(
-    const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, int64_t T, int d, int E, int S,
-    float* __restrict__ part) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wid = (int64_t)blockIdx.x * RW_WAVES + (threadIdx.x >> 6);
-    const int ET = (E + 15) / 16;
-    const int64_t TT = (T + 15) / 16;
-    if (wid >= TT * ET * S) return;                  // the whole wave leaves together
-    const int c = (int)(wid % S);
-    const int64_t tile = wid / S;
-    const int e0 = (int)(tile % ET) * 16;
-    const int64_t t0 = (tile / ET) * 16;
+__global__ __launch_bounds__(SS_WAVES * 64) void score_small_kernel(
+    const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, const float* __restrict__ bias,
+    int64_t T, int d, int E, float* __restrict__ out) {
+    __shared__ f32x4 part[SS_WAVES][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int e0 = blockIdx.x * 16;
+    const int64_t t0 = (int64_t)blockIdx.y * 16;
     const int nt = (int)((T - t0) < 16 ? (T - t0) : 16);
     const int ne = E - e0 < 16 ? E - e0 : 16;
     const int row = lane & 15, kq = (lane >> 4) * 8;
@@ -222,32 +197,36 @@ __global__ __launch_bounds__(RW_WAVES * 64) void route_wave_kernel(
         (void*)(X + t0 * d), (short)0, nt * d * 2, RB_RSRC_WORD3);
     const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(W + (int64_t)e0 * d), (short)0, ne * d * 2, RB_RSRC_WORD3);
-    const int nsteps_all = (d + 31) / 32;
-    const int sbeg = (int)((int64_t)c * nsteps_all / S);
-    const int send = (int)((int64_t)(c + 1) * nsteps_all / S);
+    // the thread that finishes (token r, expert e): its bias, loaded beside the operands
+    const int r = (tid >> 4) & 15, e = tid & 15;
+    const float b = bias && tid < 256 && e < ne ? bias[e0 + e] : 0.f;
+    const int nsteps = (d + 31) / 32;
+    const int sbeg = wave * nsteps / SS_WAVES, send = (wave + 1) * nsteps / SS_WAVES;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = sbeg; s0 < send; s0 += RW_STEPS) {
-        uint4 a[RW_STEPS], b[RW_STEPS];
+    for (int s0 = sbeg; s0 < send; s0 += SS_STEPS) {
+        uint4 a[SS_STEPS], w[SS_STEPS];
 #pragma unroll
-        for (int i = 0; i < RW_STEPS; ++i) {
+        for (int i = 0; i < SS_STEPS; ++i) {
             const int k = (s0 + i) * 32 + kq;
             const int off = (s0 + i < send && k < d) ? (row * d + k) * 2 : RB_OOB;
             a[i] = rb_load16(xr, off);
-            b[i] = rb_load16(wr, off);
+            w[i] = rb_load16(wr, off);
         }
 #pragma unroll
-        for (int i = 0; i < RW_STEPS; ++i)
+        for (int i = 0; i < SS_STEPS; ++i)
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]),
-                                                          __builtin_bit_cast(bf16x8, b[i]), acc,
+                                                          __builtin_bit_cast(bf16x8, w[i]), acc,
                                                           0, 0, 0);
     }
+    part[wave][lane] = acc;
+    __syncthreads();
     // accumulator element i of lane L: token 4 (L / 16) + i, expert L % 16
-    if (row < ne) {
+    if (tid < 256 && r < nt && e < ne) {
+        const float* p = (const float*)&part[0][(r >> 2) * 16 + e] + (r & 3);
+        float sum = p[0];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = 4 * (lane >> 4) + i;
-            if (r < nt) part[((int64_t)c * T + t0 + r) * E + e0 + row] = acc[i];
-        }
+        for (int v = 1; v < SS_WAVES; ++v) sum += p[v * 256];
+        out[(t0 + r) * E + e0 + e] = sum + b;
     }
 }
 
@@ -344,44 +323,15 @@ __global__ __launch_bounds__(RF_WAVES * 64) void route_f32_kernel(
     finish_tokens<KM, C, 1>(Sm, ldS, nt, t0, E, k, renorm, bias, logits, idx, gate);
 }
 
-// Scores handed in (MOE_LOGITS_IN) or K-chunk partial scores to be summed: `tpb` tokens per workgroup of 256 threads, one
-// token per top-k lane group (topk_tokens_per_block), so short batches still
-// spread over many workgroups.  MAXS: the most chunks a partial-sum launch adds.
-template <int MODE, int KM, int C, int MAXS = ROUTE_MAX_SPLIT>
-__global__ __launch_bounds__(ROUTE_THREADS) void route_simple_kernel(
-    const float* __restrict__ bias, int64_t T, int E, int k, int renorm, float* __restrict__ logits,
-    int32_t* __restrict__ idx, float* __restrict__ gate, int S, const float* __restrict__ part,
-    int tpb) {
-    extern __shared__ __attribute__((aligned(16))) float smem[];
-    const int ldS = ((E + 15) & ~15) + 1;
-    float* Sm = smem;
-    const int tid = threadIdx.x;
+// Top-k of given scores: `tpb` tokens per workgroup of 256 threads, straight from
+// global memory.
+template <int KM, int C>
+__global__ __launch_bounds__(ROUTE_THREADS) void topk_given_kernel(
+    const float* __restrict__ scores, int64_t T, int E, int k, int renorm,
+    int32_t* __restrict__ idx, float* __restrict__ gate, int tpb) {
     const int64_t t0 = (int64_t)blockIdx.x * tpb;
     const int nt = (int)((T - t0) < tpb ? (T - t0) : tpb);
-    if (MODE == MODE_PARTIALS) {
-        // K chunks summed in chunk order.  Chunks are split only for short
-        // batches, where a thread has few elements: per element, all
-        // MAXS chunk loads go out together (unconditionally, clamped to
-        // chunk S - 1 and masked by a 0/1 factor), one round trip per element
-        const float* pb = part + t0 * E;
-        const int64_t cs = T * E;                     // chunk stride
-        for (int c = tid; c < nt * E; c += ROUTE_THREADS) {
-            float x[MAXS];
-#pragma unroll
-            for (int ch = 0; ch < MAXS; ++ch) x[ch] = pb[(ch < S ? ch : S - 1) * cs + c];
-            float sum = 0.f;
-#pragma unroll
-            for (int ch = 0; ch < MAXS; ++ch) sum = fmaf(x[ch], ch < S ? 1.0f : 0.0f, sum);
-            const int r = c / E, e = c - r * E;
-            Sm[r * ldS + e] = sum;
-        }
-    } else {
-        // scores handed in: top-k straight from global memory
-        topk_tokens<KM, C>(logits + t0 * E, E, nt, t0, E, k, renorm, idx, gate);
-        return;
-    }
-    __syncthreads();
-    finish_tokens<KM, C>(Sm, ldS, nt, t0, E, k, renorm, bias, logits, idx, gate);
+    topk_tokens<KM, C>(scores + t0 * E, E, nt, t0, E, k, renorm, idx, gate);
 }
 
 // Token rows per workgroup of the bf16 score kernel, by expert count.
@@ -393,9 +343,9 @@ int route_rows(int E) {
     return 16 * (E_pad <= 16 ? 1 : (E_pad <= 128 ? 2 : 1));
 }
 
-// Tokens per workgroup of route_simple_kernel: at most one pass of the top-k
+// Tokens per workgroup of topk_given_kernel: at most one pass of the top-k
 // lane groups, and few enough that a short batch still spreads over >= 128
-// workgroups (the chunk sums and the top-k are latency-bound per workgroup).
+// workgroups (the top-k is latency-bound per workgroup).
 int simple_tokens_per_block(int64_t T, int E) {
     const int cap = topk_tokens_per_block(E);
     const int64_t want = ceil_div(T, 128);
@@ -408,13 +358,16 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
               hipStream_t s) {
     const int renorm = (flags & MOE_RENORM) ? 1 : 0;
     const int E_pad = (E + 15) & ~15;
-    if (!(flags & MOE_LOGITS_IN) && dtype == MOE_BF16) {
-        const int rows = route_rows(E);
+    const float* given = logits;
+    if (!(flags & MOE_LOGITS_IN) && dtype == MOE_F32) {
+        const int vec = d % 4 == 0 && (((uintptr_t)x | (uintptr_t)w) & 15u) == 0;
+        hipLaunchKernelGGL((route_f32_kernel<KM, C>), dim3((unsigned)ceil_div(T, RF_TOKENS)),
+                           dim3(RF_WAVES * 64), 0, s, (const float*)x, (const float*)w, bias, T, d, E,
+                           k, renorm, vec, logits, idx, gate);
+        return launch_status();
+    }
+    if (!(flags & MOE_LOGITS_IN)) {
         const int St = score_tiles_split(T, 2 * d, E, true);
-        const int S = St > 0 ? St : route_split(T, d, E);
-        const size_t lds = (size_t)4 * rows * (E_pad + 1) * sizeof(float);
-        const dim3 grid((unsigned)ceil_div(T, rows), (unsigned)S), block(RB_THREADS);
-        float* part = (float*)ws;
         if (St == 1 && E <= 64) {
             // long batch over 33-64 experts: the tiled score kernel with its top-k in
             // the same launch (scores + bias to `logits` when requested).  Wider E
@@ -425,104 +378,65 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
             return launch_score_tiles_topk(x, w, bias, T, 2 * d, E, k, renorm, logits, idx, gate,
                                            s);
         }
-        if (St > 0) {
-            // the tiled score kernel with its K split: partial scores to the workspace
-            float* out = (St == 1 && logits) ? logits : part;
-            const int st = launch_score_tiles(false, x, w, nullptr, nullptr, bias, T, 2 * d, E,
-                                              St, out, s);
+        float* out = logits ? logits : (float*)ws;
+        given = out;
+        if (St == 1) {
+            const int st = launch_score_tiles(false, x, w, nullptr, nullptr, bias, T, 2 * d, E, 1,
+                                              out, s);
             if (st != MOE_OK) return st;
-            if (St == 1) {
-                const int tpb = simple_tokens_per_block(T, E);
-                hipLaunchKernelGGL((route_simple_kernel<MODE_LOGITS_IN, KM, C>),
-                                   dim3((unsigned)ceil_div(T, tpb)), dim3(ROUTE_THREADS), 0, s,
-                                   nullptr, T, E, k, renorm, out, idx, gate, 1,
-                                   nullptr, tpb);
-                return launch_status();
-            }
-        } else if (S > 1 && E > 16) {
-            const int64_t waves = ceil_div(T, 16) * ((E + 15) / 16) * S;
-            hipLaunchKernelGGL(route_wave_kernel, dim3((unsigned)ceil_div(waves, RW_WAVES)),
-                               dim3(RW_WAVES * 64), 0, s, (const bf16_t*)x, (const bf16_t*)w, T, d,
-                               E, S, part);
+        } else if (route_short(T, d, E)) {
+            launch_scores_short(x, w, bias, T, d, E, out, s);
         } else {
+            const int rows = route_rows(E);
+            const size_t lds = (size_t)4 * rows * (E_pad + 1) * sizeof(float);
 #define MOE_RB_LAUNCH(RT, NTM)                                                                  \
     do {                                                                                        \
         if (lds > 65536 && allow_dynamic_lds<route_bf16_kernel<RT, NTM, KM, C>>(lds) != MOE_OK)  \
             return MOE_ERR_DEVICE;                                                              \
-        hipLaunchKernelGGL((route_bf16_kernel<RT, NTM, KM, C>), grid, block, lds, s,               \
-                           (const bf16_t*)x, (const bf16_t*)w, bias, T, d, E, k, renorm,        \
-                           logits, idx, gate, S, part);                                         \
+        hipLaunchKernelGGL((route_bf16_kernel<RT, NTM, KM, C>),                                 \
+                           dim3((unsigned)ceil_div(T, rows)), dim3(RB_THREADS), lds, s,         \
+                           (const bf16_t*)x, (const bf16_t*)w, bias, T, d, E, k, renorm, logits, \
+                           idx, gate);                                                          \
     } while (0)
-        if constexpr (C == 0) MOE_RB_LAUNCH(1, 1);          // E <= 16
-        else if constexpr (C <= 2) MOE_RB_LAUNCH(2, 4);     // E <= 64
-        else if constexpr (C == 3) MOE_RB_LAUNCH(2, 8);     // E <= 128
-        else MOE_RB_LAUNCH(1, 16);
+            if constexpr (C == 0) MOE_RB_LAUNCH(1, 1);          // E <= 16
+            else if constexpr (C <= 2) MOE_RB_LAUNCH(2, 4);     // E <= 64
+            else if constexpr (C == 3) MOE_RB_LAUNCH(2, 8);     // E <= 128
+            else MOE_RB_LAUNCH(1, 16);
 #undef MOE_RB_LAUNCH
+            return launch_status();
         }
-        if (S > 1) {
-            const int tpb = simple_tokens_per_block(T, E);
-            const size_t lds2 = (size_t)tpb * (E_pad + 1) * sizeof(float);
-            // as few clamped chunk loads per score as the split needs
-            if (S <= 16)
-                hipLaunchKernelGGL((route_simple_kernel<MODE_PARTIALS, KM, C, 16>),
-                                   dim3((unsigned)ceil_div(T, tpb)), dim3(ROUTE_THREADS), lds2, s,
-                                   bias, T, E, k, renorm, logits, idx, gate, S,
-                                   (const float*)part, tpb);
-            else
-                hipLaunchKernelGGL((route_simple_kernel<MODE_PARTIALS, KM, C, ROUTE_MAX_SPLIT>),
-                                   dim3((unsigned)ceil_div(T, tpb)), dim3(ROUTE_THREADS), lds2, s,
-                                   bias, T, E, k, renorm, logits, idx, gate, S,
-                                   (const float*)part, tpb);
-        }
-        return launch_status();
     }
-    if (flags & MOE_LOGITS_IN) {
-        const int tpb = simple_tokens_per_block(T, E);
-        hipLaunchKernelGGL((route_simple_kernel<MODE_LOGITS_IN, KM, C>),
-                           dim3((unsigned)ceil_div(T, tpb)), dim3(ROUTE_THREADS), 0, s, nullptr,
-                           T, E, k, renorm, logits, idx, gate, 1, nullptr,
-                           tpb);
-        return launch_status();
-    }
-    const int vec = d % 4 == 0 && (((uintptr_t)x | (uintptr_t)w) & 15u) == 0;
-    hipLaunchKernelGGL((route_f32_kernel<KM, C>), dim3((unsigned)ceil_div(T, RF_TOKENS)),
-                       dim3(RF_WAVES * 64), 0, s, (const float*)x, (const float*)w, bias, T, d, E, k,
-                       renorm, vec, logits, idx, gate);
+    const int tpb = simple_tokens_per_block(T, E);
+    hipLaunchKernelGGL((topk_given_kernel<KM, C>), dim3((unsigned)ceil_div(T, tpb)),
+                       dim3(ROUTE_THREADS), 0, s, given, T, E, k, renorm, idx, gate, tpb);
     return launch_status();
 }
 
 }  // namespace
 
-// K chunks of the bf16 scores when there are few token blocks (decode batches);
-// 1 = the one-launch kernel with the top-k in its epilogue.  More than 16
-// experts: route_wave_kernel gets about 1024 waves of 16 x 16 tiles with at
-// least two K steps each (Qwen3-30B-A3B-shaped decode routing 16.8 -> 11.9 us).
-// At most 16 experts a 16-wide tile is mostly padding, and the block kernel
-// splits K into chunks of at least four steps instead (its LDS reduction sums
-// the waves of a block).
-int route_split(int64_t T, int d, int E) {
-    const int64_t blocks = ceil_div(T, route_rows(E));
-    if (blocks <= 0 || blocks >= 128) return 1;
-    const int nsteps = (d + 31) / 32;
-    int64_t S;
-    if (E <= 16) {
-        S = ceil_div(256, blocks);
-        if (S > 16) S = 16;
-        if (S > nsteps / 4) S = nsteps / 4;
-    } else {
-        S = ceil_div(1024, ceil_div(T, 16) * ((E + 15) / 16));
-        if (S > ROUTE_MAX_SPLIT) S = ROUTE_MAX_SPLIT;
-        if (S > nsteps / 2) S = nsteps / 2;
-    }
-    return S < 1 ? 1 : (int)S;
+// Short batches: too few token blocks for the one-launch kernel (fewer than 128) and
+// K long enough to be worth splitting over 16 waves.  Their scores come from
+// score_small_kernel, the top-k from a launch of its own (or from the packaging
+// launch).
+bool route_short(int64_t T, int d, int E) {
+    return T > 0 && ceil_div(T, route_rows(E)) < 128 && (d + 31) / 32 >= (E <= 16 ? 8 : 4) &&
+           score_tiles_split(T, 2 * d, E, true) == 0;
 }
 
+int launch_scores_short(const void* x, const void* w, const float* bias, int64_t T, int d, int E,
+                        float* out, hipStream_t s) {
+    hipLaunchKernelGGL(score_small_kernel, dim3((unsigned)ceil_div(E, 16), (unsigned)ceil_div(T, 16)),
+                       dim3(SS_WAVES * 64), 0, s, (const bf16_t*)x, (const bf16_t*)w, bias, T, d, E,
+                       out);
+    return launch_status();
+}
+
+// scores kept for the top-k's launch when the caller wants none stored
 size_t route_ws_bytes(int dtype, int64_t T, int d, int E, int flags) {
     if ((flags & MOE_LOGITS_IN) || dtype != MOE_BF16 || T <= 0) return 0;
-    const int St = score_tiles_split(T, 2 * d, E, true);
-    const int S = St > 0 ? St : route_split(T, d, E);
-    // the tiled kernel with one chunk keeps its scores here when none are requested
-    return (S > 1 || St == 1) ? (size_t)S * (size_t)T * (size_t)E * sizeof(float) : 0;
+    return route_short(T, d, E) || score_tiles_split(T, 2 * d, E, true) == 1
+               ? (size_t)T * (size_t)E * sizeof(float)
+               : 0;
 }
 
 int launch_topk_given(const float* scores, int64_t T, int E, int k, int flags, int32_t* idx,

@@ -302,6 +302,17 @@ class LayerShare:
                         self.dev, E=self.E, cap_rows=self.cap_rows, out=self.perm, ws=self.ws_perm,
                         copy_rows=not self.gather_in_ffn)
 
+    def _route_package(self, logits_in: Optional[torch.Tensor] = None):
+        """Enqueue routing, counts and packaging as one call: `route`, the histogram and
+        `package`, the same outputs in fewer launches over short batches."""
+        moe.moe_route_package(self.X, self.Wr, self.bias, self.placement, self.dev,
+                              logits=self.logits if logits_in is None else logits_in,
+                              topk_idx=self.topk_idx, topk_gate=self.topk_gate,
+                              ws_route=self.ws_route, counts=self.counts, coact=self.coact,
+                              out=self.perm, ws_perm=self.ws_perm, cap_rows=self.cap_rows,
+                              renorm=self.renorm, logits_in=logits_in is not None,
+                              copy_rows=not self.gather_in_ffn)
+
     def routed_ffn(self, fused: Optional[bool] = None):
         """Enqueue the routed experts' FFN call as `run` makes it: moe_grouped_ffn (or
         moe_grouped_ffn_rows) into y_perm, or, when the share fuses the combine (fused
@@ -345,18 +356,14 @@ class LayerShare:
             # the fused call reads y_shared: the shared branch overlaps the routing
             if self._side is not None:
                 fork_shared()
-            self.route(logits_in)
-            moe.moe_expert_histogram(self.topk_idx, self.E, counts=self.counts, coact=self.coact)
-            self.package()
+            self._route_package(logits_in)
             if self._side is not None:
                 main.wait_event(self._join)
             elif self.shared_weights is not None:
                 self._shared_ffn()
             self.routed_ffn()
             return self.y
-        self.route(logits_in)
-        moe.moe_expert_histogram(self.topk_idx, self.E, counts=self.counts, coact=self.coact)
-        self.package()
+        self._route_package(logits_in)
         # the shared branch forks after the routing launches, which would otherwise
         # wait for CUs held by its GEMMs, and overlaps the routed experts' FFN, whose
         # launches leave CUs idle

@@ -28,7 +28,7 @@ MOE_PERMUTE_NOALLOC_MAX_WS = 4 << 20
 
 EXPORTS = ("moe_status_string", "moe_route_topk", "moe_route_topk_ws_bytes",
            "moe_expert_histogram", "moe_permute_ws_bytes",
-           "moe_permute", "moe_permute_noalloc", "moe_grouped_ffn_ws_bytes", "moe_grouped_ffn",
+           "moe_permute", "moe_permute_noalloc", "moe_route_package", "moe_grouped_ffn_ws_bytes", "moe_grouped_ffn",
            "moe_grouped_ffn_products", "moe_grouped_ffn_combine",
            "moe_grouped_ffn_rows", "moe_grouped_ffn_rows_products", "moe_grouped_ffn_rows_shared",
            "moe_combine", "moe_combine_shared",
@@ -67,6 +67,9 @@ def load_library(path: str = LIB_PATH):
     lib.moe_permute_noalloc.argtypes = [P, I, P, P, P, L, I, I, I, P, I, I, I, P, L, P, P, P, P, P,
                                         P]
     lib.moe_permute_noalloc.restype = I
+    lib.moe_route_package.argtypes = [P, I, P, P, L, I, I, I, I, P, P, P, P, S, P, P, P, I, I, I, P,
+                                      L, P, P, P, P, P, P, S, P]
+    lib.moe_route_package.restype = I
     lib.moe_grouped_ffn_ws_bytes.argtypes = [I, L, I, I, I]
     lib.moe_grouped_ffn_ws_bytes.restype = S
     lib.moe_grouped_ffn.argtypes = [P, I, P, I, P, P, I, I, L, P, P, S, P]
@@ -304,6 +307,45 @@ def moe_permute(x: torch.Tensor, topk_idx: torch.Tensor, topk_gate: torch.Tensor
         ws = workspace(moe_permute_ws_bytes(T, k, E), device)
     _check("moe_permute", lib.moe_permute(*args, _dev(ws, "ws"), ws.numel(), _stream(stream)))
     return o
+
+
+def moe_route_package(x: torch.Tensor, w_router: Optional[torch.Tensor],
+                      bias: Optional[torch.Tensor], placement: np.ndarray, dev: int, *,
+                      logits: Optional[torch.Tensor], topk_idx: torch.Tensor,
+                      topk_gate: torch.Tensor, ws_route: Optional[torch.Tensor],
+                      counts: torch.Tensor, coact: Optional[torch.Tensor], out: dict,
+                      ws_perm: torch.Tensor, cap_rows: int, renorm: bool = True,
+                      logits_in: bool = False, copy_rows: bool = True, c_max: int = 0, stream=None):
+    """moe_route_topk, moe_expert_histogram and moe_permute of one batch in one call,
+    into the caller's buffers (`out` as moe_permute's; copy_rows=False: row maps only)."""
+    lib = load_library()
+    T, d = x.shape
+    k = topk_idx.shape[1]
+    E = counts.numel()
+    dtype = _dtype_code(x)
+    if not logits_in and (w_router.dtype != x.dtype or tuple(w_router.shape) != (E, d)):
+        raise ValueError("w_router must be [E, d] of x's dtype")
+    if logits_in and (logits is None or tuple(logits.shape) != (T, E)):
+        raise ValueError("logits_in needs logits [T, E]")
+    placement = np.ascontiguousarray(placement, dtype=np.uint8)
+    if placement.ndim != 2 or placement.shape[0] != E:
+        raise ValueError("placement must be a [E, G] array")
+    flags = (MOE_RENORM if renorm else 0) | (MOE_LOGITS_IN if logits_in else 0)
+    st = lib.moe_route_package(
+        _dev(x, "x"), dtype, None if logits_in else _dev(w_router, "w_router"),
+        _dev(bias, "bias", torch.float32), T, d, E, k, flags, _dev(logits, "logits", torch.float32),
+        _dev(topk_idx, "topk_idx", torch.int32), _dev(topk_gate, "topk_gate", torch.float32),
+        _dev(ws_route, "ws_route"), 0 if ws_route is None else ws_route.numel(),
+        _dev(counts, "counts", torch.int32), _dev(coact, "coact", torch.int32),
+        placement.ctypes.data_as(ctypes.c_void_p), placement.shape[1], dev, c_max,
+        _dev(out["x_perm"], "x_perm", x.dtype) if copy_rows else None, cap_rows,
+        _dev(out["group_offsets"], "group_offsets", torch.int32),
+        _dev(out["row_token"], "row_token", torch.int32),
+        _dev(out["row_gate"], "row_gate", torch.float32),
+        _dev(out["token_row"], "token_row", torch.int32),
+        _dev(out.get("send_counts"), "send_counts", torch.int32), _dev(ws_perm, "ws_perm"),
+        ws_perm.numel(), _stream(stream))
+    _check("moe_route_package", st)
 
 
 class WeightTable:

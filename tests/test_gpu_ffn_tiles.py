@@ -1,0 +1,70 @@
+"""The bf16 expert FFN at the edges of its kernels: tiles of 256 rows and their LDS
+ring (K of one and two 64-wide steps, column tails, row tiles in blocks of eight, many
+tiles a workgroup), whole-K strips (32 output columns, 64- and 128-row tiles, K from
+64 to their longest), each against the oracle's expert FFN in float64 on sampled rows.
+The tolerance is the parity protocol's: h and y are rounded to bf16 (2^-9 relative
+each), sums in fp32."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2607_08782_amd import moe
+
+from parity import OUT_TOL, close, np32, say
+
+pytestmark = pytest.mark.gpu
+LARGE, SMALL = moe.MOE_FFN_LARGE_GROUPS, moe.MOE_FFN_SMALL_GROUPS
+
+
+@pytest.mark.parametrize("sizes,d,f,hint,gather", [
+    ([257, 300], 64, 64, LARGE, False),             # one 64-wide K step: rings not chained
+    ([700, 1, 0, 513], 64, 192, LARGE, True),
+    ([300, 600], 128, 64, LARGE, True),             # gate/up chained, down not
+    ([256, 512, 1024], 192, 448, LARGE, False),     # exact tiles, column tails
+    ([2305], 256, 320, LARGE, False),               # ten row tiles: two blocks of five
+    ([4500, 260], 128, 128, LARGE, True),           # 18 row tiles: three blocks of six
+    ([300] * 20, 64, 128, LARGE, False),
+    ([1, 64, 33, 0, 17], 64, 64, SMALL, True),      # strips, one K stage
+    ([1, 64, 33, 0, 17], 2048, 128, SMALL, True),   # longest K, 64-row tiles
+    ([128, 129, 256, 65], 192, 2048, SMALL, False),   # 128-row tiles and tails
+    ([200, 3], 2112, 128, SMALL, False),            # gate/up split over workgroups, down a strip
+    ([40, 90], 128, 2112, SMALL, True),             # and the reverse
+    ([30, 5, 64], 256, 128, 0, False),              # no hint
+    ([700, 5, 64, 200], 256, 128, 0, True),
+])
+def test_bf16_ffn_tile_edges(sizes, d, f, hint, gather):
+    say("[bf16 ffn]", sizes, "d=%d f=%d hint=%d gather=%s" % (d, f, hint, gather))
+    gen = torch.Generator().manual_seed(d * 31 + f)
+    N = sum(sizes)
+    T = max(sizes) + 5
+    x = torch.randn((T if gather else N, d), generator=gen).bfloat16()
+    w13 = [(torch.randn((2 * f, d), generator=gen) * d ** -0.5).bfloat16() for _ in sizes]
+    w2 = [(torch.randn((d, f), generator=gen) * f ** -0.5).bfloat16() for _ in sizes]
+    tok = torch.cat([torch.randperm(T, generator=gen)[:n] for n in sizes]).to(torch.int32)
+    tok = torch.cat([tok, torch.zeros(2, dtype=torch.int32)])
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    wt = moe.WeightTable([w.cuda() for w in w13], [w.cuda() for w in w2])
+    y = torch.full((N + 2, d), 5.0, dtype=torch.bfloat16, device="cuda")
+    off = torch.tensor(offs).cuda()
+    for _ in range(2):
+        if gather:
+            moe.moe_grouped_ffn_rows(x.cuda(), tok.cuda(), off, wt, cap_rows=N + 2, y_perm=y,
+                                     products=3 | hint)
+        else:
+            moe.moe_grouped_ffn(x.cuda(), off, wt, cap_rows=N, y_perm=y, products=3 | hint)
+    torch.cuda.synchronize()
+    got = np32(y)
+    rows = np32(x)[np32(tok).astype(np.int64)[:N]] if gather else np32(x)
+    rng = np.random.default_rng(0)
+    for g, n in enumerate(sizes):
+        a = int(offs[g])
+        if n == 0:
+            continue
+        # every row of the first and last 16, and some between
+        pick = np.unique(np.concatenate([np.arange(min(n, 16)), np.arange(max(0, n - 16), n),
+                                         rng.integers(0, n, 24)])) + a
+        ref = oracle.expert_ffn(rows[pick], np32(w13[g]), np32(w2[g]))
+        close(got[pick], ref, OUT_TOL["bf16"], "group %d" % g)
+        assert np.isfinite(got[a:a + n]).all()
+    assert np.all(got[N:] == 5.0)

@@ -1,0 +1,85 @@
+"""moe_route_package against its three parts, bit for bit: batches on both sides of
+the one-workgroup packaging launch (1024 tokens), of the top-k taken inside it, and of
+each top-k class, with and without co-activation counts, scores handed in, replicas,
+row copies, both element types; the parts are checked against the oracle elsewhere."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2607_08782_amd import moe, synth
+
+from parity import say
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # T, E, k, d, G, coact, dtype, logits_in, copy
+    (1, 8, 2, 256, 2, False, "bf16", False, True),
+    (64, 128, 8, 2048, 9, True, "bf16", False, False),
+    (65, 16, 4, 512, 3, True, "bf16", False, True),
+    (128, 128, 8, 256, 4, False, "bf16", False, False),
+    (129, 128, 8, 256, 4, True, "bf16", False, False),      # top-k in a launch of its own
+    (256, 64, 6, 256, 8, False, "bf16", False, False),
+    (257, 60, 4, 256, 8, False, "bf16", False, False),
+    (512, 8, 2, 512, 4, True, "bf16", False, True),
+    (300, 200, 16, 256, 5, True, "bf16", False, False),     # E above the LDS co-activation bins
+    (63, 256, 16, 256, 5, False, "bf16", False, False),
+    (256, 17, 16, 256, 2, False, "bf16", False, False),     # exactly PLAN_IDS assignments
+    (1023, 32, 4, 64, 4, False, "bf16", False, False),      # short K: the one-launch router
+    (1024, 8, 2, 320, 4, True, "bf16", False, False),
+    (1025, 8, 2, 320, 4, True, "bf16", False, True),        # three launches
+    (77, 12, 3, 72, 3, True, "f32", False, True),
+    (64, 8, 2, 128, 1, False, "f32", True, False),
+    (200, 40, 5, 64, 4, False, "bf16", True, False),
+    (0, 8, 2, 64, 2, True, "bf16", False, True),
+]
+
+
+@pytest.mark.parametrize("T,E,k,d,G,coact,dtype,logits_in,copy", CASES)
+def test_route_package_equals_its_parts(T, E, k, d, G, coact, dtype, logits_in, copy):
+    say("[package] T=%d E=%d k=%d d=%d G=%d" % (T, E, k, d, G), coact, dtype, logits_in, copy)
+    cfg = synth.custom_config(dtype=dtype, d=d, E=E, k=k, f=64, G=G, replicas=min(2, G - 1),
+                              zipf=1.1)
+    inp = synth.make_layer(cfg, T, seed=3, device="cuda", experts="none")
+    n_local = int(inp.placement[:, 0].sum())
+    cap = T * min(k, n_local)
+    handed = torch.randn((T, E), device="cuda") if logits_in else None
+
+    def fresh():
+        i32 = dict(dtype=torch.int32, device="cuda")
+        return {"logits": handed.clone() if logits_in else torch.zeros((T, E), device="cuda"),
+                "idx": torch.zeros((T, k), **i32), "gate": torch.zeros((T, k), device="cuda"),
+                "counts": torch.full((E,), -1, **i32),
+                "coact": torch.full((E, E), -1, **i32) if coact else None,
+                "perm": {"x_perm": torch.zeros((max(cap, 1), d), dtype=inp.X.dtype, device="cuda"),
+                         "group_offsets": torch.full((n_local + 1,), -1, **i32),
+                         "row_token": torch.full((max(cap, 1),), -1, **i32),
+                         "row_gate": torch.zeros((max(cap, 1),), device="cuda"),
+                         "token_row": torch.full((T, k), -9, **i32),
+                         "send_counts": torch.full((G,), -1, **i32)}}
+
+    code = moe.MOE_BF16 if dtype == "bf16" else moe.MOE_F32
+    need = moe.moe_route_topk_ws_bytes(code, T, d, E, moe.MOE_RENORM)
+    ws_r = moe.workspace(need, "cuda")
+    ws_p = moe.workspace(moe.moe_permute_ws_bytes(T, k, E), "cuda")
+    a, b = fresh(), fresh()
+    moe.moe_route_topk(None if logits_in else inp.X, inp.Wr, inp.bias, k, logits=a["logits"],
+                       logits_in=logits_in, topk_idx=a["idx"], topk_gate=a["gate"], ws=ws_r)
+    moe.moe_expert_histogram(a["idx"], E, counts=a["counts"], coact=a["coact"])
+    moe.moe_permute(inp.X, a["idx"], a["gate"], a["counts"], inp.placement, 0, E=E, cap_rows=cap,
+                    out=a["perm"], ws=ws_p, copy_rows=copy)
+    for _ in range(2):                                    # twice into the same buffers
+        moe.moe_route_package(inp.X, inp.Wr, inp.bias, inp.placement, 0, logits=b["logits"],
+                              topk_idx=b["idx"], topk_gate=b["gate"], ws_route=ws_r,
+                              counts=b["counts"], coact=b["coact"], out=b["perm"], ws_perm=ws_p,
+                              cap_rows=cap, logits_in=logits_in, copy_rows=copy)
+    torch.cuda.synchronize()
+    flat = lambda s: {**{n: v for n, v in s.items() if n != "perm"}, **s["perm"]}   # noqa: E731
+    fa, fb = flat(a), flat(b)
+    for name in fa:
+        if fa[name] is not None:
+            assert torch.equal(fa[name], fb[name]), name
+    if T:
+        assert int(fa["counts"].sum()) == T * k
+        np.testing.assert_array_equal(np.bincount(fa["idx"].cpu().numpy().ravel(), minlength=E),
+                                      fa["counts"].cpu().numpy())
