@@ -261,6 +261,13 @@ __global__ __launch_bounds__(PERM_TOKENS) void perm_scatter_kernel(
 constexpr int SMALL_T = 1024;
 constexpr int SMALL_BLK = SMALL_T / PERM_TOKENS;
 constexpr int PLAN_IDS = 4096;
+constexpr int PLAN_U = 4;                // assignments a thread loads at a time
+
+// replica_lo for a short batch's counts (q <= 64, c <= SMALL_T): 32-bit, and no
+// division for an expert with one host
+__device__ __forceinline__ uint32_t replica_lo_small(int q, uint32_t c, int n) {
+    return n == 1 ? (q ? c : 0u) : (uint32_t)q * c / (uint32_t)n;
+}
 
 struct SmallArgs {
     const int32_t* idx;                  // [T][k] (KM == 0)
@@ -295,106 +302,127 @@ __global__ __launch_bounds__(SMALL_T) void perm_small_kernel(SmallArgs a, SlotTa
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int T = a.T, k = a.k, E = a.E, n_local = a.n_local;
     const int nblk = (int)ceil_div(T, PERM_TOKENS);
-    const int t = tid;
-    int ev[MOE_MAX_K];
-    float gv[MOE_MAX_K];
-    if (KM == 0 && t < T) {
-        load_ids(a.idx, t, k, ev);
-        load_gates(a.gate, t, k, gv);
-    }
+    // slots of wave 0's lanes, read before the first wait
+    int my_expert[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+        my_expert[c] = wave == 0 && lane + 64 * c < n_local ? ht.expert_of_slot[lane + 64 * c] : 0;
     for (int e = tid; e < E; e += SMALL_T) {
         slot_lds[e] = st.slot_of[e];
         cnt_s[e] = COUNT ? 0 : a.counts_in[e];
         hosts_s[e] = ht.hosts[e];
     }
     if (tid < MOE_MAX_G) send_s[tid] = 0;
-    for (int i = tid; i < SMALL_BLK * MOE_MAX_GROUPS; i += SMALL_T)
+    for (int i = tid; i < nblk * MOE_MAX_GROUPS; i += SMALL_T)
         bits[i / MOE_MAX_GROUPS][i % MOE_MAX_GROUPS] = 0ull;
     const bool coact = COUNT && a.coact != nullptr;
     if (coact)
         for (int i = tid; i < E * E; i += SMALL_T) co_s[i] = 0;
     if constexpr (KM > 0) topk_tokens<KM, C, 1>(a.scores, E, T, 0, E, k, a.renorm, ids_s, gates_s);
     __syncthreads();
-    if (KM > 0 && t < T) {
+    // The assignments i = t k + r, one per thread and PLAN_U per thread at a time: f(i,
+    // token, expert).  A loop over a token's k assignments by one thread each waited
+    // for k dependent LDS round trips.  (i + 0.5) / k truncates to the token exactly: n
+    // is at most 2^14.
+    const int n = T * k;
+    const int32_t* ids = KM > 0 ? ids_s : a.idx;
+    const float rk = 1.0f / (float)k;
+    auto each = [&](auto f) {
+        for (int i0 = tid; i0 < n; i0 += PLAN_U * SMALL_T) {
+            int e[PLAN_U];
 #pragma unroll
-        for (int r = 0; r < MOE_MAX_K; ++r) {
-            ev[r] = ids_s[t * k + (r < k ? r : k - 1)];
-            gv[r] = gates_s[t * k + (r < k ? r : k - 1)];
-        }
-    }
-    if (KM > 0)
-        for (int i = tid; i < T * k; i += SMALL_T) {
-            a.idx_out[i] = ids_s[i];
-            a.gate_out[i] = gates_s[i];
-        }
-    set_bits(ev, t < T, k, E, slot_lds, bits[wave], lane);
-    if (COUNT && t < T) {
+            for (int u = 0; u < PLAN_U; ++u) {
+                const int i = i0 + u * SMALL_T;
+                e[u] = ids[i < n ? i : i0];
+            }
 #pragma unroll
-        for (int r = 0; r < MOE_MAX_K; ++r) {
-            if (r >= k) break;
-            // out-of-range expert ids are ignored rather than counted out of bounds
-            if ((unsigned)ev[r] < (unsigned)E) atomicAdd(&cnt_s[ev[r]], 1);
-        }
-    }
-    if (coact) {
-        // thread i takes assignment (i / k, i % k) and adds its row of the token's k x k
-        // block
-        const int32_t* ids = KM > 0 ? ids_s : a.idx;
-        for (int i = tid; i < T * k; i += SMALL_T) {
-            const int tok = i / k;
-            const int e = ids[i];
-            if ((unsigned)e >= (unsigned)E) continue;
-            for (int q = 0; q < k; ++q) {
-                const int e2 = ids[tok * k + q];
-                if ((unsigned)e2 < (unsigned)E) atomicAdd(&co_s[e * E + e2], 1);
+            for (int u = 0; u < PLAN_U; ++u) {
+                const int i = i0 + u * SMALL_T;
+                if (i < n) f(i, (int)(((float)i + 0.5f) * rk), e[u]);
             }
         }
+    };
+    each([&](int i, int t, int e) {
+        // out-of-range expert ids are ignored rather than counted out of bounds
+        if ((unsigned)e >= (unsigned)E) return;
+        const int s = slot_lds[e];
+        if (s >= 0) atomicOr(&bits[t / PERM_TOKENS][s], 1ull << (t % PERM_TOKENS));
+        if (COUNT) atomicAdd(&cnt_s[e], 1);
+        if (coact)
+            for (int q = 0; q < k; ++q) {
+                const int e2 = ids[t * k + q];
+                if ((unsigned)e2 < (unsigned)E) atomicAdd(&co_s[e * E + e2], 1);
+            }
+    });
+    __syncthreads();
+    if (wave == 0) {
+        // replica range, group size and offset of every slot (at most 128)
+        int32_t carry = 0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int s = lane + 64 * c;
+            int32_t size = 0;
+            if (s < n_local) {
+                const uint64_t h = hosts_s[my_expert[c]];
+                const int hosts = __popcll(h);
+                const int q = a.dev == 0 ? 0 : __popcll(h & (~0ull >> (64 - a.dev)));
+                const uint32_t cnt = (uint32_t)cnt_s[my_expert[c]];
+                const uint32_t lo = replica_lo_small(q, cnt, hosts);
+                lo_s[s] = (int32_t)lo;
+                size = (int32_t)(replica_lo_small(q + 1, cnt, hosts) - lo);
+                size_s[s] = size;
+            }
+            const int32_t incl = wave_incl_scan(size, lane);
+            if (s < n_local) off_s[s + 1] = carry + incl;
+            carry += __shfl(incl, 63, 64);
+        }
+        if (lane == 0) off_s[0] = 0;
+    } else if (wave < 3) {
+        for (int s = tid - 64; s < n_local; s += 128) {
+            int32_t run = 0;
+            for (int b = 0; b < nblk; ++b) {
+                base[b][s] = run;
+                run += __popcll(bits[b][s]);
+            }
+        }
+    } else if (a.send_counts) {
+        for (int e = tid - 192; e < E; e += SMALL_T - 192) {
+            uint64_t h = hosts_s[e];
+            const uint32_t c = (uint32_t)cnt_s[e];
+            const int hosts = __popcll(h);
+            for (int q = 0; h; ++q, h &= h - 1ull)
+                atomicAdd(&send_s[__builtin_ctzll(h)],
+                          (int32_t)(replica_lo_small(q + 1, c, hosts) - replica_lo_small(q, c, hosts)));
+        }
     }
-    if (COUNT) __syncthreads();
-    if (a.send_counts) add_send_counts(cnt_s, hosts_s, E, tid, SMALL_T, send_s);
+    __syncthreads();
+    // the stores come after the last barrier: a barrier waits for those before it
+    each([&](int i, int t, int e) {
+        int32_t p = -1;
+        const int s = (unsigned)e < (unsigned)E ? (int)slot_lds[e] : -1;
+        if (s >= 0) {
+            const int b = t / PERM_TOKENS;
+            const int32_t rank =
+                base[b][s] + __popcll(bits[b][s] & ((1ull << (t % PERM_TOKENS)) - 1ull));
+            const int32_t lo = lo_s[s];
+            if (rank >= lo && rank < lo + size_s[s]) {
+                p = off_s[s] + (rank - lo);
+                a.row_token[p] = t;
+                a.row_gate[p] = KM > 0 ? gates_s[i] : a.gate[i];
+            }
+        }
+        a.token_row[i] = p;
+        if (KM > 0) {
+            a.idx_out[i] = e;
+            a.gate_out[i] = gates_s[i];
+        }
+    });
+    for (int sl = tid; sl <= n_local; sl += SMALL_T) a.group_offsets[sl] = off_s[sl];
+    if (a.send_counts && tid < a.G) a.send_counts[tid] = send_s[tid];
     if (COUNT)
         for (int e = tid; e < E; e += SMALL_T) a.counts[e] = cnt_s[e];
     if (coact)
         for (int i = tid; i < E * E; i += SMALL_T) a.coact[i] = co_s[i];
-    __syncthreads();
-    if (tid < n_local) {
-        int32_t run = 0;
-        for (int b = 0; b < nblk; ++b) {
-            base[b][tid] = run;
-            run += __popcll(bits[b][tid]);
-        }
-        const int e = ht.expert_of_slot[tid];
-        const uint64_t h = hosts_s[e];
-        const int n = __popcll(h);
-        const int q = a.dev == 0 ? 0 : __popcll(h & (~0ull >> (64 - a.dev)));
-        const int64_t lo = replica_lo(q, cnt_s[e], n);
-        lo_s[tid] = (int32_t)lo;
-        size_s[tid] = (int32_t)(replica_lo(q + 1, cnt_s[e], n) - lo);
-    }
-    if (a.send_counts && tid < a.G) a.send_counts[tid] = send_s[tid];
-    __syncthreads();
-    if (wave == 0) wave_offsets(size_s, n_local, off_s, lane);
-    __syncthreads();
-    for (int sl = tid; sl <= n_local; sl += SMALL_T) a.group_offsets[sl] = off_s[sl];
-    if (t >= T) return;
-    const unsigned long long lower = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int r = 0; r < MOE_MAX_K; ++r) {
-        if (r >= k) break;
-        const int e = ev[r];
-        int32_t p = -1;
-        const int sl = (unsigned)e < (unsigned)E ? (int)slot_lds[e] : -1;
-        if (sl >= 0) {
-            const int32_t rank = base[wave][sl] + __popcll(bits[wave][sl] & lower);
-            const int32_t lo = lo_s[sl];
-            if (rank >= lo && rank < lo + size_s[sl]) {
-                p = off_s[sl] + (rank - lo);
-                a.row_token[p] = t;
-                a.row_gate[p] = gv[r];
-            }
-        }
-        a.token_row[t * k + r] = p;
-    }
 }
 
 template <typename U>
@@ -544,13 +572,13 @@ int launch_small_topk(const SmallArgs& a, const SlotTable& st, const HostTable& 
     }
 }
 
-// Whether the packaging launch also takes the top-k: at most two passes of its 1024
+// Whether the packaging launch also takes the top-k: at most one pass of its 1024
 // threads (L lanes a token), and the ids within PLAN_IDS.  Measured per step against
 // the top-k launch of its own, see launch_route_package.
 bool plan_topk(int64_t T, int k, int E) {
     const int C = topk_class(E);
     const int L = C == 0 ? 4 : C <= 2 ? 8 : C == 3 ? 16 : 32;
-    return T * L <= 2 * SMALL_T && T * k <= PLAN_IDS;
+    return T * L <= SMALL_T && T * k <= PLAN_IDS;
 }
 
 }  // namespace

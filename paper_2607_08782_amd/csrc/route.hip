@@ -172,7 +172,7 @@ __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
     finish_tokens<KM, C, 1>(Sm, ldS, nt, t0, E, k, renorm, bias, logits, idx, gate);
 }
 
-// bf16 gate scores of short batches (few token blocks, e.g. decode): one 16-wave
+// bf16 gate scores of short batches (few token blocks, e.g. decode): one 8-wave
 // workgroup per (16 tokens, 16 experts) on MFMA 16x16x32, the waves splitting K,
 // every operand load of a wave's slice issued before its first product (up to 8
 // K steps at a time), the 16 partial tiles summed in wave order through LDS.  Rows
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
 // descriptors.  Bound by load latency: the scores leave finished, where K chunks on
 // separate workgroups left up to 32 partial scores each for the top-k's launch to
 // read back.
-constexpr int SS_WAVES = 16;
+constexpr int SS_WAVES = 8;
 constexpr int SS_STEPS = 8;            // 32-wide K steps of loads issued at once
 
 __global__ __launch_bounds__(SS_WAVES * 64) void score_small_kernel(
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(SS_WAVES * 64) void score_small_kernel(
         (void*)(W + (int64_t)e0 * d), (short)0, ne * d * 2, RB_RSRC_WORD3);
     // the thread that finishes (token r, expert e): its bias, loaded beside the operands
     const int r = (tid >> 4) & 15, e = tid & 15;
-    const float b = bias && tid < 256 && e < ne ? bias[e0 + e] : 0.f;
+    const float b = bias && e < ne ? bias[e0 + e] : 0.f;
     const int nsteps = (d + 31) / 32;
     const int sbeg = wave * nsteps / SS_WAVES, send = (wave + 1) * nsteps / SS_WAVES;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};

@@ -222,6 +222,8 @@ __device__ __forceinline__ void topk_tokens(const float* S, int ldS, int nt, int
     const int tid = threadIdx.x, groups = blockDim.x / L;
     const int grp = tid / L, g = tid % L;
     for (int base = 0; base < nt; base += groups * NT) {
+        // a whole wave without tokens leaves (its groups come after every valid one)
+        if (base + (tid & ~63) / L >= nt) break;
         const float* sp[NT];
         bool valid[NT];
         int32_t* ip[NT];
