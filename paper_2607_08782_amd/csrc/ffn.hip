@@ -876,34 +876,39 @@ __global__ __launch_bounds__(ST_THREADS, ST_WG_PER_CU) void stream_gemm_kernel(S
 // ---------------------------------------------------------------------------
 // Strips: the streamed groups' products where K is short (strip_product): one
 // launch, no split of K over workgroups, no partial sums and no launch to add
-// them.  A workgroup takes M rows of a group x 64 weight rows (SwiGLU: 32 gate and
-// the matching 32 up rows) over the whole of K; both operands go straight into an
-// LDS ring of R 64-wide K stages, R - 1 in flight.  What bounds it: at decode the
-// latency of the launch and of the first loads, then the weight stream; an item of
-// the split kernel reads a few K steps only and pays for the partial sums' round
-// trip and the second launch.  Waves 2 x 2, each M / 2 rows x 32 weight rows;
-// 128-byte LDS rows, 16-byte chunk c of row r at c ^ (r & 7) (conflict-free for the
-// fragment reads); weights as the MFMA's A operand, so a lane holds 4 consecutive
-// output columns of one row.  Every sum runs over K in ascending stages, whatever
-// M and R, so the choice of shape does not change the bits.
+// them.  A workgroup takes up to 64 rows of a group x 64 weight rows (SwiGLU: 32 gate
+// and the matching 32 up rows) over the whole of K; both operands go straight into an
+// LDS ring of R 64-wide K stages.  What bounds it: at decode the latency of the launch
+// and of the first loads, then the weight stream; an item of the split kernel reads a
+// few K steps only and pays for the partial sums' round trip and the second launch.
+// At the barrier of stage t the fragments of stage t are in registers and stage t + 1
+// has landed: its fragments come from LDS and stage t + R into the ring while stage t
+// multiplies.  The tile is as high as its rows need (32 or 64: fewer LDS bytes per
+// stage and more stages in the same LDS; one token, DeepSeek-V2-Lite: 40.3 -> 34.4 us
+// a step; a third height of 16 gained nothing); three workgroups fit a CU.  128-byte LDS
+// rows, 16-byte chunk c of row r at c ^ (r & 7) (conflict-free for the fragment
+// reads); weights as the MFMA's A operand, so a lane holds 4 consecutive output
+// columns of one row.  Every sum runs over K in ascending stages, whatever the height.
 // ---------------------------------------------------------------------------
+constexpr int SP_M = 64;                 // rows per tile, at most
 constexpr int SP_N = 64;                 // weight rows per tile
 constexpr int SP_THREADS = 256;
 constexpr int SP_ROWB = 128;             // LDS row bytes: 64 K
+constexpr int SP_WG_PER_CU = 3;
+constexpr int strip_lds(int M, int R) { return R * (M + SP_N) * SP_ROWB; }
+constexpr int SP_R32 = 4, SP_R64 = 3;    // ring stages by tile height
+constexpr int SP_LDS = strip_lds(64, SP_R64);
+static_assert(strip_lds(32, SP_R32) <= SP_LDS, "ring size");
 constexpr int STRIP_MAX_K = 2048;
 
-template <bool SWIGLU, bool GATHER, int M, int R>
-__global__ __launch_bounds__(SP_THREADS, 2) void strip_gemm_kernel(StreamArgs args) {
+template <bool SWIGLU, bool GATHER>
+__global__ __launch_bounds__(SP_THREADS, SP_WG_PER_CU) void strip_gemm_kernel(StreamArgs args) {
 #ifdef __HIP_DEVICE_COMPILE__
     extern __shared__ __attribute__((aligned(1024))) char strip_ring[];
     __shared__ int s_off[MOE_MAX_GROUPS + 1], s_tstart[MOE_MAX_GROUPS + 1];
-    constexpr int SA = M * SP_ROWB, STAGE = SA + SP_N * SP_ROWB;
-    constexpr int NA = M / 32, NB = SP_N / 32, P = NA + NB;    // 1 KB loads per wave per stage
-    constexpr int MT = M / 32;                                 // 16-row tiles per wave
     constexpr int OUT = SWIGLU ? SP_N / 2 : SP_N;              // output columns per tile
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave & 1, wn = wave >> 1;
     const int n_groups = args.n_groups, K = args.K;
     const int n_out = SWIGLU ? args.N / 2 : args.N;
     const int nt = n_out / OUT;
@@ -916,7 +921,7 @@ __global__ __launch_bounds__(SP_THREADS, 2) void strip_gemm_kernel(StreamArgs ar
         for (int g0 = 0; g0 < n_groups; g0 += 64) {
             const int g = g0 + lane;
             const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
-            const int v = rows <= lim || args.zero_big ? (int)ceil_div(rows, M) * nt : 0;
+            const int v = rows <= lim || args.zero_big ? (int)ceil_div(rows, SP_M) * nt : 0;
             const int incl = wave_incl_scan(v, lane);
             if (g < n_groups) s_tstart[g + 1] = carry + incl;
             carry += __shfl(incl, 63, 64);
@@ -931,22 +936,20 @@ __global__ __launch_bounds__(SP_THREADS, 2) void strip_gemm_kernel(StreamArgs ar
     // load i of a wave fills LDS rows 32 i + 8 wave + lane / 8, chunk slot lane % 8
     const int lrow = 8 * wave + (lane >> 3);
     const int kc = ((lane & 7) ^ ((lane >> 3) & 7)) * 8;
-    const int wvoff = ((SWIGLU ? lrow : w_order(lrow)) * K + kc) * 2;
     const int frow = lane & 15;
-    const int c0 = ((lane >> 4) ^ (frow & 7)) * 16, c1 = c0 ^ 64;
-    const int a_frag = (wm * (M / 2) + frow) * SP_ROWB;
-    const int b_frag = SA + (wn * (SWIGLU ? 16 : 32) + frow) * SP_ROWB;
-    constexpr int B_STEP = (SWIGLU ? 32 : 16) * SP_ROWB;       // second column tile
+    const int c0 = ((lane >> 4) ^ (frow & 7)) * 16;
 
     for (int tile = t_begin + blockIdx.x / NUM_XCD; tile < t_end; tile += gridDim.x / NUM_XCD) {
         const int g = __builtin_amdgcn_readfirstlane(last_le(s_tstart, n_groups, tile));
         const int start = __builtin_amdgcn_readfirstlane(s_off[g]);
         const int rows = __builtin_amdgcn_readfirstlane(s_off[g + 1]) - start;
-        const int mt = (rows + M - 1) / M;
+        const int mt = (rows + SP_M - 1) / SP_M;
         const int local = tile - __builtin_amdgcn_readfirstlane(s_tstart[g]);
         const int m = local % mt, n0 = (local / mt) * OUT;
-        const int row0 = start + m * M, rows_valid = min(M, rows - m * M);
-        const int nst = rows <= lim ? K / 64 : 0;
+        const int row0 = start + m * SP_M, rows_valid = min(SP_M, rows - m * SP_M);
+        // uniform (the compiler loops over the lanes' values for a descriptor it cannot
+        // prove to be)
+        const int nst = __builtin_amdgcn_readfirstlane(rows <= lim ? K / 64 : 0);
         // rows past the group read as zero or leave LDS as it is: not stored either way
         const __amdgpu_buffer_rsrc_t ar =
             GATHER ? __builtin_amdgcn_make_buffer_rsrc((void*)args.a, (short)0, args.a_total * K * 2,
@@ -959,80 +962,127 @@ __global__ __launch_bounds__(SP_THREADS, 2) void strip_gemm_kernel(StreamArgs ar
         const __amdgpu_buffer_rsrc_t ur = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(W + (int64_t)(SWIGLU ? n_out : 0) * K), (short)0, (SWIGLU ? 32 : SP_N) * K * 2,
             RSRC_WORD3);
-        int av[NA];
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int rin = lrow + 32 * i;
-            av[i] = !GATHER ? (rin * K + kc) * 2
-                    : rin < rows_valid ? (args.a_rows[row0 + rin] * K + kc) * 2 : A_OOB;
-        }
-        auto dma = [&](int s) {
-            char* base = strip_ring + (s % R) * STAGE + wave * 1024;
-            const int so = s * SP_ROWB;
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    SWIGLU && i ? ur : br, (lds_void*)(base + SA + i * 4096), 16,
-                    wvoff + (SWIGLU ? 0 : i * 64 * K), so, 0, 0);
-#pragma unroll
-            for (int i = 0; i < NA; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(ar, (lds_void*)(base + i * 4096), 16, av[i], so,
-                                                         0, 0);
-        };
-        f32x4 acc[MT][2];
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < R - 1; ++s)
-            if (s < nst) dma(s);
-        for (int t = 0; t < nst; ++t) {
-            // stage t has landed; the R - 2 after it may still fly
-            if (nst - 1 - t >= R - 2) wait_vm<(R - 2) * P>();
-            else wait_vm<0>();
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (t + R - 1 < nst) dma(t + R - 1);
-            const char* st = strip_ring + (t % R) * STAGE;
-            // row tiles past the group are left out (uniform across the wave)
-            const int live = rows_valid - wm * (M / 2);
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int cq = q ? c1 : c0;
-                const bf16x8 b0 = *(const bf16x8*)(st + b_frag + cq);
-                const bf16x8 b1 = *(const bf16x8*)(st + b_frag + B_STEP + cq);
-#pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    if (i * 16 >= live) break;
-                    const bf16x8 a = *(const bf16x8*)(st + a_frag + i * 16 * SP_ROWB + cq);
-                    acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b0, a, acc[i][0], 0, 0, 0);
-                    acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a, acc[i][1], 0, 0, 0);
-                }
-            }
-        }
+        const __amdgpu_buffer_rsrc_t none =
+            __builtin_amdgcn_make_buffer_rsrc((void*)args.a, (short)0, 0, RSRC_WORD3);
         const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(args.out + (int64_t)row0 * args.ldo), (short)0, rows_valid * args.ldo * 2,
             RSRC_WORD3);
+
+        // the tile at a height of M rows: waves 2 x 2, each M / 2 rows x 32 weight rows
+        // (SwiGLU: 16 gate, 16 up)
+        auto run = [&](auto height, auto ring) {
+            constexpr int M = decltype(height)::value, R = decltype(ring)::value;
+            constexpr int SA = M * SP_ROWB, STAGE = SA + SP_N * SP_ROWB;
+            constexpr int NA = M / 32, NB = SP_N / 32, P = NA + NB;   // 1 KB loads a wave a stage
+            constexpr int MT = M / 32;                             // 16-row tiles per wave
+            const int wm = wave & 1, wn = wave >> 1;
+            const int a_frag = (wm * (M / 2) + frow) * SP_ROWB;
+            const int b_frag = SA + (wn * (SWIGLU ? 16 : 32) + frow) * SP_ROWB;
+            constexpr int B_STEP = (SWIGLU ? 32 : 16) * SP_ROWB;   // second column tile
+            const int wvoff = ((SWIGLU ? lrow : w_order(lrow)) * K + kc) * 2;
+            int av[NA];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            const int row_in = wm * (M / 2) + i * 16 + frow;
-            if constexpr (SWIGLU) {
-                float v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = silu(acc[i][0][r]) * acc[i][1][r];
-                const u32x2 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-                __builtin_amdgcn_raw_buffer_store_b64(
-                    w, orsrc, (row_in * args.ldo + n0 + wn * 16 + (lane >> 4) * 4) * 2, 0, 0);
-            } else {
-                const u32x4 w = {pack_bf16x2(acc[i][0][0], acc[i][0][1]),
-                                 pack_bf16x2(acc[i][0][2], acc[i][0][3]),
-                                 pack_bf16x2(acc[i][1][0], acc[i][1][1]),
-                                 pack_bf16x2(acc[i][1][2], acc[i][1][3])};
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    w, orsrc, (row_in * args.ldo + n0 + wn * 32 + (lane >> 4) * 8) * 2, 0, 0);
+            for (int i = 0; i < NA; ++i) {
+                const int rin = lrow + 32 * i;
+                av[i] = !GATHER ? (rin * K + kc) * 2
+                        : rin < rows_valid ? (args.a_rows[row0 + rin] * K + kc) * 2 : A_OOB;
             }
-        }
-        // every wave is done with the ring before the next tile refills it
+            // stage s into slot s % R; past the tile's K: empty ranges, loads without
+            // traffic, so that the counts the waits rely on stay the same
+            auto dma = [&](int s) {
+                char* base = strip_ring + (s % R) * STAGE + wave * 1024;
+                const int so = s * SP_ROWB;
+                const bool in = s < nst;
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        in ? (SWIGLU && i ? ur : br) : none, (lds_void*)(base + SA + i * 4096), 16,
+                        wvoff + (SWIGLU ? 0 : i * 64 * K), so, 0, 0);
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(in ? ar : none,
+                                                             (lds_void*)(base + i * 4096), 16, av[i],
+                                                             so, 0, 0);
+            };
+            f32x4 acc[MT][2];
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            struct Frags {
+                bf16x8 a[2][MT], b[2][2];                   // two 32-wide K steps
+            };
+            auto read = [&](int s, Frags& f) {
+                const char* st = strip_ring + (s % R) * STAGE;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int cq = c0 ^ (q * 64);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        f.b[q][j] = *(const bf16x8*)(st + b_frag + j * B_STEP + cq);
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+                        f.a[q][i] = *(const bf16x8*)(st + a_frag + i * 16 * SP_ROWB + cq);
+                }
+            };
+            auto step = [&](int t, const Frags& f, Frags& next) {
+                // stage t + 1 has landed (the R - 2 after it may still fly), and every
+                // wave holds its fragments of stage t
+                wait_vm<(R - 2) * P>();
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                read(t + 1, next);
+                dma(t + R);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                f.b[q][j], f.a[q][i], acc[i][j], 0, 0, 0);
+            };
+            if (nst > 0) {
+                Frags f0, f1;
+#pragma unroll
+                for (int s = 0; s < R; ++s) dma(s);
+                wait_vm<(R - 1) * P>();
+                asm volatile("s_barrier" ::: "memory");
+                read(0, f0);
+                int t = 0;
+                for (; t + 1 < nst; t += 2) {
+                    step(t, f0, f1);
+                    step(t + 1, f1, f0);
+                }
+                if (t < nst) step(t, f0, f1);
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const int row_in = wm * (M / 2) + i * 16 + frow;
+                const int quad = lane >> 4;
+                if constexpr (SWIGLU) {
+                    float v[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = silu(acc[i][0][r]) * acc[i][1][r];
+                    const u32x2 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+                    __builtin_amdgcn_raw_buffer_store_b64(
+                        w, orsrc, (row_in * args.ldo + n0 + wn * 16 + quad * 4) * 2, 0, 0);
+                } else {
+                    const u32x4 w = {pack_bf16x2(acc[i][0][0], acc[i][0][1]),
+                                     pack_bf16x2(acc[i][0][2], acc[i][0][3]),
+                                     pack_bf16x2(acc[i][1][0], acc[i][1][1]),
+                                     pack_bf16x2(acc[i][1][2], acc[i][1][3])};
+                    __builtin_amdgcn_raw_buffer_store_b128(
+                        w, orsrc, (row_in * args.ldo + n0 + wn * 32 + quad * 8) * 2, 0, 0);
+                }
+            }
+        };
+        if (rows_valid <= 32)
+            run(std::integral_constant<int, 32>{}, std::integral_constant<int, SP_R32>{});
+        else
+            run(std::integral_constant<int, 64>{}, std::integral_constant<int, SP_R64>{});
+        // every wave is done with the ring, and no load for it is on its way, before the
+        // next tile (of another height, perhaps) refills it or the workgroup ends
+        wait_vm<0>();
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
 #endif
@@ -1317,23 +1367,11 @@ static bool strip_product(int K, int64_t cap_rows, int n_groups) {
 }
 
 template <bool SWIGLU, bool GATHER>
-static int launch_strips(const StreamArgs& a, int64_t max_rows, int cus, hipStream_t s) {
-    const dim3 grid((unsigned)(2 * cus / NUM_XCD * NUM_XCD)), block(SP_THREADS);
-    // groups of at most 64 rows (max_rows bounds them): half the rows per tile, one
-    // stage more in flight in the same LDS
-#define MOE_STRIPS(M, R)                                                                         \
-    do {                                                                                         \
-        static LdsGrant grant;                                                                   \
-        constexpr int lds = R * (M + SP_N) * SP_ROWB;                                            \
-        if (allow_dynamic_lds((const void*)strip_gemm_kernel<SWIGLU, GATHER, M, R>, lds,         \
-                              grant) != MOE_OK)                                                  \
-            return MOE_ERR_DEVICE;                                                               \
-        hipLaunchKernelGGL((strip_gemm_kernel<SWIGLU, GATHER, M, R>), grid, block, lds, s, a);   \
-    } while (0)
-    if (max_rows <= 64) MOE_STRIPS(64, 4);
-    else MOE_STRIPS(128, 3);
-#undef MOE_STRIPS
-    return MOE_OK;
+static int launch_strips(const StreamArgs& a, int cus, hipStream_t s) {
+    hipLaunchKernelGGL((strip_gemm_kernel<SWIGLU, GATHER>),
+                       dim3((unsigned)(SP_WG_PER_CU * cus / NUM_XCD * NUM_XCD)), dim3(SP_THREADS),
+                       SP_LDS, s, a);
+    return launch_status();
 }
 
 int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, int n_groups,
@@ -1434,8 +1472,6 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
     s1.product = 0;
     s1.lim0 = a1.lim0;
     s1.zero_big = 0;
-    // a group's rows: at most every token once where the row map tells their number
-    const int64_t max_rows = a_rows && a_total < cap_rows ? a_total : cap_rows;
     // the chunk sums' launch: nothing streamed to add up when the strips did it
     auto reduce_args = [](StreamArgs r, bool strips) {
         if (strips) {
@@ -1447,8 +1483,8 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
     const bool strips1 = strip_product(d, cap_rows, n_groups);
     if (up) {
         if (!large && strips1) {
-            const int st = a_rows ? launch_strips<true, true>(s1, max_rows, cus, s)
-                                  : launch_strips<true, false>(s1, max_rows, cus, s);
+            const int st = a_rows ? launch_strips<true, true>(s1, cus, s)
+                                  : launch_strips<true, false>(s1, cus, s);
             if (st != MOE_OK) return st;
         } else if (!large && a_rows)
             hipLaunchKernelGGL(stream_gemm_kernel<true>, dim3(sgrid), dim3(ST_THREADS), 0, s, s1);
@@ -1493,7 +1529,7 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
             s2.out = (bf16_t*)part;
             s2.zero_big = 1;
         }
-        const int st = launch_strips<false, false>(s2, max_rows, cus, s);
+        const int st = launch_strips<false, false>(s2, cus, s);
         if (st != MOE_OK) return st;
         if (combine != nullptr) {
             const CombineArgs& cb = *(const CombineArgs*)combine;
