@@ -208,7 +208,10 @@ __device__ __forceinline__ TilePos tile_pos(int local, int mt, int n_tiles) {
 // launch is short and latency-bound: every workgroup still runs several K
 // stages of a 256 x 256 tile, on a fraction of the CUs.  Streaming every group
 // of up to SMALL_ROWS_MAX rows instead spreads the weight reads over all CUs
-// (a DeepSeek-V2-Lite-shaped decode step: 219 -> 188 us).  Otherwise the small
+// (a DeepSeek-V2-Lite-shaped decode step: 219 -> 188 us).  Only when no group is
+// larger still: a call that tiles one group anyway tiles them all, in one launch's
+// rounds instead of two launches (777 tokens of the Mixtral shape, groups of about
+// 500 and 120 rows: step 344 -> 325 us).  Otherwise the small
 // groups join the tiled launch, whose rounds leave CUs free for their tiles,
 // rather than stream in a launch of their own after it (the two run one after
 // the other): DeepSeek-V2-Lite prefill FFN 364 -> 332 us, Qwen1.5 batch 137 ->
@@ -217,15 +220,21 @@ __device__ __forceinline__ void small_limits(const int* s_off, int n_groups, int
                                              int tiles_down, int split_units, int lane,
                                              int& lim_up, int& lim_down) {
     int mt = 0;                                      // 256-row tiles of the groups > SMALL_ROWS
+    int most = 0;
     for (int g0 = 0; g0 < n_groups; g0 += 64) {
         const int g = g0 + lane;
         const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
         mt += rows > SMALL_ROWS ? (int)ceil_div(rows, BM) : 0;
+        most = max(most, rows);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mt += __shfl_xor(mt, o, 64);
-    lim_up = 4 * mt * tiles_up <= split_units ? SMALL_ROWS_MAX : 0;
-    lim_down = 4 * mt * tiles_down <= split_units ? SMALL_ROWS_MAX : 0;
+    for (int o = 32; o > 0; o >>= 1) {
+        mt += __shfl_xor(mt, o, 64);
+        most = max(most, __shfl_xor(most, o, 64));
+    }
+    const bool fits = most <= SMALL_ROWS_MAX;
+    lim_up = fits && 4 * mt * tiles_up <= split_units ? SMALL_ROWS_MAX : 0;
+    lim_down = fits && 4 * mt * tiles_down <= split_units ? SMALL_ROWS_MAX : 0;
 }
 
 // Persistent grouped NT GEMM: 4 waves (2 x 2), one per SIMD, each a 128 x 128
@@ -899,7 +908,7 @@ constexpr int strip_lds(int M, int R) { return R * (M + SP_N) * SP_ROWB; }
 constexpr int SP_R32 = 4, SP_R64 = 3;    // ring stages by tile height
 constexpr int SP_LDS = strip_lds(64, SP_R64);
 static_assert(strip_lds(32, SP_R32) <= SP_LDS, "ring size");
-constexpr int STRIP_MAX_K = 2048;
+constexpr int STRIP_MAX_K = 4096;
 
 template <bool SWIGLU, bool GATHER>
 __global__ __launch_bounds__(SP_THREADS, SP_WG_PER_CU) void strip_gemm_kernel(StreamArgs args) {
@@ -1359,9 +1368,10 @@ size_t grouped_ffn_ws_bytes(int dtype, int64_t cap_rows, int d, int f, int n_gro
 
 // Whether the streamed groups of a product run as strips: K short enough for one
 // workgroup to walk, and a call whose rows may all lie in streamed groups (which
-// also bounds the rows the fused combine keeps in the workspace).  A longer K (the
-// Mixtral-shaped layers' 4096 and 14336) leaves too few strips of too long a chain:
-// there K is split over workgroups.
+// also bounds the rows the fused combine keeps in the workspace).  A longer K leaves
+// too few strips of too long a chain, and is split over workgroups (Mixtral-shaped
+// decode step: the gate/up product, K = 4096, as strips 178.6 -> 176.0 us, the down
+// product too, K = 14336, 216).
 static bool strip_product(int K, int64_t cap_rows, int n_groups) {
     return K <= STRIP_MAX_K && cap_rows <= (int64_t)SMALL_ROWS_MAX * n_groups;
 }

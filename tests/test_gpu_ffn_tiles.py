@@ -1,6 +1,6 @@
 """The bf16 expert FFN at the edges of its kernels: tiles of 256 rows and their LDS
 ring (K of one and two 64-wide steps, column tails, row tiles in blocks of eight, many
-tiles a workgroup), whole-K strips (32 output columns, 64- and 128-row tiles, K from
+tiles a workgroup), whole-K strips (32 output columns, 32- and 64-row tiles, K from
 64 to their longest), each against the oracle's expert FFN in float64 on sampled rows.
 The tolerance is the parity protocol's: h and y are rounded to bf16 (2^-9 relative
 each), sums in fp32."""
@@ -26,10 +26,10 @@ LARGE, SMALL = moe.MOE_FFN_LARGE_GROUPS, moe.MOE_FFN_SMALL_GROUPS
     ([4500, 260], 128, 128, LARGE, True),           # 18 row tiles: three blocks of six
     ([300] * 20, 64, 128, LARGE, False),
     ([1, 64, 33, 0, 17], 64, 64, SMALL, True),      # strips, one K stage
-    ([1, 64, 33, 0, 17], 2048, 128, SMALL, True),   # longest K, 64-row tiles
-    ([128, 129, 256, 65], 192, 2048, SMALL, False),   # 128-row tiles and tails
-    ([200, 3], 2112, 128, SMALL, False),            # gate/up split over workgroups, down a strip
-    ([40, 90], 128, 2112, SMALL, True),             # and the reverse
+    ([1, 64, 33, 0, 17], 4096, 128, SMALL, True),   # longest K, both tile heights
+    ([128, 129, 256, 65], 192, 2048, SMALL, False),   # several row tiles and tails
+    ([200, 3], 4160, 128, SMALL, False),            # gate/up split over workgroups, down a strip
+    ([40, 90], 128, 4160, SMALL, True),             # and the reverse
     ([30, 5, 64], 256, 128, 0, False),              # no hint
     ([700, 5, 64, 200], 256, 128, 0, True),
 ])
