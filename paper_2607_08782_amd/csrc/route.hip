@@ -368,16 +368,9 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
     }
     if (!(flags & MOE_LOGITS_IN)) {
         const int St = score_tiles_split(T, 2 * d, E, true);
-        if (St == 1 && E <= 64) {
-            // long batch over 33-64 experts: the tiled score kernel with its top-k in
-            // the same launch (scores + bias to `logits` when requested).  Wider E
-            // keeps the separate top-k launch: there the workgroup's own top-k (more
-            // lanes per token, more passes over its 64 tokens) cost more than the
-            // launch it saves (E = 128: 33.4 -> 34.6 us, E = 256: 35 -> 45 us per call;
-            // E = 64: 22.8 -> 21.5 us)
-            return launch_score_tiles_topk(x, w, bias, T, 2 * d, E, k, renorm, logits, idx, gate,
-                                           s);
-        }
+        if (St == 1 && E <= SCORE_TOPK_MAX_E)
+            return launch_score_tiles_topk(false, x, w, nullptr, nullptr, bias, T, 2 * d, E, k,
+                                           renorm, logits, idx, gate, s);
         float* out = logits ? logits : (float*)ws;
         given = out;
         if (St == 1) {
