@@ -132,111 +132,97 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(
     Vec<Elem, V>::store(y + t * d + col, acc);
 }
 
-// Rows that are a whole number of wave widths (every lane of a wave serves the
-// same token): the token's local rows are compacted in registers (ascending r,
-// by selects, no indexed registers), their count is uniform across the wave,
-// and one of KM + 1 straight paths issues exactly that many row loads at once.
-// At k = 8 with about two local rows per token this issues a quarter of the
-// loads of the kernel above; the sum is the same, in the same order.
-template <typename Elem, int V, int N>
-__device__ __forceinline__ void combine_rows(const Elem* __restrict__ y_perm, const int32_t* q,
-                                             const float* h, int d, int col, float* acc) {
-    if constexpr (N > 0) {
-        float v[N][V];
+// Rows that are a whole number of wave widths: a wave serves CH chunks per lane of one
+// token.  Lane r holds the token's assignment r, a ballot says which have a row here, and
+// their row numbers and gates come out of the lanes in ascending r as scalars, so exactly
+// the loads of the local rows are issued.  The sum is that of the kernel above, in the same
+// order.  Bound by the memory rate; with a copy of the k indices and their compaction in
+// every lane the vector unit was (16384 tokens, d = 2048, k = 8, two local rows a token).
+// N rows from the head of the list `here` (a bit per assignment), those past its end row 0
+// of y_perm, loaded and dropped.
+template <typename Elem, int V, int CH, int N>
+__device__ __forceinline__ void combine_rows(const Elem* __restrict__ y_perm, int p, float g,
+                                             uint64_t& here, int d, int col, float (&acc)[CH][V]) {
+    float v[N][CH][V], h[N];
+    bool ok[N];
 #pragma unroll
-        for (int j = 0; j < N; ++j) Vec<Elem, V>::load(y_perm + (int64_t)q[j] * d + col, v[j]);
+    for (int j = 0; j < N; ++j) {
+        ok[j] = here != 0;
+        const int r = ok[j] ? __builtin_ctzll(here) : 0;
+        const int row = ok[j] ? __builtin_amdgcn_readlane(p, r) : 0;
+        h[j] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(g), r));
+        here &= here - 1;
 #pragma unroll
-        for (int j = 0; j < N; ++j)
-#pragma unroll
-            for (int i = 0; i < V; ++i) acc[i] = fmaf(h[j], v[j][i], acc[i]);
+        for (int c = 0; c < CH; ++c)
+            Vec<Elem, V>::load(y_perm + (int64_t)row * d + col + c * 64 * V, v[j][c]);
     }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        if (ok[j])
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int i = 0; i < V; ++i) acc[c][i] = fmaf(h[j], v[j][c][i], acc[c][i]);
 }
 
-template <typename Elem, int V, int KM>
-__global__ __launch_bounds__(COMBINE_THREADS) void combine_compact_kernel(
+template <typename Elem, int V, int CH>
+__global__ __launch_bounds__(COMBINE_THREADS) void combine_wave_kernel(
     const Elem* __restrict__ y_perm, const int32_t* __restrict__ token_row,
-    const float* __restrict__ gate, const Elem* __restrict__ y_shared, int n_shared, int64_t T,
-    int d, int k, int chunks_per_row, Elem* __restrict__ y) {
-    const int64_t gid = (int64_t)blockIdx.x * COMBINE_THREADS + threadIdx.x;
-    const int64_t t = gid / chunks_per_row;
-    const int c = (int)(gid - t * chunks_per_row);
-    if (t >= T) return;                      // whole waves: T * chunks_per_row is a multiple of 64
-    const int col = c * V;
-    int32_t p[KM];
-    float g[KM];
+    const float* __restrict__ gate, const Elem* __restrict__ y_shared, int n_shared, int T,
+    int d, int k, int parts, Elem* __restrict__ y) {
+    // wave w: token w / parts, its chunks from (w % parts) * 64 CH
+    const int w = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (COMBINE_THREADS / 64) +
+                                                 (int)(threadIdx.x >> 6));
+    const int t = parts == 1 ? w : (int)((unsigned)w / (unsigned)parts);
+    if (t >= T) return;
+    const int lane = (int)(threadIdx.x & 63);
+    const int col = ((w - t * parts) * 64 * CH + lane) * V;
+    const int rr = lane < k ? lane : k - 1;
+    const int p = token_row[(int64_t)t * k + rr];
+    const float g = gate[(int64_t)t * k + rr];
+    uint64_t here = __ballot(lane < k && p >= 0);
+    float acc[CH][V];
 #pragma unroll
-    for (int r = 0; r < KM; ++r) {
-        const int rr = r < k ? r : k - 1;
-        p[r] = r < k ? token_row[t * k + rr] : -1;
-        g[r] = gate[t * k + rr];
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[c][i] = 0.f;
+    // all at once up to two, then two (four chunks a lane) or four at a time
+    constexpr int B = CH == 1 ? 4 : 2;
+    const int n = __popcll(here);
+    if (n == 1) combine_rows<Elem, V, CH, 1>(y_perm, p, g, here, d, col, acc);
+    else if (n == 2) combine_rows<Elem, V, CH, 2>(y_perm, p, g, here, d, col, acc);
+    else
+        while (here) combine_rows<Elem, V, CH, B>(y_perm, p, g, here, d, col, acc);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int64_t o = (int64_t)t * d + col + c * 64 * V;
+        add_shared<Elem, V>(y_shared, n_shared, (int64_t)T * d, o, acc[c]);
+        Vec<Elem, V>::store(y + o, acc[c]);
     }
-    // slot j of the compacted list takes the r with p[r] >= 0 and j local rows before it
-    int32_t q[KM];
-    float h[KM];
-#pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        q[j] = 0;
-        h[j] = 0.f;
-    }
-    int n = 0;
-#pragma unroll
-    for (int r = 0; r < KM; ++r) {
-        const bool here = p[r] >= 0;
-#pragma unroll
-        for (int j = 0; j <= r; ++j) {
-            const bool take = here && n == j;
-            q[j] = take ? p[r] : q[j];
-            h[j] = take ? g[r] : h[j];
-        }
-        n += here ? 1 : 0;
-    }
-    n = __builtin_amdgcn_readfirstlane(n);
-    float acc[V];
-#pragma unroll
-    for (int i = 0; i < V; ++i) acc[i] = 0.f;
-    static_assert(KM > 2, "the compacting combine serves k > 2");
-    switch (n) {
-        case 0: break;
-        case 1: combine_rows<Elem, V, 1>(y_perm, q, h, d, col, acc); break;
-        case 2: combine_rows<Elem, V, 2>(y_perm, q, h, d, col, acc); break;
-        case 3: combine_rows<Elem, V, 3>(y_perm, q, h, d, col, acc); break;
-        case 4: combine_rows<Elem, V, 4>(y_perm, q, h, d, col, acc); break;
-        default:
-            // more than four rows: four at a time, in order (slots past n hold row
-            // 0, which is loaded and dropped)
-#pragma unroll
-            for (int j0 = 0; j0 < KM; j0 += 4) {
-                if (j0 < n) {
-                    float v[4][V];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        Vec<Elem, V>::load(y_perm + (int64_t)q[j0 + j] * d + col, v[j]);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int i = 0; i < V; ++i)
-                            acc[i] = j0 + j < n ? fmaf(h[j0 + j], v[j][i], acc[i]) : acc[i];
-                }
-            }
-            break;
-    }
-    add_shared<Elem, V>(y_shared, n_shared, T * d, t * d + col, acc);
-    Vec<Elem, V>::store(y + t * d + col, acc);
 }
 
 template <typename Elem, int V, int KM>
 int launch_k(const void* y_perm, const int32_t* token_row, const float* gate, const void* y_shared,
              int n_shared, int64_t T, int d, int k, void* y, hipStream_t s) {
     const int chunks = d / V;
-    const int64_t blocks = ceil_div(T * chunks, COMBINE_THREADS);
-    if constexpr (KM > 2) {
-        if (chunks % 64 == 0) {
-            hipLaunchKernelGGL((combine_compact_kernel<Elem, V, KM>), dim3((unsigned)blocks),
-                               dim3(COMBINE_THREADS), 0, s, (const Elem*)y_perm, token_row, gate,
-                               (const Elem*)y_shared, n_shared, T, d, k, chunks, (Elem*)y);
-            return launch_status();
-        }
+    if (V > 1 && chunks % 64 == 0 && T * (chunks / 64) < ((int64_t)1 << 30)) {
+        // four chunks a lane when that leaves 32 waves per CU (8192 tokens, d = 2048, k = 8:
+        // 16.7 -> 14.8 us against the kernel before; 2048 tokens with one 5.8 -> 4.8), else
+        // one, and also with several shared slices, whose loads then go chunk by chunk
+        // (16384 tokens, four slices: 69.9 -> 72.4 us with four chunks)
+        const int ch = n_shared < 2 && chunks % 256 == 0 && T * (chunks / 256) >= 8192 ? 4 : 1;
+        const int parts = chunks / 64 / ch;
+        const unsigned blocks = (unsigned)ceil_div(T * parts, COMBINE_THREADS / 64);
+#define MOE_CW(CH)                                                                               \
+    hipLaunchKernelGGL((combine_wave_kernel<Elem, V, CH>), dim3(blocks), dim3(COMBINE_THREADS), \
+                       0, s, (const Elem*)y_perm, token_row, gate, (const Elem*)y_shared, n_shared, \
+                       (int)T, d, k, parts, (Elem*)y)
+        if (ch == 4) MOE_CW(4);
+        else MOE_CW(1);
+#undef MOE_CW
+        return launch_status();
     }
+    const int64_t blocks = ceil_div(T * chunks, COMBINE_THREADS);
     hipLaunchKernelGGL((combine_kernel<Elem, V, KM>), dim3((unsigned)blocks), dim3(COMBINE_THREADS),
                        0, s, (const Elem*)y_perm, token_row, gate, (const Elem*)y_shared, n_shared,
                        T, d, k, chunks, (Elem*)y);
