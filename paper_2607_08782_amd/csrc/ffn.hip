@@ -711,8 +711,15 @@ struct StreamPlan {
     int n_small, S, total, n_tiles;
 };
 
+// Row limit of the streamed groups.  Most calls of a few hundred rows a group stream
+// none (limit 0): the streaming launches and the chunk sums look at it first and leave
+// out their plans.
+__device__ __forceinline__ int stream_limit(const StreamArgs& a) {
+    return a.limits != nullptr ? a.limits[a.product] : a.lim0;
+}
+
 __device__ void make_stream_plan(const StreamArgs& a, StreamPlan& P, int nthreads) {
-    const int lim = a.limits != nullptr ? a.limits[a.product] : a.lim0;
+    const int lim = stream_limit(a);
     for (int g = threadIdx.x; g <= a.n_groups; g += nthreads)
         P.off[g] = group_start(a.offsets, a.lead, a.lead_rows, g);
     __syncthreads();
@@ -770,6 +777,7 @@ __global__ __launch_bounds__(ST_THREADS, ST_WG_PER_CU) void stream_gemm_kernel(S
     __shared__ __attribute__((aligned(16))) bf16_t Bs[ST_N * LDK];
     __shared__ StreamPlan P;
     __shared__ int s_item[4];
+    if (stream_limit(args) <= 0) return;
     make_stream_plan(args, P, ST_THREADS);
     if (P.total == 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -921,7 +929,8 @@ __global__ __launch_bounds__(SP_THREADS, SP_WG_PER_CU) void strip_gemm_kernel(St
     const int n_groups = args.n_groups, K = args.K;
     const int n_out = SWIGLU ? args.N / 2 : args.N;
     const int nt = n_out / OUT;
-    const int lim = args.limits != nullptr ? args.limits[args.product] : args.lim0;
+    const int lim = stream_limit(args);
+    if (lim <= 0 && !args.zero_big) return;                    // nothing streamed
     for (int g = tid; g <= n_groups; g += SP_THREADS)
         s_off[g] = group_start(args.offsets, args.lead, args.lead_rows, g);
     __syncthreads();
@@ -1187,8 +1196,7 @@ __global__ __launch_bounds__(ST_THREADS) void split_reduce_kernel(StreamArgs arg
     __shared__ StreamPlan P;
     __shared__ int t_off[MOE_MAX_GROUPS + 1], t_tstart[MOE_MAX_GROUPS + 1];
     const int tsplit = targs.part != nullptr ? *targs.split_info : 1;   // used at the end
-    // no group can be streamed (MOE_FFN_LARGE_GROUPS): no streaming plan to build
-    if (args.limits != nullptr || args.lim0 > 0) {
+    if (stream_limit(args) > 0) {
         make_stream_plan(args, P, ST_THREADS);
         stream_reduce<SWIGLU>(args, P);
     }
@@ -1245,7 +1253,7 @@ __global__ __launch_bounds__(ST_THREADS) void stream_reduce_combine_kernel(Strea
                                                                            CombineArgs cb) {
     __shared__ StreamPlan P;
     make_stream_plan(args, P, ST_THREADS);
-    const int lim = args.limits != nullptr ? args.limits[args.product] : args.lim0;
+    const int lim = stream_limit(args);
     const int S = P.S;
     const int d = args.N;
     const int chunks = d / 4;
