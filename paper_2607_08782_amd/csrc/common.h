@@ -143,6 +143,8 @@ int launch_topk_given(const float* scores, int64_t T, int E, int k, int flags, i
 
 int launch_histogram(const int32_t* idx, int64_t T, int k, int E, int32_t* counts, int32_t* coact,
                      hipStream_t s);
+// co-activation counts added to coact (already cleared)
+int launch_coact(const int32_t* idx, int64_t T, int k, int E, int32_t* coact, hipStream_t s);
 
 struct PermuteTables {
     uint64_t hosts[MOE_MAX_E];          // bit j set iff GPU j hosts expert e

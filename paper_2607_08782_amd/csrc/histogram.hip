@@ -26,7 +26,8 @@ __global__ void zero_i32_kernel(int32_t* __restrict__ a, int64_t na, int32_t* __
 
 // DIRECT: a single workgroup covers all tokens and stores its bins (zeros
 // included), so the outputs need no clearing launch beforehand.
-template <bool COACT, bool LDS_COACT, bool DIRECT = false>
+// COUNTS = false: the co-activation counts alone (counts null).
+template <bool COACT, bool LDS_COACT, bool DIRECT = false, bool COUNTS = true>
 __global__ __launch_bounds__(HIST_THREADS) void histogram_kernel(
     const int32_t* __restrict__ idx, int64_t T, int k, int E, int32_t* __restrict__ counts,
     int32_t* __restrict__ coact) {
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(HIST_THREADS) void histogram_kernel(
         for (int r = 0; r < MOE_MAX_K; ++r) {
             if (r >= k) break;
             if (sel[r] < 0) continue;
-            atomicAdd(&c_lds[sel[r]], 1);
+            if (COUNTS) atomicAdd(&c_lds[sel[r]], 1);
             if (COACT) {
 #pragma unroll
                 for (int q = 0; q < MOE_MAX_K; ++q) {
@@ -70,8 +71,9 @@ __global__ __launch_bounds__(HIST_THREADS) void histogram_kernel(
             for (int i = threadIdx.x; i < E * E; i += HIST_THREADS) coact[i] = co_lds[i];
         return;
     }
-    for (int i = threadIdx.x; i < E; i += HIST_THREADS)
-        if (c_lds[i]) atomicAdd(&counts[i], c_lds[i]);
+    if (COUNTS)
+        for (int i = threadIdx.x; i < E; i += HIST_THREADS)
+            if (c_lds[i]) atomicAdd(&counts[i], c_lds[i]);
     if (LDS_COACT)
         for (int i = threadIdx.x; i < E * E; i += HIST_THREADS)
             if (co_lds[i]) atomicAdd(&coact[i], co_lds[i]);
@@ -212,6 +214,21 @@ int launch_histogram(const int32_t* idx, int64_t T, int k, int E, int32_t* count
         if (blocks > 512) blocks = 512;
         hipLaunchKernelGGL((histogram_kernel<true, false>), dim3((unsigned)blocks),
                            dim3(HIST_THREADS), 0, s, idx, T, k, E, counts, coact);
+    }
+    return launch_status();
+}
+
+int launch_coact(const int32_t* idx, int64_t T, int k, int E, int32_t* coact, hipStream_t s) {
+    int64_t blocks = ceil_div(T, HIST_THREADS);
+    if (E <= LDS_COACT_MAX_E) {
+        if (blocks > 64) blocks = 64;                // as in launch_histogram
+        hipLaunchKernelGGL((histogram_kernel<true, true, false, false>), dim3((unsigned)blocks),
+                           dim3(HIST_THREADS), (size_t)E * E * sizeof(int32_t), s, idx, T, k, E,
+                           (int32_t*)nullptr, coact);
+    } else {
+        if (blocks > 512) blocks = 512;
+        hipLaunchKernelGGL((histogram_kernel<true, false, false, false>), dim3((unsigned)blocks),
+                           dim3(HIST_THREADS), 0, s, idx, T, k, E, (int32_t*)nullptr, coact);
     }
     return launch_status();
 }

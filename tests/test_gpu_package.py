@@ -32,6 +32,15 @@ CASES = [
     (64, 8, 2, 128, 1, False, "f32", True, False),
     (200, 40, 5, 64, 4, False, "bf16", True, False),
     (0, 8, 2, 64, 2, True, "bf16", False, True),
+    # long batches: the count of all experts per block (up to 32768 tokens, room for it)
+    (1088, 128, 8, 256, 9, True, "bf16", False, False),
+    (5001, 13, 3, 64, 4, False, "bf16", False, True),
+    (2111, 256, 16, 64, 5, True, "bf16", False, False),
+    (3000, 200, 5, 64, 3, True, "bf16", False, False),
+    (32768, 60, 4, 64, 8, False, "bf16", False, False),
+    (32769, 60, 4, 64, 8, False, "bf16", False, False),     # one block more
+    (4096, 8, 2, 64, 1, True, "bf16", False, False),        # every expert here: no room
+    (1500, 4, 2, 72, 2, True, "f32", True, True),
 ]
 
 
