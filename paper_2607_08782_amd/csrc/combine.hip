@@ -3,8 +3,8 @@
 // Sec. II-B), plus always-on shared experts with weight 1 (one or more
 // [T][d] slices of shared-expert output, added in slice order).
 //
-// Bandwidth-bound gather: each thread owns one 16-byte chunk of one token's
-// output row, reads the k expert rows it needs (all loads issued together;
+// Bandwidth-bound gather: each thread owns one 16-byte chunk (or four) of one
+// token's output row, reads the expert rows it needs (loads issued together;
 // assignments placed on other GPUs are skipped), accumulates in fp32 in
 // ascending r, and stores once.
 #include "common.h"

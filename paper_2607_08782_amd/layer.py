@@ -1,8 +1,8 @@
-"""One GPU's share of one MoE layer, run through the five C-ABI calls.
+"""One GPU's share of one MoE layer, run through the C-ABI calls.
 
 `LayerShare` owns the device buffers of one share (allocated once with
 torch) and enqueues, on the current stream:
-    moe_route_topk -> moe_expert_histogram -> moe_permute
+    moe_route_package (moe_route_topk, moe_expert_histogram and moe_permute in one)
     -> moe_grouped_ffn (routed experts) -> moe_combine
 with no host synchronisation in between (decode-sized batches stream every
 expert group and skip the tiled GEMM launches; at most 64 tokens with k <= 2 the
