@@ -64,8 +64,9 @@ __device__ __forceinline__ int last_le(const int* a, int n, int v) {
 
 __host__ __device__ constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Launch-error check shared by the host wrappers.
-inline int launch_status() {
+// Launch-error check shared by the host wrappers.  Reading the error clears it, so a
+// status that a caller drops is lost: it and the launchers below are [[nodiscard]].
+[[nodiscard]] inline int launch_status() {
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? MOE_OK : MOE_ERR_DEVICE;
 }
@@ -81,7 +82,7 @@ struct LdsGrant {
     int granted[kMaxDevices] = {};
 };
 
-inline int allow_dynamic_lds(const void* kernel, size_t bytes, LdsGrant& g) {
+[[nodiscard]] inline int allow_dynamic_lds(const void* kernel, size_t bytes, LdsGrant& g) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= LdsGrant::kMaxDevices)
         return MOE_ERR_DEVICE;
@@ -95,7 +96,7 @@ inline int allow_dynamic_lds(const void* kernel, size_t bytes, LdsGrant& g) {
 }
 
 template <auto F>
-inline int allow_dynamic_lds(size_t bytes) {
+[[nodiscard]] inline int allow_dynamic_lds(size_t bytes) {
     static LdsGrant grant;
     return allow_dynamic_lds((const void*)F, bytes, grant);
 }
@@ -103,18 +104,22 @@ inline int allow_dynamic_lds(size_t bytes) {
 // ---------------------------------------------------------------------------
 // Internal launchers (one translation unit each); arguments already validated.
 // ---------------------------------------------------------------------------
+[[nodiscard]]
 int launch_route_topk(const void* x, int dtype, const void* w, const float* bias, int64_t T, int d,
                       int E, int k, int flags, float* logits, int32_t* idx, float* gate, void* ws,
                       hipStream_t s);
 // bf16 scores of a short batch (route.hip): whether a batch takes them, and the launch
 // (scores + bias to out[T][E])
 bool route_short(int64_t T, int d, int E);
+[[nodiscard]]
 int launch_scores_short(const void* x, const void* w, const float* bias, int64_t T, int d, int E,
                         float* out, hipStream_t s);
 size_t route_ws_bytes(int dtype, int64_t T, int d, int E, int flags);
 
+[[nodiscard]]
 int launch_quantize_e4m3(const void* x, int dtype, int64_t rows, int cols, uint8_t* q, float* scales,
                          hipStream_t s);
+[[nodiscard]]
 int launch_route_topk_e4m3(const uint8_t* xq, const float* sx, const uint8_t* wq, const float* sw,
                            const float* bias, int64_t T, int d, int E, int k, int flags,
                            float* logits, int32_t* idx, float* gate, hipStream_t s);
@@ -123,6 +128,7 @@ int launch_route_topk_e4m3(const uint8_t* xq, const float* sx, const uint8_t* wq
 // suit it; launch with S chunks (S == 1 writes scores + bias to out[T][E],
 // S > 1 partial scores to out[S][T][E], to be summed in chunk order).
 int score_tiles_split(int64_t T, int rowbytes, int E, bool allow_split);
+[[nodiscard]]
 int launch_score_tiles(bool fp8, const void* x, const void* w, const float* sx, const float* sw,
                        const float* bias, int64_t T, int rowbytes, int E, int S, float* out,
                        hipStream_t s);
@@ -133,17 +139,21 @@ int launch_score_tiles(bool fp8, const void* x, const void* w, const float* sx, 
 // workgroup's passes over its tokens cost more than the launch).  Fused at 65-128
 // experts: 16384 x 128 routing 25.3 -> 23.0 us, E4M3 20.6 -> 18.3; 8192 x 128 even.
 constexpr int SCORE_TOPK_MAX_E = 128;
+[[nodiscard]]
 int launch_score_tiles_topk(bool fp8, const void* x, const void* w, const float* sx,
                             const float* sw, const float* bias, int64_t T, int rowbytes, int E,
                             int k, int renorm, float* logits, int32_t* idx, float* gate,
                             hipStream_t s);
 // Top-k and gates of given scores (route.hip): scores[T][E] read in place.
+[[nodiscard]]
 int launch_topk_given(const float* scores, int64_t T, int E, int k, int flags, int32_t* idx,
                       float* gate, hipStream_t s);
 
+[[nodiscard]]
 int launch_histogram(const int32_t* idx, int64_t T, int k, int E, int32_t* counts, int32_t* coact,
                      hipStream_t s);
 // co-activation counts added to coact (already cleared)
+[[nodiscard]]
 int launch_coact(const int32_t* idx, int64_t T, int k, int E, int32_t* coact, hipStream_t s);
 
 struct PermuteTables {
@@ -152,6 +162,7 @@ struct PermuteTables {
     int16_t expert_of_slot[MOE_MAX_GROUPS];
 };
 
+[[nodiscard]]
 int launch_permute(const void* x, int dtype, const int32_t* idx, const float* gate,
                    const int32_t* counts, int64_t T, int d, int k, int E, const PermuteTables& tab,
                    int n_local, int G, int dev, void* x_perm, int64_t cap_rows,
@@ -159,6 +170,7 @@ int launch_permute(const void* x, int dtype, const int32_t* idx, const float* ga
                    int32_t* send_counts, void* ws, hipStream_t s);
 size_t permute_ws_bytes(int64_t T, int k, int E);
 // route_topk, histogram and permute in one call (x_perm null: no row copy)
+[[nodiscard]]
 int launch_route_package(const void* x, int dtype, const void* w, const float* bias, int64_t T,
                          int d, int E, int k, int flags, float* logits, int32_t* idx, float* gate,
                          void* ws_route, int32_t* counts, int32_t* coact, const PermuteTables& tab,
@@ -167,6 +179,7 @@ int launch_route_package(const void* x, int dtype, const void* w, const float* b
                          int32_t* token_row, int32_t* send_counts, void* ws_perm, hipStream_t s);
 // Device address of the library's own permute scratch on the current device
 // (MOE_PERMUTE_NOALLOC_MAX_WS bytes, 256-byte aligned).
+[[nodiscard]]
 int permute_scratch(void** ptr);
 
 // a_rows (nullable): row p of the first product's input is row a_rows[p] of
@@ -174,6 +187,7 @@ int permute_scratch(void** ptr);
 // lead > 0: the first `lead` of the n_groups groups hold lead_rows rows each,
 // and offsets (n_groups - lead + 1 entries) counts the others' rows from row
 // lead * lead_rows.
+[[nodiscard]]
 int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, int n_groups,
                        const void* const* w13, const void* const* w2, int d, int f,
                        int64_t cap_rows, void* y_perm, void* ws, hipStream_t s,
@@ -182,12 +196,14 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
                        const void* combine = nullptr, int lead = 0, int lead_rows = 0);
 // moe_grouped_ffn with every group streamed and the down product's chunk sum
 // writing the gate-weighted combine (bf16)
+[[nodiscard]]
 int launch_grouped_ffn_combine(const void* x_perm, const int32_t* offsets, int n_groups,
                                const void* const* w13, const void* const* w2, int d, int f,
                                int64_t cap_rows, const int32_t* token_row, const float* gate,
                                const void* y_shared, int64_t T, int k, void* y, void* ws,
                                hipStream_t s);
 // the fp32 products (ffn_f32.hip); h: [cap_rows][f] scratch
+[[nodiscard]]
 int launch_ffn_f32(const float* x, const int32_t* offsets, int n_groups, const void* const* w13,
                    const void* const* w2, int d, int f, int64_t cap_rows, float* y, float* h,
                    const int32_t* a_rows, int products, int lead, int lead_rows, int cus,
@@ -195,6 +211,7 @@ int launch_ffn_f32(const float* x, const int32_t* offsets, int n_groups, const v
 size_t grouped_ffn_ws_bytes(int dtype, int64_t cap_rows, int d, int f, int n_groups);
 
 // y_shared: n_shared slices of [T][d] (nullable: none)
+[[nodiscard]]
 int launch_combine(const void* y_perm, int dtype, const int32_t* token_row, const float* gate,
                    const void* y_shared, int n_shared, int64_t T, int d, int k, void* y,
                    hipStream_t s);

@@ -378,7 +378,8 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
                                               out, s);
             if (st != MOE_OK) return st;
         } else if (route_short(T, d, E)) {
-            launch_scores_short(x, w, bias, T, d, E, out, s);
+            const int st = launch_scores_short(x, w, bias, T, d, E, out, s);
+            if (st != MOE_OK) return st;
         } else {
             const int rows = route_rows(E);
             const size_t lds = (size_t)4 * rows * (E_pad + 1) * sizeof(float);
