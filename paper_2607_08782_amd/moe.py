@@ -126,6 +126,15 @@ def _dev(t: Optional[torch.Tensor], name: str, dtype=None):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def _holds(t: Optional[torch.Tensor], name: str, *shape: int):
+    """t (None passes) holds at least the elements of this shape."""
+    want = 1
+    for n in shape:
+        want *= n
+    if t is not None and t.numel() < want:
+        raise ValueError("%s must hold %s elements, got %s" % (name, tuple(shape), tuple(t.shape)))
+
+
 def _stream(stream) -> ctypes.c_void_p:
     if stream is None:
         stream = torch.cuda.current_stream()
@@ -317,19 +326,35 @@ def moe_route_package(x: torch.Tensor, w_router: Optional[torch.Tensor],
                       ws_perm: torch.Tensor, cap_rows: int, renorm: bool = True,
                       logits_in: bool = False, copy_rows: bool = True, c_max: int = 0, stream=None):
     """moe_route_topk, moe_expert_histogram and moe_permute of one batch in one call,
-    into the caller's buffers (`out` as moe_permute's; copy_rows=False: row maps only)."""
+    into the caller's buffers (`out` as moe_permute's; copy_rows=False: row maps only).
+    Every buffer's size is checked: the kernels write T, k, E and cap_rows entries."""
     lib = load_library()
     T, d = x.shape
     k = topk_idx.shape[1]
     E = counts.numel()
     dtype = _dtype_code(x)
-    if not logits_in and (w_router.dtype != x.dtype or tuple(w_router.shape) != (E, d)):
+    if not logits_in and (w_router is None or w_router.dtype != x.dtype
+                          or tuple(w_router.shape) != (E, d)):
         raise ValueError("w_router must be [E, d] of x's dtype")
     if logits_in and (logits is None or tuple(logits.shape) != (T, E)):
         raise ValueError("logits_in needs logits [T, E]")
     placement = np.ascontiguousarray(placement, dtype=np.uint8)
     if placement.ndim != 2 or placement.shape[0] != E:
         raise ValueError("placement must be a [E, G] array")
+    G = placement.shape[1]
+    n_local = int(np.count_nonzero(placement[:, dev])) if 0 <= dev < G else 0
+    _holds(bias, "bias", E)
+    _holds(logits, "logits", T, E)
+    _holds(topk_idx, "topk_idx", T, k)
+    _holds(topk_gate, "topk_gate", T, k)
+    _holds(coact, "coact", E, E)
+    _holds(out["token_row"], "token_row", T, k)
+    _holds(out["group_offsets"], "group_offsets", n_local + 1)
+    _holds(out["row_token"], "row_token", cap_rows)
+    _holds(out["row_gate"], "row_gate", cap_rows)
+    _holds(out.get("send_counts"), "send_counts", G)
+    if copy_rows:
+        _holds(out["x_perm"], "x_perm", cap_rows, d)
     flags = (MOE_RENORM if renorm else 0) | (MOE_LOGITS_IN if logits_in else 0)
     st = lib.moe_route_package(
         _dev(x, "x"), dtype, None if logits_in else _dev(w_router, "w_router"),
@@ -337,7 +362,7 @@ def moe_route_package(x: torch.Tensor, w_router: Optional[torch.Tensor],
         _dev(topk_idx, "topk_idx", torch.int32), _dev(topk_gate, "topk_gate", torch.float32),
         _dev(ws_route, "ws_route"), 0 if ws_route is None else ws_route.numel(),
         _dev(counts, "counts", torch.int32), _dev(coact, "coact", torch.int32),
-        placement.ctypes.data_as(ctypes.c_void_p), placement.shape[1], dev, c_max,
+        placement.ctypes.data_as(ctypes.c_void_p), G, dev, c_max,
         _dev(out["x_perm"], "x_perm", x.dtype) if copy_rows else None, cap_rows,
         _dev(out["group_offsets"], "group_offsets", torch.int32),
         _dev(out["row_token"], "row_token", torch.int32),

@@ -71,6 +71,32 @@ int main() {
     EXPECT(moe_permute_noalloc(F, 1, (int32_t*)F, (float*)F, (int32_t*)F, 10, 12, 2, 4, pl, 2, 0,
                                0, F, 20, (int32_t*)F, (int32_t*)F, (float*)F, (int32_t*)F,
                                nullptr, nullptr), MOE_ERR_SHAPE);
+    // moe_route_package: the router's checks, the packaging's, both workspaces
+    auto package = [&](void* x, int64_t T, int d, int k, int flags, float* logits, void* wsr, size_t nr,
+                       int dev, int c_max, int64_t cap, int32_t* token_row, void* wsp, size_t np) {
+        return moe_route_package(x, 1, x, nullptr, T, d, 4, k, flags, logits, (int32_t*)F, (float*)F,
+                                 wsr, nr, (int32_t*)F, nullptr, pl, 2, dev, c_max, F, cap, (int32_t*)F,
+                                 (int32_t*)F, (float*)F, token_row, nullptr, wsp, np, nullptr);
+    };
+    int32_t* I = (int32_t*)F;
+    float* L = (float*)F;
+    const size_t nr = moe_route_topk_ws_bytes(1, 10, 4096, 4, 1), np = moe_permute_ws_bytes(10, 2, 4);
+    EXPECT(package(F, 10, 4096, 0, 1, L, W, nr, 0, 0, 20, I, W, np), MOE_ERR_ARG);
+    EXPECT(package(F, -1, 4096, 2, 1, L, W, nr, 0, 0, 20, I, W, np), MOE_ERR_ARG);
+    EXPECT(package(F, 10, 4096, 2, 8, L, W, nr, 0, 0, 20, I, W, np), MOE_ERR_ARG);
+    EXPECT(package(nullptr, 10, 4096, 2, 1, L, W, nr, 0, 0, 20, I, W, np), MOE_ERR_ARG);
+    EXPECT(package(nullptr, 10, 4096, 2, 3, L, W, nr, 0, 0, 20, I, W, np), MOE_ERR_ARG);
+    EXPECT(package(F, 10, 4096, 2, 3, nullptr, W, nr, 0, 0, 20, I, W, np), MOE_ERR_ARG);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr, 0, 0, 20, nullptr, W, np), MOE_ERR_ARG);
+    EXPECT(package(F, 10, 12, 2, 1, L, W, nr, 0, 0, 20, I, W, np), MOE_ERR_SHAPE);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr - 1, 0, 0, 20, I, W, np), MOE_ERR_SHAPE);
+    EXPECT(package(F, 10, 4096, 2, 1, L, (char*)W + 16, nr, 0, 0, 20, I, W, np), MOE_ERR_SHAPE);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr, 2, 0, 20, I, W, np), MOE_ERR_PLACEMENT);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr, 0, 1, 20, I, W, np), MOE_ERR_PLACEMENT);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr, 0, 0, 19, I, W, np), MOE_ERR_SHAPE);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr, 0, 0, 20, I, W, np - 1), MOE_ERR_SHAPE);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr, 0, 0, 20, I, (char*)W + 16, np), MOE_ERR_SHAPE);
+    EXPECT(package(F, 10, 4096, 2, 1, L, W, nr, 0, 0, 20, I, nullptr, np), MOE_ERR_SHAPE);
     // moe_grouped_ffn and its variants
     EXPECT(moe_grouped_ffn(F, 1, (int32_t*)F, 0, wp, wp, 128, 64, 16, F, W, 1 << 30, nullptr),
            MOE_ERR_ARG);

@@ -150,6 +150,90 @@ def test_permute_noalloc_validation(lib):
     assert lib.moe_permute_ws_bytes(T, 8, E) <= moe.MOE_PERMUTE_NOALLOC_MAX_WS
 
 
+def test_route_package_validation(lib):
+    """The checks of moe_route_topk and moe_permute, with both workspaces."""
+    f = lib.moe_route_package
+    pl = np.array([[1, 0], [0, 1], [1, 1], [0, 1]], np.uint8)
+    need = lib.moe_route_topk_ws_bytes(1, 10, 4096, 4, 1)
+    assert need > 0
+    ok = dict(x=FAKE, dtype=1, w=FAKE, T=10, d=4096, E=4, k=2, flags=1, lg=FAKE, idx=FAKE, gate=FAKE,
+              ws_r=0x100000, ws_r_bytes=need, counts=FAKE, coact=None, pl=pl, dev=0, c_max=0,
+              xp=FAKE, cap=20, off=FAKE, rt=FAKE, rg=FAKE, tr=FAKE, send=None, ws_p=0x200000,
+              ws_p_bytes=lib.moe_permute_ws_bytes(10, 2, 4))
+
+    def call(**kw):
+        a = dict(ok, **kw)
+        p = np.ascontiguousarray(a["pl"])
+        return f(a["x"], a["dtype"], a["w"], None, a["T"], a["d"], a["E"], a["k"], a["flags"],
+                 a["lg"], a["idx"], a["gate"], ctypes.c_void_p(a["ws_r"]), a["ws_r_bytes"],
+                 a["counts"], a["coact"], p.ctypes.data_as(ctypes.c_void_p), p.shape[1], a["dev"],
+                 a["c_max"], a["xp"], a["cap"], a["off"], a["rt"], a["rg"], a["tr"], a["send"],
+                 ctypes.c_void_p(a["ws_p"]), a["ws_p_bytes"], None)
+    for bad in (dict(k=0), dict(k=5), dict(T=-1), dict(E=0), dict(E=300), dict(dtype=7), dict(flags=8),
+                dict(idx=None), dict(gate=None), dict(x=None), dict(w=None), dict(counts=None),
+                dict(off=None), dict(rt=None), dict(rg=None), dict(tr=None), dict(cap=-1),
+                dict(x=ctypes.c_void_p(0x1002)),                     # misaligned bf16 rows
+                dict(flags=3, lg=None),                              # logits-in without logits
+                dict(flags=3, x=None, w=None),                       # rows to copy, but no x
+                dict(flags=3, T=1 << 30, k=4, cap=1 << 40)):         # T * k past 32 bits
+        assert call(**bad) == moe.MOE_ERR_ARG, bad
+    orphan = pl.copy()
+    orphan[3] = 0
+    for bad in (dict(pl=orphan), dict(dev=2), dict(dev=-1), dict(c_max=1),
+                dict(pl=np.ones((4, 65), np.uint8))):
+        assert call(**bad) == moe.MOE_ERR_PLACEMENT, bad
+    for bad in (dict(d=12), dict(cap=19), dict(ws_r=0), dict(ws_r_bytes=need - 1), dict(ws_r=0x100010),
+                dict(ws_p=0), dict(ws_p_bytes=ok["ws_p_bytes"] - 1), dict(ws_p=0x200010),
+                dict(E=4, d=1 << 30)):                               # router past 32-bit offsets
+        assert call(**bad) == moe.MOE_ERR_SHAPE, bad
+
+
+def test_route_package_wrapper_checks_every_buffer():
+    """Buffers that the kernels would write past are refused before anything else is
+    looked at (CPU tensors: a call that passes the size checks is then refused for not
+    being on the GPU)."""
+    import torch
+
+    T, d, E, k, G, cap = 6, 16, 8, 2, 2, 12
+    pl = np.zeros((E, G), np.uint8)
+    pl[np.arange(E), np.arange(E) % G] = 1
+    i32 = dict(dtype=torch.int32)
+
+    def call(copy_rows=True, logits_in=False, **kw):
+        a = dict(x=torch.zeros(T, d), w=torch.zeros(E, d), bias=torch.zeros(E), logits=torch.zeros(T, E),
+                 topk_idx=torch.zeros(T, k, **i32), topk_gate=torch.zeros(T, k),
+                 counts=torch.zeros(E, **i32), coact=torch.zeros(E, E, **i32),
+                 x_perm=torch.zeros(cap, d), group_offsets=torch.zeros(5, **i32),
+                 row_token=torch.zeros(cap, **i32), row_gate=torch.zeros(cap),
+                 token_row=torch.zeros(T, k, **i32), send_counts=torch.zeros(G, **i32))
+        a.update(kw)
+        out = {n: a[n] for n in ("x_perm", "group_offsets", "row_token", "row_gate", "token_row",
+                                 "send_counts")}
+        moe.moe_route_package(a["x"], a["w"], a["bias"], pl, 0, logits=a["logits"],
+                              topk_idx=a["topk_idx"], topk_gate=a["topk_gate"], ws_route=None,
+                              counts=a["counts"], coact=a["coact"], out=out,
+                              ws_perm=torch.zeros(1 << 16, dtype=torch.uint8), cap_rows=cap,
+                              logits_in=logits_in, copy_rows=copy_rows)
+
+    for good in (dict(), dict(bias=None, coact=None, logits=None, send_counts=None),
+                 dict(copy_rows=False, x_perm=None)):
+        with pytest.raises(ValueError, match="must be a GPU tensor"):
+            call(**good)
+    for name, t in (("bias", torch.zeros(E - 1)), ("logits", torch.zeros(T - 1, E)),
+                    ("logits", torch.zeros(T, E - 1)), ("topk_idx", torch.zeros(T - 1, k, **i32)),
+                    ("topk_gate", torch.zeros(T - 1, k)), ("topk_gate", torch.zeros(T, k - 1)),
+                    ("coact", torch.zeros(E, E - 1, **i32)), ("token_row", torch.zeros(T - 1, k, **i32)),
+                    ("group_offsets", torch.zeros(4, **i32)), ("row_token", torch.zeros(cap - 1, **i32)),
+                    ("row_gate", torch.zeros(cap - 1)), ("send_counts", torch.zeros(G - 1, **i32)),
+                    ("x_perm", torch.zeros(cap - 1, d))):
+        with pytest.raises(ValueError, match=name + " must hold "):
+            call(**{name: t})
+    for bad in (dict(logits_in=True, logits=torch.zeros(T, E + 1)), dict(logits_in=True, logits=None),
+                dict(w=None), dict(w=torch.zeros(E, d + 1))):
+        with pytest.raises(ValueError):
+            call(**bad)
+
+
 def test_grouped_ffn_products_validation(lib):
     f = lib.moe_grouped_ffn_products
     arr = (ctypes.c_void_p * 2)(0x1000, 0x2000)
