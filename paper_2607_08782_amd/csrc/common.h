@@ -32,9 +32,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)pack_bf16x2(f, f); }
 
-// a / (1 + exp(-a)) with the hardware reciprocal (within 1 ulp)
+// a / (1 + exp(-a)), the quotient correctly rounded: a multiplication by the hardware
+// reciprocal is up to an ulp off and gives zero where 1 + exp(-a) is above 2^126 (its
+// reciprocal is subnormal).
 __device__ __forceinline__ float silu(float a) {
-    return a * __builtin_amdgcn_rcpf(1.0f + __expf(-a));
+    return a / (1.0f + __expf(-a));
 }
 
 // Inclusive prefix sum across the 64 lanes of a wave (every lane active), by DPP
