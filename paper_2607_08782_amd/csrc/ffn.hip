@@ -963,7 +963,13 @@ __global__ __launch_bounds__(SP_THREADS, SP_WG_PER_CU) void strip_gemm_kernel(St
         const int rows = __builtin_amdgcn_readfirstlane(s_off[g + 1]) - start;
         const int mt = (rows + SP_M - 1) / SP_M;
         const int local = tile - __builtin_amdgcn_readfirstlane(s_tstart[g]);
-        const int m = local % mt, n0 = (local / mt) * OUT;
+        // the row tiles of a strip in another order from turn to turn: a workgroup's turns
+        // are gridDim.x / NUM_XCD tiles apart, a multiple of mt for most mt, and a group's
+        // last row tile is the short one, so in a fixed order some workgroups would take
+        // short tiles only and others none (8 groups of 65 rows, d = 4096, f = 14336: FFN
+        // 924 us, in turn 684)
+        const int strip = local / mt;
+        const int m = (local + strip * mt / (int)(gridDim.x / NUM_XCD)) % mt, n0 = strip * OUT;
         const int row0 = start + m * SP_M, rows_valid = min(SP_M, rows - m * SP_M);
         // uniform (the compiler loops over the lanes' values for a descriptor it cannot
         // prove to be)
