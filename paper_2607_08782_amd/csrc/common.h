@@ -32,11 +32,34 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)pack_bf16x2(f, f); }
 
-// a / (1 + exp(-a)), the quotient correctly rounded: a multiplication by the hardware
-// reciprocal is up to an ulp off and gives zero where 1 + exp(-a) is above 2^126 (its
-// reciprocal is subnormal).
-__device__ __forceinline__ float silu(float a) {
-    return a / (1.0f + __expf(-a));
+// SiLU(a) = a / (1 + exp(-a)), the quotient correctly rounded: by the division, or for
+// |a| < SILU_NEAR by the hardware reciprocal and one residual step, which for every one of
+// the 2^31 floats in that range gives the division's bits (-0 gives +0) at under half its
+// instructions (DeepSeek-V2-Lite prefill, 8192 tokens: divisions 548 us a step, this 537.5,
+// the reciprocal alone, an ulp off for 4.6 % of the floats, 534.5).  Past the range the
+// reciprocal goes subnormal, which the hardware gives as zero, from a = -87.3 down, and an
+// infinity has no residual.
+constexpr float SILU_NEAR = 87.0f;
+
+__device__ __forceinline__ float silu_near(float a) {
+    const float d = 1.0f + __expf(-a), r = __builtin_amdgcn_rcpf(d), q = a * r;
+    return fmaf(fmaf(-d, q, a), r, q);
+}
+
+__device__ __forceinline__ float silu_div(float a) { return a / (1.0f + __expf(-a)); }
+
+template <int N>
+__device__ __forceinline__ void silu(float (&a)[N]) {
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(a[i]));
+    if (m < SILU_NEAR) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) a[i] = silu_near(a[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) a[i] = silu_div(a[i]);
+    }
 }
 
 // Inclusive prefix sum across the 64 lanes of a wave (every lane active), by DPP

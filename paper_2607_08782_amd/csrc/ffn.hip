@@ -617,26 +617,41 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
                     (void*)(args.out + (int64_t)cur.row0 * args.ldo), (short)0,
                     wcol + 32 * p < args.N ? cur.rows_valid * args.ldo * 2 : 0, RSRC_WORD3);
             };
-            int vo = (lrow_out * args.ldo + wcol + colq) * 2;
-#pragma unroll
-            for (int m = 0; m < MS; ++m) {
+            // NEAR: SiLU by the short form, the largest gate value to `most`
+            float most = 0.f;
+            auto store_tile = [&](auto near) {
+                constexpr bool NEAR = decltype(near)::value;
                 constexpr int NP = SWIGLU ? NS / 4 : NS / 2;
-                use(m);
+                int vo = (lrow_out * args.ldo + wcol + colq) * 2;
 #pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    float v[8];
+                for (int m = 0; m < MS; ++m) {
+                    use(m);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int j = 2 * p + (e >> 2);
-                        if constexpr (SWIGLU) v[e] = silu(acc[m][j][e & 3]) * acc[m][NS / 2 + j][e & 3];
-                        else v[e] = acc[m][j][e & 3];
+                    for (int p = 0; p < NP; ++p) {
+                        float v[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const int j = 2 * p + (e >> 2);
+                            v[e] = acc[m][j][e & 3];
+                            if constexpr (SWIGLU) {
+                                if (NEAR) most = fmaxf(most, fabsf(v[e]));
+                                v[e] = (NEAR ? silu_near(v[e]) : silu_div(v[e])) *
+                                       acc[m][NS / 2 + j][e & 3];
+                            }
+                        }
+                        const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
+                                         pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+                        __builtin_amdgcn_raw_buffer_store_b128(w, orsrc(p), vo + 64 * p, 0, 0);
                     }
-                    const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
-                                     pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-                    __builtin_amdgcn_raw_buffer_store_b128(w, orsrc(p), vo + 64 * p, 0, 0);
+                    vo += 32 * args.ldo;
                 }
-                vo += 32 * args.ldo;
-            }
+            };
+            store_tile(std::true_type{});
+            // some gate value out of the short form's range: the tile again (the stores are
+            // then more than the stage waits allow for, which only makes them wait longer).
+            // One test a tile: a branch per eight values cost as much as the divisions
+            if constexpr (SWIGLU)
+                if (__any(!(most < SILU_NEAR))) store_tile(std::false_type{});
         }
         if (!has_next) break;
         q = qn;
@@ -1084,9 +1099,10 @@ __global__ __launch_bounds__(SP_THREADS, SP_WG_PER_CU) void strip_gemm_kernel(St
                 const int row_in = wm * (M / 2) + i * 16 + frow;
                 const int quad = lane >> 4;
                 if constexpr (SWIGLU) {
-                    float v[4];
+                    float v[4] = {acc[i][0][0], acc[i][0][1], acc[i][0][2], acc[i][0][3]};
+                    silu(v);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = silu(acc[i][0][r]) * acc[i][1][r];
+                    for (int r = 0; r < 4; ++r) v[r] *= acc[i][1][r];
                     const u32x2 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
                     __builtin_amdgcn_raw_buffer_store_b64(
                         w, orsrc, (row_in * args.ldo + n0 + wn * 16 + quad * 4) * 2, 0, 0);
@@ -1147,6 +1163,20 @@ __device__ __forceinline__ void add_chunks(const float* pr, int64_t cstride, int
     else if (c < S) add_chunk_batch<SWIGLU, 4>(pr, cstride, up, c, S, x, y);
 }
 
+// Four summed columns in bf16 (SWIGLU: SiLU(x) * y).
+template <bool SWIGLU>
+__device__ __forceinline__ uint2 pack_sum(const float4& x, const float4& y) {
+    float o[4] = {x.x, x.y, x.z, x.w};
+    if constexpr (SWIGLU) {
+        silu(o);
+        o[0] *= y.x;
+        o[1] *= y.y;
+        o[2] *= y.z;
+        o[3] *= y.w;
+    }
+    return make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+}
+
 // Sums, in chunk order, the K chunks of the tiled kernel's split tiles (fp32
 // partial tiles [row][weight row]; SWIGLU: gate in tile columns [0, 128), up
 // in [128, 256)) and applies the epilogue: out = SiLU(gate) * up, or the sum.
@@ -1182,11 +1212,7 @@ __device__ void tile_split_reduce(const GemmArgs& t, int* s_off, int* s_tstart) 
         float4 x, y;
         add_chunks<SWIGLU>(t.part + ((int64_t)q * S * BM + row) * BNW + j, (int64_t)BM * BNW,
                            BNW / 2, S, x, y);
-        const float o[4] = {SWIGLU ? silu(x.x) * y.x : x.x, SWIGLU ? silu(x.y) * y.y : x.y,
-                            SWIGLU ? silu(x.z) * y.z : x.z, SWIGLU ? silu(x.w) * y.w : x.w};
-        uint2 pk;
-        pk.x = pack_bf16x2(o[0], o[1]);
-        pk.y = pack_bf16x2(o[2], o[3]);
+        const uint2 pk = pack_sum<SWIGLU>(x, y);
         *(uint2*)(t.out + (int64_t)(s_off[g] + m0 + row) * t.ldo + n0 + j) = pk;
     }
 }
@@ -1227,11 +1253,7 @@ __device__ __forceinline__ void stream_reduce(const StreamArgs& args, const Stre
         const int p = P.off[g] + (q - P.qbase[g]);
         float4 x, y;
         add_chunks<SWIGLU>(args.part + (int64_t)q * args.N + c4, cstride, cols, S, x, y);
-        const float o0 = SWIGLU ? silu(x.x) * y.x : x.x, o1 = SWIGLU ? silu(x.y) * y.y : x.y;
-        const float o2 = SWIGLU ? silu(x.z) * y.z : x.z, o3 = SWIGLU ? silu(x.w) * y.w : x.w;
-        uint2 pk;
-        pk.x = pack_bf16x2(o0, o1);
-        pk.y = pack_bf16x2(o2, o3);
+        const uint2 pk = pack_sum<SWIGLU>(x, y);
         *(uint2*)(args.out + (int64_t)p * args.ldo + c4) = pk;
     }
 }
