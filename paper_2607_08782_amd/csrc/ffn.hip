@@ -931,7 +931,7 @@ constexpr int strip_lds(int M, int R) { return R * (M + SP_N) * SP_ROWB; }
 constexpr int SP_R32 = 4, SP_R64 = 3;    // ring stages by tile height
 constexpr int SP_LDS = strip_lds(64, SP_R64);
 static_assert(strip_lds(32, SP_R32) <= SP_LDS, "ring size");
-constexpr int STRIP_MAX_K = 4096;
+constexpr int STRIP_ANY_K = 2048, STRIP_MAX_K = 4096;   // see strip_product
 
 template <bool SWIGLU, bool GATHER>
 __global__ __launch_bounds__(SP_THREADS, SP_WG_PER_CU) void strip_gemm_kernel(StreamArgs args) {
@@ -1402,14 +1402,29 @@ size_t grouped_ffn_ws_bytes(int dtype, int64_t cap_rows, int d, int f, int n_gro
     return (size_t)(h + part + tile_part_bytes(cap_rows) + 256);
 }
 
-// Whether the streamed groups of a product run as strips: K short enough for one
-// workgroup to walk, and a call whose rows may all lie in streamed groups (which
-// also bounds the rows the fused combine keeps in the workspace).  A longer K leaves
-// too few strips of too long a chain, and is split over workgroups (Mixtral-shaped
-// decode step: the gate/up product, K = 4096, as strips 178.6 -> 176.0 us, the down
-// product too, K = 14336, 216).
-static bool strip_product(int K, int64_t cap_rows, int n_groups) {
-    return K <= STRIP_MAX_K && cap_rows <= (int64_t)SMALL_ROWS_MAX * n_groups;
+// Whether the streamed groups of a product run as strips (n_out output columns in
+// strips of `out`).  Only in a call whose rows may all lie in streamed groups, which also
+// bounds the rows the fused combine keeps in the workspace.  Up to K = 2048 strips are
+// ahead at every group size.  Past it a strip is a long chain, and a group above 64 rows
+// reads its weight strip once per 64 rows through LDS where the split kernel's items are
+// twice as wide: ahead while groups hold up to 64 rows (K = 4096, f = 14336, FFN of 2 and
+// 4 groups of 64 rows: split 169 and 310 us, strips 158 and 291) in up to 9 rounds of
+// workgroups (8 groups: 585 against 607), behind above (4 groups of 128 and 256 rows: 404
+// and 641 against 410 and 693; 16 groups of 128 at f = 4096: 458 against 492), and so
+// taken by the rows a group may hold on average.
+// With one or two groups that bound says little (a batch's capacity is then its tokens
+// in every group): there also above, if the strips make more than two rounds of
+// workgroups (Mixtral-shaped step, 2 of 8 experts here, 256 tokens: split 246 us, strips
+// 233; at two rounds or less f = 8192, 2 groups of 128 rows: 134 against 159).  Past
+// K = 4096 the chain is too long (Mixtral-shaped down product, K = 14336: step 176 us
+// split, 216 as strips).
+static bool strip_product(int K, int n_out, int out, int64_t cap_rows, int n_groups, int cus) {
+    if (K > STRIP_MAX_K || cap_rows > (int64_t)SMALL_ROWS_MAX * n_groups) return false;
+    if (K <= STRIP_ANY_K) return true;
+    const int64_t tiles = (cap_rows / SP_M + n_groups) * (n_out / out);
+    const int64_t round = (int64_t)SP_WG_PER_CU * cus;
+    if (cap_rows <= (int64_t)SP_M * n_groups && tiles <= 9 * round) return true;
+    return n_groups <= 2 && tiles > 2 * round;
 }
 
 template <bool SWIGLU, bool GATHER>
@@ -1526,7 +1541,7 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
         }
         return r;
     };
-    const bool strips1 = strip_product(d, cap_rows, n_groups);
+    const bool strips1 = strip_product(d, f, SP_N / 2, cap_rows, n_groups, cus);
     if (up) {
         if (!large && strips1) {
             const int st = a_rows ? launch_strips<true, true>(s1, cus, s)
@@ -1566,7 +1581,7 @@ int launch_grouped_ffn(const void* x_perm, int dtype, const int32_t* offsets, in
     s2.ldo = d;
     s2.a_rows = nullptr;
     s2.product = 1;
-    const bool strips2 = strip_product(f, cap_rows, n_groups);
+    const bool strips2 = strip_product(f, d, SP_N, cap_rows, n_groups, cus);
     if (strips2 && !large) {
         if (combine != nullptr) {
             // the fused combine's y_perm: the partial sums' place (at most 256 rows a

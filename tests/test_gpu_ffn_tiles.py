@@ -30,6 +30,10 @@ LARGE, SMALL = moe.MOE_FFN_LARGE_GROUPS, moe.MOE_FFN_SMALL_GROUPS
     ([128, 129, 256, 65], 192, 2048, SMALL, False),   # several row tiles and tails
     ([200, 3], 4160, 128, SMALL, False),            # gate/up split over workgroups, down a strip
     ([40, 90], 128, 4160, SMALL, True),             # and the reverse
+    ([60, 64, 10], 2112, 128, SMALL, False),        # past K = 2048: strips up to 64 rows on average,
+    ([100, 70, 80], 2112, 128, SMALL, False),       # split above,
+    ([200, 130], 2112, 4096, SMALL, True),          # also with two groups in few strips,
+    ([200, 130], 2112, 9856, SMALL, True),          # strips in many
     ([30, 5, 64], 256, 128, 0, False),              # no hint
     ([700, 5, 64, 200], 256, 128, 0, True),
 ])
