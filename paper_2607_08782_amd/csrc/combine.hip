@@ -3,10 +3,11 @@
 // Sec. II-B), plus always-on shared experts with weight 1 (one or more
 // [T][d] slices of shared-expert output, added in slice order).
 //
-// Bandwidth-bound gather: each thread owns one 16-byte chunk (or four) of one
-// token's output row, reads the expert rows it needs (loads issued together;
-// assignments placed on other GPUs are skipped), accumulates in fp32 in
-// ascending r, and stores once.
+// Bandwidth-bound gather: each thread owns one chunk of 16 bytes (one element where d
+// is no multiple of them) of one token's output row, reads the expert rows it needs
+// (loads issued together; assignments placed on other GPUs are skipped), accumulates in
+// fp32 in ascending r, and stores once.  A wave serves one token where rows are whole
+// wave widths (combine_wave_kernel).
 #include "common.h"
 
 namespace moe {
@@ -132,18 +133,21 @@ __global__ __launch_bounds__(COMBINE_THREADS) void combine_kernel(
     Vec<Elem, V>::store(y + t * d + col, acc);
 }
 
-// Rows that are a whole number of wave widths: a wave serves CH chunks per lane of one
+// Rows that are a whole number of wave widths: a wave serves one chunk per lane of one
 // token.  Lane r holds the token's assignment r, a ballot says which have a row here, and
 // their row numbers and gates come out of the lanes in ascending r as scalars, so exactly
 // the loads of the local rows are issued.  The sum is that of the kernel above, in the same
 // order.  Bound by the memory rate; with a copy of the k indices and their compaction in
-// every lane the vector unit was (16384 tokens, d = 2048, k = 8, two local rows a token).
+// every lane the vector unit was (16384 tokens, d = 2048, k = 8, two local rows a token:
+// 42.2 -> 33.5 us cold).  One chunk a lane: with four, which saved the row map's reads,
+// batches above 8192 waves lost up to 8 % in fp32 (16384 tokens, d = 4096, k = 2: 125 ->
+// 116 us) and bf16 gained nothing.
 // N rows from the head of the list `here` (a bit per assignment), those past its end row 0
 // of y_perm, loaded and dropped.
-template <typename Elem, int V, int CH, int N>
+template <typename Elem, int V, int N>
 __device__ __forceinline__ void combine_rows(const Elem* __restrict__ y_perm, int p, float g,
-                                             uint64_t& here, int d, int col, float (&acc)[CH][V]) {
-    float v[N][CH][V], h[N];
+                                             uint64_t& here, int d, int col, float (&acc)[V]) {
+    float v[N][V], h[N];
     bool ok[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -152,53 +156,44 @@ __device__ __forceinline__ void combine_rows(const Elem* __restrict__ y_perm, in
         const int row = ok[j] ? __builtin_amdgcn_readlane(p, r) : 0;
         h[j] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(g), r));
         here &= here - 1;
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-            Vec<Elem, V>::load(y_perm + (int64_t)row * d + col + c * 64 * V, v[j][c]);
+        Vec<Elem, V>::load(y_perm + (int64_t)row * d + col, v[j]);
     }
 #pragma unroll
     for (int j = 0; j < N; ++j)
         if (ok[j])
 #pragma unroll
-            for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int i = 0; i < V; ++i) acc[c][i] = fmaf(h[j], v[j][c][i], acc[c][i]);
+            for (int i = 0; i < V; ++i) acc[i] = fmaf(h[j], v[j][i], acc[i]);
 }
 
-template <typename Elem, int V, int CH>
+template <typename Elem, int V>
 __global__ __launch_bounds__(COMBINE_THREADS) void combine_wave_kernel(
     const Elem* __restrict__ y_perm, const int32_t* __restrict__ token_row,
     const float* __restrict__ gate, const Elem* __restrict__ y_shared, int n_shared, int T,
     int d, int k, int parts, Elem* __restrict__ y) {
-    // wave w: token w / parts, its chunks from (w % parts) * 64 CH
+    // wave w: token w / parts, its chunks from (w % parts) * 64
     const int w = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (COMBINE_THREADS / 64) +
                                                  (int)(threadIdx.x >> 6));
     const int t = parts == 1 ? w : (int)((unsigned)w / (unsigned)parts);
     if (t >= T) return;
     const int lane = (int)(threadIdx.x & 63);
-    const int col = ((w - t * parts) * 64 * CH + lane) * V;
+    const int col = ((w - t * parts) * 64 + lane) * V;
     const int rr = lane < k ? lane : k - 1;
     const int p = token_row[(int64_t)t * k + rr];
     const float g = gate[(int64_t)t * k + rr];
     uint64_t here = __ballot(lane < k && p >= 0);
-    float acc[CH][V];
+    float acc[V];
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int i = 0; i < V; ++i) acc[c][i] = 0.f;
-    // all at once up to two, then two (four chunks a lane) or four at a time
-    constexpr int B = CH == 1 ? 4 : 2;
+    for (int i = 0; i < V; ++i) acc[i] = 0.f;
+    // all at once up to two, then four, above four rows eight at a time (16384 tokens,
+    // d = 1024, eight rows a token: four at a time 47.8 us, eight 46.1)
     const int n = __popcll(here);
-    if (n == 1) combine_rows<Elem, V, CH, 1>(y_perm, p, g, here, d, col, acc);
-    else if (n == 2) combine_rows<Elem, V, CH, 2>(y_perm, p, g, here, d, col, acc);
-    else
-        while (here) combine_rows<Elem, V, CH, B>(y_perm, p, g, here, d, col, acc);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int64_t o = (int64_t)t * d + col + c * 64 * V;
-        add_shared<Elem, V>(y_shared, n_shared, (int64_t)T * d, o, acc[c]);
-        Vec<Elem, V>::store(y + o, acc[c]);
-    }
+    if (n == 1) combine_rows<Elem, V, 1>(y_perm, p, g, here, d, col, acc);
+    else if (n == 2) combine_rows<Elem, V, 2>(y_perm, p, g, here, d, col, acc);
+    else if (n > 4) while (here) combine_rows<Elem, V, 8>(y_perm, p, g, here, d, col, acc);
+    else if (n > 0) combine_rows<Elem, V, 4>(y_perm, p, g, here, d, col, acc);
+    const int64_t o = (int64_t)t * d + col;
+    add_shared<Elem, V>(y_shared, n_shared, (int64_t)T * d, o, acc);
+    Vec<Elem, V>::store(y + o, acc);
 }
 
 template <typename Elem, int V, int KM>
@@ -206,20 +201,11 @@ int launch_k(const void* y_perm, const int32_t* token_row, const float* gate, co
              int n_shared, int64_t T, int d, int k, void* y, hipStream_t s) {
     const int chunks = d / V;
     if (V > 1 && chunks % 64 == 0 && T * (chunks / 64) < ((int64_t)1 << 30)) {
-        // four chunks a lane when that leaves 32 waves per CU (8192 tokens, d = 2048, k = 8:
-        // 16.7 -> 14.8 us against the kernel before; 2048 tokens with one 5.8 -> 4.8), else
-        // one, and also with several shared slices, whose loads then go chunk by chunk
-        // (16384 tokens, four slices: 69.9 -> 72.4 us with four chunks)
-        const int ch = n_shared < 2 && chunks % 256 == 0 && T * (chunks / 256) >= 8192 ? 4 : 1;
-        const int parts = chunks / 64 / ch;
-        const unsigned blocks = (unsigned)ceil_div(T * parts, COMBINE_THREADS / 64);
-#define MOE_CW(CH)                                                                               \
-    hipLaunchKernelGGL((combine_wave_kernel<Elem, V, CH>), dim3(blocks), dim3(COMBINE_THREADS), \
-                       0, s, (const Elem*)y_perm, token_row, gate, (const Elem*)y_shared, n_shared, \
-                       (int)T, d, k, parts, (Elem*)y)
-        if (ch == 4) MOE_CW(4);
-        else MOE_CW(1);
-#undef MOE_CW
+        const int parts = chunks / 64;
+        hipLaunchKernelGGL((combine_wave_kernel<Elem, V>),
+                           dim3((unsigned)ceil_div(T * parts, COMBINE_THREADS / 64)),
+                           dim3(COMBINE_THREADS), 0, s, (const Elem*)y_perm, token_row, gate,
+                           (const Elem*)y_shared, n_shared, (int)T, d, k, parts, (Elem*)y);
         return launch_status();
     }
     const int64_t blocks = ceil_div(T * chunks, COMBINE_THREADS);

@@ -1,5 +1,6 @@
-"""Combine over many tokens (marked `gpu`): the rule that gives a wave four chunks a lane,
-its edges in T and d, every number of local rows from none to k, in bf16 and fp32.
+"""Combine over many tokens (marked `gpu`): a wave per token and the other widths, every
+number of local rows from none to k (one, two, up to four and up to eight rows loaded
+together), in bf16 and fp32.
 Values are small integers and gates powers of two, so every sum is exact and the output
 equals the oracle's bit for bit.
 """
