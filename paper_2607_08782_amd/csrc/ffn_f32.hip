@@ -12,7 +12,9 @@
 // loads of the next two blocks are in flight while two blocks multiply.  The
 // four waves of a workgroup split K of one tile (short K chains, four times the
 // waves; partial sums added in wave order through LDS) unless there are enough
-// tiles, when they take a 2 x 2 arrangement of tiles and share operands in L1.
+// tiles, when they take a 2 x 2 arrangement of tiles and share operands in L1, each
+// adding the same four partial sums in the same order: an output's bits depend on
+// neither the arrangement, nor the call's capacity, nor the operands' alignment.
 // It replaced 16 x 16 output tiles staged through LDS and multiplied on the
 // vector unit: 1000 tokens, d = 256, f = 512, 8 experts, top-2: gate/up 74 -> 30
 // us, down 73 -> 19 us; 64 tokens, d = 128, f = 256: 12.7 -> 7.3 and 20.7 -> 5.9 us.
@@ -90,8 +92,8 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
     }
     __syncthreads();
     const int nblk = (int)((K + 15) / 16);
-    const int ks = KS == 4 ? wave : 0;
-    const int b0 = (int)((int64_t)ks * nblk / KS), b1 = (int)((int64_t)(ks + 1) * nblk / KS);
+    auto quarter = [&](int i) { return (int)((int64_t)i * nblk / 4); };   // of K, in blocks
+    const int b0 = KS == 4 ? quarter(wave) : 0, b1 = KS == 4 ? quarter(wave + 1) : nblk;
     const int wm = KS == 1 ? wave & 1 : 0, wn = KS == 1 ? wave >> 1 : 0;
     const int fr = lane & 15, kq = (lane >> 4) * 4;
 
@@ -117,13 +119,14 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
             for (int j = 0; j < NT; ++j)
                 bp[q][j] = args.w[g] + ((int64_t)q * N + min(n0 + j * 16 + fr, N - 1)) * K;
 
-        f32x4 acc[NP][F_MT][NT];
+        f32x4 acc[NP][F_MT][NT], sum[NP][F_MT][NT];      // sum: KS == 1
 #pragma unroll
         for (int q = 0; q < NP; ++q)
 #pragma unroll
             for (int i = 0; i < F_MT; ++i)
 #pragma unroll
-                for (int j = 0; j < NT; ++j) acc[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int j = 0; j < NT; ++j)
+                    acc[q][i][j] = sum[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         f32x4 a[2][F_U][F_MT], b[2][F_U][NP][NT];
         // blocks at or past b1 load zeros, so the products need no branch
         auto load = [&](int slot, int blk) {
@@ -138,27 +141,45 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
                     for (int j = 0; j < NT; ++j) b[slot][u][q][j] = load_k4<VEC>(bp[q][j], k, K);
             }
         };
-        auto mma = [&](int slot) {
+        // f(q, i, j) for every accumulator
+        auto each = [&](auto f) {
 #pragma unroll
-            for (int u = 0; u < F_U; ++u)
+            for (int q = 0; q < NP; ++q)
+#pragma unroll
+                for (int i = 0; i < F_MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) f(q, i, j);
+        };
+        auto mma = [&](int slot, int blk) {
+#pragma unroll
+            for (int u = 0; u < F_U; ++u) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int q = 0; q < NP; ++q)
-#pragma unroll
-                        for (int i = 0; i < F_MT; ++i)
-#pragma unroll
-                            for (int j = 0; j < NT; ++j)
-                                acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                    a[slot][u][i][e], b[slot][u][q][j][e], acc[q][i][j], 0, 0, 0);
+                    each([&](int q, int i, int j) {
+                        acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            a[slot][u][i][e], b[slot][u][q][j][e], acc[q][i][j], 0, 0, 0);
+                    });
+                // whole K in one wave: the sums of the quarters that four waves would take,
+                // added in the same order, so the sums are the same bits either way
+                if constexpr (KS == 1) {
+                    const int done = blk + u + 1;
+                    if (done == quarter(1) || done == quarter(2) || done == quarter(3))
+                        each([&](int q, int i, int j) {
+                            sum[q][i][j] += acc[q][i][j];
+                            acc[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        });
+                }
+            }
         };
         load(0, b0);
         for (int blk = b0; blk < b1; blk += 2 * F_U) {
             load(1, blk + F_U);
-            mma(0);
+            mma(0, blk);
             load(0, blk + 2 * F_U);
-            mma(1);
+            mma(1, blk + F_U);
         }
+        if constexpr (KS == 1)
+            each([&](int q, int i, int j) { acc[q][i][j] = sum[q][i][j] + acc[q][i][j]; });
 
         // accumulator element r of lane l: row 4 (l / 16) + r, column l % 16
         auto store = [&](int i, int j, const f32x4& x, const f32x4& y) {

@@ -64,6 +64,37 @@ def test_f32_ffn_tile_edges(sizes, d, f, shift, gather):
     assert np.all(got[N:] == 5.0)
 
 
+@pytest.mark.parametrize("d,f", [(20, 2051), (132, 2304), (2052, 36), (1000, 2048), (17, 2100)])
+def test_f32_ffn_bits_are_the_rows_own(d, f):
+    """An output row's bits are those of its input row and weights: the same through the
+    row map from misaligned token rows, from an aligned packaged copy, in a larger
+    workspace, and in a call of a few rows (whole-K waves against K over four waves)."""
+    say("[f32 bits] d=%d f=%d" % (d, f))
+    gen = torch.Generator().manual_seed(d + f)
+    sizes, T = [1000, 70, 1100], 300
+    N = sum(sizes)
+    x = torch.randn((T, d), generator=gen)
+    w13 = [(torch.randn((2 * f, d), generator=gen) * d ** -0.5).cuda() for _ in sizes]
+    w2 = [(torch.randn((d, f), generator=gen) * f ** -0.5).cuda() for _ in sizes]
+    tok = torch.randint(0, T, (N,), generator=gen, dtype=torch.int32)
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    wt, off = moe.WeightTable(w13, w2), torch.tensor(offs).cuda()
+    packed = x[tok.long()].contiguous()
+    want = moe.moe_grouped_ffn(packed.cuda(), off, wt)
+    rows = moe.moe_grouped_ffn_rows(_placed(x, 1), tok.cuda(), off, wt, cap_rows=N)
+    wide = torch.zeros((4 * N, d), device="cuda")
+    wide[:N] = packed.cuda()
+    roomy = moe.moe_grouped_ffn(wide, off, wt)
+    misaligned = moe.moe_grouped_ffn(_placed(packed, 3), off, wt)
+    for name, y in (("row map", rows), ("capacity", roomy[:N]), ("misaligned", misaligned)):
+        assert torch.equal(y, want), name
+    for g, n in enumerate(sizes):
+        few = packed[offs[g]:offs[g] + 5].contiguous().cuda()
+        y = moe.moe_grouped_ffn(few, torch.tensor([0, 5], dtype=torch.int32).cuda(),
+                                moe.WeightTable(w13[g:g + 1], w2[g:g + 1]))
+        assert torch.equal(y, want[offs[g]:offs[g] + 5]), "a few rows of group %d" % g
+
+
 @pytest.mark.parametrize("T,E,k,d,shift", [(1, 1, 1, 1, 0), (16, 16, 2, 64, 0), (17, 17, 4, 65, 0),
                                            (33, 33, 8, 130, 0), (50, 100, 8, 516, 0),
                                            (31, 200, 16, 1028, 0), (15, 256, 16, 16, 1)])
