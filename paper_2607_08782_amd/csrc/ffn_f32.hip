@@ -18,6 +18,8 @@
 // It replaced 16 x 16 output tiles staged through LDS and multiplied on the
 // vector unit: 1000 tokens, d = 256, f = 512, 8 experts, top-2: gate/up 74 -> 30
 // us, down 73 -> 19 us; 64 tokens, d = 128, f = 256: 12.7 -> 7.3 and 20.7 -> 5.9 us.
+#include <type_traits>
+
 #include "common.h"
 
 namespace moe {
@@ -33,37 +35,50 @@ struct F32Args {
     const int32_t* a_rows;               // row p of the input is x[a_rows[p]]; nullptr: x[p]
     const int32_t* offsets;              // row offsets of the groups after the first `lead`
     float* out;                          // [rows][N]
-    int64_t K;
-    int N;
+    int K, N;
     int n_groups, lead, lead_rows;
 };
 
-// 4 consecutive K elements from k of a row; zero from K on (VEC: K is a multiple
-// of 4 and the row 16-byte aligned).  The address is clamped, so a lane past the
-// end re-reads the row's first elements.
-template <bool VEC>
-__device__ __forceinline__ f32x4 load_k4(const float* __restrict__ row, int64_t k, int64_t K) {
+// Four floats at any float's address: one 16-byte load (global loads need no more than
+// the element's alignment).  Rows off a 16-byte boundary and odd widths took an element a
+// load before, behind the vector kernel these products replaced (1500 rows of 5 groups, d
+// = 73, f = 41: that 14.6 us, so 22.2, now 9.7; 4500 rows, d = 1023, f = 513: 972, 532, 234).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// 4 consecutive K elements from k of a row, as they come and before zero_past.  The
+// address is moved down so that all four lie in the row; with K < 4 (TINY), where that
+// is not possible, every element has an address of its own.
+template <bool TINY>
+__device__ __forceinline__ f32x4 load_k4(const float* __restrict__ row, unsigned k, unsigned K) {
     f32x4 v;
-    if (VEC) {
-        const bool ok = k < K;
-        v = *(const f32x4*)(row + (ok ? k : 0));
+    if (TINY) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = ok ? v[j] : 0.f;
+        for (int j = 0; j < 4; ++j) v[j] = row[k + j < K ? k + j : 0];
     } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool ok = k + j < K;
-            const float e = row[ok ? k + j : 0];
-            v[j] = ok ? e : 0.f;
-        }
+        v = *(const f32x4_any*)(row + min(k, K - 4));
     }
     return v;
 }
 
+// Element j of load_k4 is K element k + j, or zero from K on.
+template <bool TINY>
+__device__ __forceinline__ void zero_past(f32x4& v, unsigned k, unsigned K) {
+    if (TINY) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = k + j < K ? v[j] : 0.f;
+    } else {
+        const unsigned s = k - min(k, K - 4);                // by how many the address was moved
+        v[0] = s == 0 ? v[0] : s == 1 ? v[1] : s == 2 ? v[2] : s == 3 ? v[3] : 0.f;
+        v[1] = s == 0 ? v[1] : s == 1 ? v[2] : s == 2 ? v[3] : 0.f;
+        v[2] = s == 0 ? v[2] : s == 1 ? v[3] : 0.f;
+        v[3] = s == 0 ? v[3] : 0.f;
+    }
+}
+
 // NT: 16-column tiles per wave (SWIGLU: of gate and of up each).  KS: waves that
 // split K of one tile (4), or 1: the waves take 2 x 2 tiles.
-template <bool SWIGLU, bool VEC, int NT, int KS>
-__global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
+template <bool SWIGLU, bool TINY, int NT, int KS>
+__global__ __launch_bounds__(F_THREADS, KS == 4 ? 3 : 2) void ffn_f32_kernel(F32Args args) {
     static_assert(KS == 1 || KS == 4, "wave arrangement");
     constexpr int WM = KS == 1 ? 2 : 1, WN = KS == 1 ? 2 : 1;
     constexpr int TM = 16 * F_MT * WM, TN = 16 * NT * WN;
@@ -73,7 +88,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_groups = args.n_groups;
     const int N = args.N;
-    const int64_t K = args.K;
+    const unsigned K = (unsigned)args.K;
     for (int s = tid; s <= n_groups; s += F_THREADS)
         s_off[s] = s < args.lead ? s * args.lead_rows
                                  : args.lead * args.lead_rows + args.offsets[s - args.lead];
@@ -91,7 +106,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
         if (lane == 0) s_tstart[0] = 0;
     }
     __syncthreads();
-    const int nblk = (int)((K + 15) / 16);
+    const int nblk = (int)((K + 15) / 16);               // K < 2^31
     auto quarter = [&](int i) { return (int)((int64_t)i * nblk / 4); };   // of K, in blocks
     const int b0 = KS == 4 ? quarter(wave) : 0, b1 = KS == 4 ? quarter(wave + 1) : nblk;
     const int wm = KS == 1 ? wave & 1 : 0, wn = KS == 1 ? wave >> 1 : 0;
@@ -111,13 +126,13 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
 #pragma unroll
         for (int i = 0; i < F_MT; ++i) {
             const int p = s_off[g] + min(m0 + i * 16 + fr, rows - 1);
-            ap[i] = args.x + (int64_t)(args.a_rows ? args.a_rows[p] : p) * K;
+            ap[i] = args.x + (int64_t)(args.a_rows ? args.a_rows[p] : p) * args.K;
         }
 #pragma unroll
         for (int q = 0; q < NP; ++q)
 #pragma unroll
             for (int j = 0; j < NT; ++j)
-                bp[q][j] = args.w[g] + ((int64_t)q * N + min(n0 + j * 16 + fr, N - 1)) * K;
+                bp[q][j] = args.w[g] + ((int64_t)q * N + min(n0 + j * 16 + fr, N - 1)) * args.K;
 
         f32x4 acc[NP][F_MT][NT], sum[NP][F_MT][NT];      // sum: KS == 1
 #pragma unroll
@@ -128,17 +143,19 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
                 for (int j = 0; j < NT; ++j)
                     acc[q][i][j] = sum[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         f32x4 a[2][F_U][F_MT], b[2][F_U][NP][NT];
-        // blocks at or past b1 load zeros, so the products need no branch
+        unsigned kb[2][F_U];                             // a slot's blocks: their first K element
+        // blocks at or past b1 count as past K: zeros, so the products need no branch
         auto load = [&](int slot, int blk) {
 #pragma unroll
             for (int u = 0; u < F_U; ++u) {
-                const int64_t k = blk + u < b1 ? (int64_t)(blk + u) * 16 + kq : K;
+                kb[slot][u] = blk + u < b1 ? (unsigned)(blk + u) * 16 : K;
+                const unsigned k = kb[slot][u] + kq;
 #pragma unroll
-                for (int i = 0; i < F_MT; ++i) a[slot][u][i] = load_k4<VEC>(ap[i], k, K);
+                for (int i = 0; i < F_MT; ++i) a[slot][u][i] = load_k4<TINY>(ap[i], k, K);
 #pragma unroll
                 for (int q = 0; q < NP; ++q)
 #pragma unroll
-                    for (int j = 0; j < NT; ++j) b[slot][u][q][j] = load_k4<VEC>(bp[q][j], k, K);
+                    for (int j = 0; j < NT; ++j) b[slot][u][q][j] = load_k4<TINY>(bp[q][j], k, K);
             }
         };
         // f(q, i, j) for every accumulator
@@ -150,9 +167,18 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
 #pragma unroll
                     for (int j = 0; j < NT; ++j) f(q, i, j);
         };
-        auto mma = [&](int slot, int blk) {
+        auto mma = [&](auto whole, int slot, int blk) {
 #pragma unroll
             for (int u = 0; u < F_U; ++u) {
+                if constexpr (!decltype(whole)::value) {
+                    const unsigned k = kb[slot][u] + kq;
+#pragma unroll
+                    for (int i = 0; i < F_MT; ++i) zero_past<TINY>(a[slot][u][i], k, K);
+#pragma unroll
+                    for (int q = 0; q < NP; ++q)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) zero_past<TINY>(b[slot][u][q][j], k, K);
+                }
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     each([&](int q, int i, int j) {
@@ -171,12 +197,22 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
                 }
             }
         };
+        // turns of blocks that all lie in the rows, then the last ones a batch at a time, so
+        // that a short K loads and multiplies no batch for its zeros (12000 rows, d = 128, f
+        // = 256: 81 -> 57 us)
+        const int full = min(b1, (int)(K / 16));
+        int blk = b0;
         load(0, b0);
-        for (int blk = b0; blk < b1; blk += 2 * F_U) {
-            load(1, blk + F_U);
-            mma(0, blk);
-            load(0, blk + 2 * F_U);
-            mma(1, blk + F_U);
+        if constexpr (!TINY)
+            for (; blk + 2 * F_U <= full; blk += 2 * F_U) {
+                load(1, blk + F_U);
+                mma(std::true_type{}, 0, blk);
+                load(0, blk + 2 * F_U);
+                mma(std::true_type{}, 1, blk + F_U);
+            }
+        for (; blk < b1; blk += F_U) {
+            mma(std::false_type{}, 0, blk);
+            if (blk + F_U < b1) load(0, blk + F_U);
         }
         if constexpr (KS == 1)
             each([&](int q, int i, int j) { acc[q][i][j] = sum[q][i][j] + acc[q][i][j]; });
@@ -223,7 +259,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void ffn_f32_kernel(F32Args args) {
 }
 
 template <bool SWIGLU>
-int launch_product(const F32Args& a, int64_t cap_rows, bool vec, int cus, hipStream_t s) {
+int launch_product(const F32Args& a, int64_t cap_rows, int cus, hipStream_t s) {
     // tiles of a TM-row, TN-column split: at most cap_rows / TM + n_groups row tiles
     auto tiles = [&](int TM, int TN) {
         return (cap_rows / TM + a.n_groups) * ceil_div(a.N, TN);
@@ -233,19 +269,17 @@ int launch_product(const F32Args& a, int64_t cap_rows, bool vec, int cus, hipStr
     // below that K is split over the waves, and with fewer than two 32 x 32 tiles
     // per CU the tile is 16 columns wide (twice the workgroups)
     const int64_t t64 = tiles(64, 64), t32 = tiles(32, 32);
-    if (!vec)
-        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, false, 2, 4>), grid(t32), dim3(F_THREADS), 0, s, a);
-    else if (t64 >= 4 * cus)
-        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, true, 2, 1>), grid(t64), dim3(F_THREADS), 0, s, a);
-    else if (t32 >= 2 * cus)
+    if (a.K < 4)
         hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, true, 2, 4>), grid(t32), dim3(F_THREADS), 0, s, a);
+    else if (t64 >= 4 * cus)
+        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, false, 2, 1>), grid(t64), dim3(F_THREADS), 0, s, a);
+    else if (t32 >= 2 * cus)
+        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, false, 2, 4>), grid(t32), dim3(F_THREADS), 0, s, a);
     else
-        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, true, 1, 4>), grid(tiles(32, 16)), dim3(F_THREADS),
+        hipLaunchKernelGGL((ffn_f32_kernel<SWIGLU, false, 1, 4>), grid(tiles(32, 16)), dim3(F_THREADS),
                            0, s, a);
     return launch_status();
 }
-
-bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
 
@@ -260,31 +294,25 @@ int launch_ffn_f32(const float* x, const int32_t* offsets, int n_groups, const v
     a.lead = lead;
     a.lead_rows = lead_rows;
     if (products & MOE_FFN_GATE_UP) {
-        bool vec = d % 4 == 0 && aligned16(x);
-        for (int i = 0; i < MOE_MAX_GROUPS; ++i) {
+        for (int i = 0; i < MOE_MAX_GROUPS; ++i)
             a.w[i] = i < n_groups ? (const float*)w13[i] : nullptr;
-            vec = vec && aligned16(a.w[i]);
-        }
         a.x = x;
         a.a_rows = a_rows;
         a.out = h;
         a.K = d;
         a.N = f;
-        const int st = launch_product<true>(a, cap_rows, vec, cus, s);
+        const int st = launch_product<true>(a, cap_rows, cus, s);
         if (st != MOE_OK) return st;
     }
     if (products & MOE_FFN_DOWN) {
-        bool vec = f % 4 == 0 && aligned16(h);
-        for (int i = 0; i < MOE_MAX_GROUPS; ++i) {
+        for (int i = 0; i < MOE_MAX_GROUPS; ++i)
             a.w[i] = i < n_groups ? (const float*)w2[i] : nullptr;
-            vec = vec && aligned16(a.w[i]);
-        }
         a.x = h;
         a.a_rows = nullptr;
         a.out = y;
         a.K = f;
         a.N = d;
-        const int st = launch_product<false>(a, cap_rows, vec, cus, s);
+        const int st = launch_product<false>(a, cap_rows, cus, s);
         if (st != MOE_OK) return st;
     }
     return MOE_OK;

@@ -36,6 +36,10 @@ def _placed(t, shift):
     ([1000, 70, 1100], 20, 2051, 0, False),        # 64 x 64 tiles of whole-K waves (gate/up)
     ([700, 65, 800], 2052, 36, 0, True),           # ... and of the down product
     ([1], 1, 1, 0, False),
+    ([33, 2], 3, 2, 1, False),                     # rows shorter than a load
+    ([5, 40], 4, 5, 3, True),
+    ([70], 6, 19, 2, False),                       # a K tail in every quarter's last block
+    ([31, 600], 65, 130, 1, True),
 ])
 def test_f32_ffn_tile_edges(sizes, d, f, shift, gather):
     say("[f32 ffn]", sizes, "d=%d f=%d shift=%d gather=%s" % (d, f, shift, gather))
