@@ -133,9 +133,11 @@ template <auto F>
 int launch_route_topk(const void* x, int dtype, const void* w, const float* bias, int64_t T, int d,
                       int E, int k, int flags, float* logits, int32_t* idx, float* gate, void* ws,
                       hipStream_t s);
-// bf16 scores of a short batch (route.hip): whether a batch takes them, and the launch
-// (scores + bias to out[T][E])
+// bf16 scores of a short batch (route.hip): whether a batch takes them, in how many K
+// chunks, and the launch (one chunk: scores + bias to out[T][E]; more: the chunks' sums to
+// out[chunk][T][E], bias left to the top-k)
 bool route_short(int64_t T, int d, int E);
+int route_chunks(int64_t T, int d, int E);
 [[nodiscard]]
 int launch_scores_short(const void* x, const void* w, const float* bias, int64_t T, int d, int E,
                         float* out, hipStream_t s);

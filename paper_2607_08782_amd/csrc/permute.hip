@@ -348,6 +348,9 @@ struct SmallArgs {
     int32_t* counts;                     // [E] (COUNT)
     int32_t* coact;                      // [E][E], nullable (COUNT)
     const float* scores;                 // [T][E], bias added (KM > 0)
+    int chunks;                          // > 1: scores come in K chunks [chunk][T][E], without
+    const float* bias;                   // the bias; their sums + bias go to sums (which may be
+    float* sums;                         // chunk 0 itself), read by the top-k
     int32_t* idx_out;                    // [T][k] (KM > 0)
     float* gate_out;
     int renorm;
@@ -390,7 +393,18 @@ __global__ __launch_bounds__(SMALL_T) void perm_small_kernel(SmallArgs a, SlotTa
     const bool coact = COUNT && a.coact != nullptr;
     if (coact)
         for (int i = tid; i < E * E; i += SMALL_T) co_s[i] = 0;
-    if constexpr (KM > 0) topk_tokens<KM, C, 1>(a.scores, E, T, 0, E, k, a.renorm, ids_s, gates_s);
+    if constexpr (KM > 0) {
+        const float* scores = a.scores;
+        if (a.chunks > 1) {
+            for (int i = tid; i < T * E; i += SMALL_T) {
+                const float v = sum_chunks(a.scores + i, (int64_t)T * E, a.chunks);
+                a.sums[i] = a.bias ? v + a.bias[i % E] : v;
+            }
+            __syncthreads();
+            scores = a.sums;
+        }
+        topk_tokens<KM, C, 1>(scores, E, T, 0, E, k, a.renorm, ids_s, gates_s);
+    }
     __syncthreads();
     // The assignments i = t k + r, one per thread and PLAN_U per thread at a time: f(i,
     // token, expert).  A loop over a token's k assignments by one thread each waited
@@ -670,12 +684,13 @@ int launch_route_package(const void* x, int dtype, const void* w, const float* b
     const bool topk = small && plan_topk(T, k, E) &&
                       (given || (dtype == MOE_BF16 && route_short(T, d, E)));
     const int dcopy = x_perm ? d : 0;
-    int st = MOE_OK;
+    int st = MOE_OK, chunks = 1;
     const float* scores = logits;
     if (!topk) {
         st = launch_route_topk(x, dtype, w, bias, T, d, E, k, flags, logits, idx, gate, ws_route, s);
     } else if (!given) {
-        float* out = logits ? logits : (float*)ws_route;
+        chunks = route_chunks(T, d, E);
+        float* out = chunks > 1 || !logits ? (float*)ws_route : logits;
         scores = out;
         st = launch_scores_short(x, w, bias, T, d, E, out, s);
     }
@@ -727,6 +742,9 @@ int launch_route_package(const void* x, int dtype, const void* w, const float* b
     a.counts = counts;
     a.coact = coact;
     a.scores = scores;
+    a.chunks = chunks;
+    a.bias = bias;
+    a.sums = logits ? logits : (float*)ws_route;
     a.idx_out = idx;
     a.gate_out = gate;
     a.renorm = (flags & MOE_RENORM) ? 1 : 0;

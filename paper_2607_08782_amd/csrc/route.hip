@@ -173,19 +173,19 @@ __global__ __launch_bounds__(RB_THREADS) void route_bf16_kernel(
 }
 
 // bf16 gate scores of short batches (few token blocks, e.g. decode): one 8-wave
-// workgroup per (16 tokens, 16 experts) on MFMA 16x16x32, the waves splitting K,
-// every operand load of a wave's slice issued before its first product (up to 8
-// K steps at a time), the 16 partial tiles summed in wave order through LDS.  Rows
+// workgroup per (16 tokens, 16 experts, K chunk) on MFMA 16x16x32, the waves splitting
+// the chunk, every operand load of a wave's slice issued before its first product (up to 8
+// K steps at a time), the 8 partial tiles summed in wave order through LDS.  Rows
 // past the batch or past E, and K past d, read as zero through the buffer
-// descriptors.  Bound by load latency: the scores leave finished, where K chunks on
-// separate workgroups left up to 32 partial scores each for the top-k's launch to
-// read back.
+// descriptors.  Bound by load latency, and past 2048 K elements by what one CU can
+// load.  With one chunk the scores leave finished, bias added; with more the chunks'
+// sums go to out[chunk][T][E] for the top-k to add (route_chunks).
 constexpr int SS_WAVES = 8;
 constexpr int SS_STEPS = 8;            // 32-wide K steps of loads issued at once
 
 __global__ __launch_bounds__(SS_WAVES * 64) void score_small_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, const float* __restrict__ bias,
-    int64_t T, int d, int E, float* __restrict__ out) {
+    int64_t T, int d, int E, int chunks, float* __restrict__ out) {
     __shared__ f32x4 part[SS_WAVES][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int e0 = blockIdx.x * 16;
@@ -199,9 +199,11 @@ __global__ __launch_bounds__(SS_WAVES * 64) void score_small_kernel(
         (void*)(W + (int64_t)e0 * d), (short)0, ne * d * 2, RB_RSRC_WORD3);
     // the thread that finishes (token r, expert e): its bias, loaded beside the operands
     const int r = (tid >> 4) & 15, e = tid & 15;
-    const float b = bias && e < ne ? bias[e0 + e] : 0.f;
-    const int nsteps = (d + 31) / 32;
-    const int sbeg = wave * nsteps / SS_WAVES, send = (wave + 1) * nsteps / SS_WAVES;
+    const float b = chunks == 1 && bias && e < ne ? bias[e0 + e] : 0.f;
+    const int nall = (d + 31) / 32, chunk = blockIdx.z;       // chunk * nall < 2^31
+    const int cbeg = chunks == 1 ? 0 : chunk * nall / chunks;
+    const int nsteps = chunks == 1 ? nall : (chunk + 1) * nall / chunks - cbeg;
+    const int sbeg = cbeg + wave * nsteps / SS_WAVES, send = cbeg + (wave + 1) * nsteps / SS_WAVES;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = sbeg; s0 < send; s0 += SS_STEPS) {
         uint4 a[SS_STEPS], w[SS_STEPS];
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(SS_WAVES * 64) void score_small_kernel(
         float sum = p[0];
 #pragma unroll
         for (int v = 1; v < SS_WAVES; ++v) sum += p[v * 256];
-        out[(t0 + r) * E + e0 + e] = sum + b;
+        out[(chunk * T + t0 + r) * E + e0 + e] = chunks == 1 ? sum + b : sum;
     }
 }
 
@@ -334,6 +336,25 @@ __global__ __launch_bounds__(ROUTE_THREADS) void topk_given_kernel(
     topk_tokens<KM, C>(scores + t0 * E, E, nt, t0, E, k, renorm, idx, gate);
 }
 
+// Top-k of scores in K chunks (part[chunk][T][E]): a token's chunks summed in chunk
+// order, then as for scores of its own (finish_tokens).
+template <int KM, int C>
+__global__ __launch_bounds__(ROUTE_THREADS) void topk_chunks_kernel(
+    const float* __restrict__ part, int chunks, const float* __restrict__ bias, int64_t T, int E,
+    int k, int renorm, float* __restrict__ logits, int32_t* __restrict__ idx,
+    float* __restrict__ gate, int tpb) {
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    const int ldS = ((E + 15) & ~15) + 1;
+    const int64_t t0 = (int64_t)blockIdx.x * tpb;
+    const int nt = (int)((T - t0) < tpb ? (T - t0) : tpb);
+    for (int c = threadIdx.x; c < nt * E; c += ROUTE_THREADS) {
+        const int r = c / E, e = c - r * E;
+        smem[r * ldS + e] = sum_chunks(part + t0 * E + c, T * E, chunks);
+    }
+    __syncthreads();
+    finish_tokens<KM, C>(smem, ldS, nt, t0, E, k, renorm, bias, logits, idx, gate);
+}
+
 // Token rows per workgroup of the bf16 score kernel, by expert count.
 int route_rows(int E) {
     const int E_pad = (E + 15) & ~15;
@@ -371,6 +392,16 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
         if (St == 1 && E <= SCORE_TOPK_MAX_E)
             return launch_score_tiles_topk(false, x, w, nullptr, nullptr, bias, T, 2 * d, E, k,
                                            renorm, logits, idx, gate, s);
+        const int chunks = route_short(T, d, E) ? route_chunks(T, d, E) : 1;
+        if (chunks > 1) {
+            const int st = launch_scores_short(x, w, nullptr, T, d, E, (float*)ws, s);
+            if (st != MOE_OK) return st;
+            const int tpb = simple_tokens_per_block(T, E);
+            hipLaunchKernelGGL((topk_chunks_kernel<KM, C>), dim3((unsigned)ceil_div(T, tpb)),
+                               dim3(ROUTE_THREADS), (size_t)tpb * (E_pad + 1) * sizeof(float), s,
+                               (const float*)ws, chunks, bias, T, E, k, renorm, logits, idx, gate, tpb);
+            return launch_status();
+        }
         float* out = logits ? logits : (float*)ws;
         given = out;
         if (St == 1) {
@@ -409,7 +440,7 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
 }  // namespace
 
 // Short batches: too few token blocks for the one-launch kernel (fewer than 128) and
-// K long enough to be worth splitting over 16 waves.  Their scores come from
+// K long enough to be worth splitting over 8 waves.  Their scores come from
 // score_small_kernel, the top-k from a launch of its own (or from the packaging
 // launch).
 bool route_short(int64_t T, int d, int E) {
@@ -417,20 +448,36 @@ bool route_short(int64_t T, int d, int E) {
            score_tiles_split(T, 2 * d, E, true) == 0;
 }
 
+// K chunks of a short batch's scores: one per 2048 elements, as long as they make no more
+// than a workgroup a CU (beyond that every CU is loading already, and the chunks' way
+// through memory costs more: 300 tokens, d = 4096, 128 experts 14.8 us in one chunk, 16.5 in
+// two).  moe_route_topk of 64 tokens in one chunk and in this many: d = 4096, 8 experts 10.4
+// and 8.5 us; d = 14336 24.6 and 9.1; d = 7168, 200 experts 24.4 and 16.3.
+int route_chunks(int64_t T, int d, int E) {
+    const int64_t tiles = ceil_div(T, 16) * ceil_div(E, 16);
+    int64_t chunks = ceil_div(d, 2048);
+    if (chunks > 256 / tiles) chunks = 256 / tiles;
+    if (chunks > 16) chunks = 16;
+    return chunks < 1 ? 1 : (int)chunks;
+}
+
 int launch_scores_short(const void* x, const void* w, const float* bias, int64_t T, int d, int E,
                         float* out, hipStream_t s) {
-    hipLaunchKernelGGL(score_small_kernel, dim3((unsigned)ceil_div(E, 16), (unsigned)ceil_div(T, 16)),
+    const int chunks = route_chunks(T, d, E);
+    hipLaunchKernelGGL(score_small_kernel,
+                       dim3((unsigned)ceil_div(E, 16), (unsigned)ceil_div(T, 16), (unsigned)chunks),
                        dim3(SS_WAVES * 64), 0, s, (const bf16_t*)x, (const bf16_t*)w, bias, T, d, E,
-                       out);
+                       chunks, out);
     return launch_status();
 }
 
-// scores kept for the top-k's launch when the caller wants none stored
+// Scores kept for the top-k: a short batch's K chunks, or its scores and those of a tiled
+// batch when the caller wants none stored.
 size_t route_ws_bytes(int dtype, int64_t T, int d, int E, int flags) {
     if ((flags & MOE_LOGITS_IN) || dtype != MOE_BF16 || T <= 0) return 0;
-    return route_short(T, d, E) || score_tiles_split(T, 2 * d, E, true) == 1
-               ? (size_t)T * (size_t)E * sizeof(float)
-               : 0;
+    const size_t scores = (size_t)T * (size_t)E * sizeof(float);
+    if (route_short(T, d, E)) return route_chunks(T, d, E) * scores;
+    return score_tiles_split(T, 2 * d, E, true) == 1 ? scores : 0;
 }
 
 int launch_topk_given(const float* scores, int64_t T, int E, int k, int flags, int32_t* idx,

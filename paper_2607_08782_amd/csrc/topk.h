@@ -241,6 +241,20 @@ __device__ __forceinline__ void topk_tokens(const float* S, int ldS, int nt, int
     }
 }
 
+// p[0] + p[stride] + ... + p[(n - 1) stride], in that order, four loads at a time: a score
+// from its K chunks (score_small_kernel).
+__device__ __forceinline__ float sum_chunks(const float* p, int64_t stride, int n) {
+    float sum = 0.f;
+    for (int c0 = 0; c0 < n; c0 += 4) {
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = p[(c0 + j < n ? c0 + j : n - 1) * stride];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum = c0 + j < n ? sum + v[j] : sum;
+    }
+    return sum;
+}
+
 // Bias, optional score store and top-k for the `nt` tokens whose scores sit in
 // S[r * ldS + e] (LDS).
 template <int KM, int C, int NT = TopkShape<C>::NT>

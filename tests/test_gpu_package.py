@@ -32,6 +32,13 @@ CASES = [
     (64, 8, 2, 128, 1, False, "f32", True, False),
     (200, 40, 5, 64, 4, False, "bf16", True, False),
     (0, 8, 2, 64, 2, True, "bf16", False, True),
+    # K above 2048: short batches' scores in K chunks, summed by either top-k
+    (1, 8, 2, 2056, 2, False, "bf16", False, False),
+    (64, 8, 2, 4096, 4, False, "bf16", False, True),
+    (60, 128, 8, 4104, 9, True, "bf16", False, False),
+    (7, 200, 16, 7168, 5, False, "bf16", False, False),
+    (300, 60, 4, 14336, 8, False, "bf16", False, False),
+    (2000, 16, 2, 4096, 4, False, "bf16", False, False),    # long: the histogram's launches
     # long batches: the count of all experts per block (up to 32768 tokens, room for it)
     (1088, 128, 8, 256, 9, True, "bf16", False, False),
     (5001, 13, 3, 64, 4, False, "bf16", False, True),
@@ -42,6 +49,38 @@ CASES = [
     (4096, 8, 2, 64, 1, True, "bf16", False, False),        # every expert here: no room
     (1500, 4, 2, 72, 2, True, "f32", True, True),
 ]
+
+
+@pytest.mark.parametrize("T,E,k,d", [(64, 8, 2, 2048), (64, 8, 2, 4096), (33, 100, 8, 7168),
+                                     (500, 40, 4, 4096), (8200, 64, 6, 256),
+                                     (2048, 128, 8, 256), (2049, 128, 8, 256)])
+def test_scores_not_asked_for(T, E, k, d):
+    """Without a place for the scores the choice and the gates are the same bits, from
+    the router alone and in one call, and the scores agree with float64."""
+    say("[package] no scores T=%d E=%d k=%d d=%d" % (T, E, k, d))
+    cfg = synth.custom_config(dtype="bf16", d=d, E=E, k=k, f=64, G=4, replicas=1, zipf=1.1)
+    inp = synth.make_layer(cfg, T, seed=5, device="cuda", experts="none")
+    logits, idx, gate = moe.moe_route_topk(inp.X, inp.Wr, inp.bias, k)
+    ref = inp.X.double() @ inp.Wr.double().t() + inp.bias.double()
+    mag = inp.X.double().abs() @ inp.Wr.double().abs().t() + inp.bias.double().abs()
+    # an fp32 sum of d exact products in any order, 2 u per addition, and the bias
+    assert bool(((logits.double() - ref).abs() <= (2 * d + 8) * 2.0 ** -24 * mag + 1e-30).all())
+    _, idx2, gate2 = moe.moe_route_topk(inp.X, inp.Wr, inp.bias, k, want_logits=False)
+    assert torch.equal(idx, idx2) and torch.equal(gate, gate2)
+    n_local = int(inp.placement[:, 0].sum())
+    cap = T * min(k, n_local)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    out = {"x_perm": None, "group_offsets": torch.zeros((n_local + 1,), **i32),
+           "row_token": torch.zeros((cap,), **i32), "row_gate": torch.zeros((cap,), device="cuda"),
+           "token_row": torch.zeros((T, k), **i32), "send_counts": None}
+    idx3, gate3 = torch.zeros_like(idx), torch.zeros_like(gate)
+    need = moe.moe_route_topk_ws_bytes(moe.MOE_BF16, T, d, E, moe.MOE_RENORM)
+    moe.moe_route_package(inp.X, inp.Wr, inp.bias, inp.placement, 0, logits=None, topk_idx=idx3,
+                          topk_gate=gate3, ws_route=moe.workspace(need, "cuda"),
+                          counts=torch.zeros((E,), **i32), coact=None, out=out,
+                          ws_perm=moe.workspace(moe.moe_permute_ws_bytes(T, k, E), "cuda"),
+                          cap_rows=cap, copy_rows=False)
+    assert torch.equal(idx, idx3) and torch.equal(gate, gate3)
 
 
 @pytest.mark.parametrize("T,E,k,d,G,coact,dtype,logits_in,copy", CASES)
