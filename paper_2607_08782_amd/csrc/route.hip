@@ -439,13 +439,18 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
 
 }  // namespace
 
-// Short batches: too few token blocks for the one-launch kernel (fewer than 128) and
-// K long enough to be worth splitting over 8 waves.  Their scores come from
-// score_small_kernel, the top-k from a launch of its own (or from the packaging
-// launch).
+// Short batches: too few token blocks for the one-launch kernel (fewer than 128), K
+// long enough to be worth splitting over 8 waves, and no more rounds of 16 x 16
+// workgroups over the CUs than half the expert tiles: a round takes about 7.6 us at d =
+// 4096, the one-launch kernel, which reads the tokens once for all experts, 30, 41 and 46 us
+// in its single round at 64, 100 and 128 experts (d = 4096, 128 experts: 2000 tokens 38.5
+// against 46.4, 2500 46.3 against 46.6, 4000 66.5 against 47.2; 64 experts: 2000 23.3
+// against 29.8, 3500 37.9 against 30.2).  Their scores come from score_small_kernel, the
+// top-k from a launch of its own (or from the packaging launch).
 bool route_short(int64_t T, int d, int E) {
+    const int64_t et = ceil_div(E, 16), tiles = ceil_div(T, 16) * et;
     return T > 0 && ceil_div(T, route_rows(E)) < 128 && (d + 31) / 32 >= (E <= 16 ? 8 : 4) &&
-           score_tiles_split(T, 2 * d, E, true) == 0;
+           ceil_div(tiles, 256) <= (et + (et <= 8)) / 2 && score_tiles_split(T, 2 * d, E, true) == 0;
 }
 
 // K chunks of a short batch's scores: one per 2048 elements, as long as they make no more
