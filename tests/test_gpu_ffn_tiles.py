@@ -1,8 +1,9 @@
 """The bf16 expert FFN at the edges of its kernels: tiles of 256 rows and their LDS
-ring (K of one and two 64-wide steps, column tails, row tiles in blocks of eight, many
-tiles a workgroup), whole-K strips (32 output columns, 32- and 64-row tiles, K from
-64 to their longest), each against the oracle's expert FFN in float64 on sampled rows.
-The tolerance is the parity protocol's: h and y are rounded to bf16 (2^-9 relative
+ring (K of one and two 64-wide steps, column tails, row tiles in blocks of eight; more
+tiles than workgroups, so that a tile's last stages load the next tile's first or, with K
+= 64, its ring starts again), whole-K strips (32 output columns, 32- and 64-row tiles, K
+from 64 to their longest), each against the oracle's expert FFN in float64 on sampled rows.
+The tolerance is the parity protocol's: h and y are rounded to bf16 (2^-8 relative
 each), sums in fp32."""
 import numpy as np
 import pytest
@@ -18,13 +19,18 @@ LARGE, SMALL = moe.MOE_FFN_LARGE_GROUPS, moe.MOE_FFN_SMALL_GROUPS
 
 
 @pytest.mark.parametrize("sizes,d,f,hint,gather", [
-    ([257, 300], 64, 64, LARGE, False),             # one 64-wide K step: rings not chained
+    ([257, 300], 64, 64, LARGE, False),             # one 64-wide K step
     ([700, 1, 0, 513], 64, 192, LARGE, True),
-    ([300, 600], 128, 64, LARGE, True),             # gate/up chained, down not
+    ([300, 600], 128, 64, LARGE, True),             # two in the gate/up product, one in the down
     ([256, 512, 1024], 192, 448, LARGE, False),     # exact tiles, column tails
     ([2305], 256, 320, LARGE, False),               # ten row tiles: two blocks of five
     ([4500, 260], 128, 128, LARGE, True),           # 18 row tiles: three blocks of six
     ([300] * 20, 64, 128, LARGE, False),
+    # two and three tiles a workgroup, ragged rows and columns
+    ([5000 + 37 * i for i in range(16)], 64, 192, LARGE, True),    # the ring starts again, the
+    ([5000 + 37 * i for i in range(16)], 64, 64, LARGE, False),    # next tile's rows gathered
+    ([5000 + 37 * i for i in range(16)], 128, 320, LARGE, True),   # four stages: chained
+    ([4900 + 41 * i for i in range(16)], 192, 128, LARGE, False),
     ([1, 64, 33, 0, 17], 64, 64, SMALL, True),      # strips, one K stage
     ([1, 64, 33, 0, 17], 4096, 128, SMALL, True),   # longest K, both tile heights
     ([128, 129, 256, 65], 192, 2048, SMALL, False),   # several row tiles and tails
@@ -72,3 +78,28 @@ def test_bf16_ffn_tile_edges(sizes, d, f, hint, gather):
         close(got[pick], ref, OUT_TOL["bf16"], "group %d" % g)
         assert np.isfinite(got[a:a + n]).all()
     assert np.all(got[N:] == 5.0)
+
+
+def test_more_tiles_than_a_list_holds():
+    """A workgroup lists 256 of its tiles at a time: 260 tiles each, the second list
+    included, every row tile and all 64 column tiles of the gate/up product (a column
+    tile that is wrong or missing moves its rows of y by an eighth of their size)."""
+    sizes, d, f = [200000, 66300], 64, 8192
+    say("[bf16 ffn] %d tiles of the gate/up product" % (sum(-(-n // 256) for n in sizes) * (f // 128)))
+    N = sum(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((N, d), generator=gen, device="cuda").bfloat16()
+    w13 = [(torch.randn((2 * f, d), generator=gen, device="cuda") * d ** -0.5).bfloat16() for _ in sizes]
+    w2 = [(torch.randn((d, f), generator=gen, device="cuda") * f ** -0.5).bfloat16() for _ in sizes]
+    off = torch.tensor([0, sizes[0], N], dtype=torch.int32).cuda()
+    y = moe.moe_grouped_ffn(x, off, moe.WeightTable(w13, w2), products=3 | LARGE)
+    torch.cuda.synchronize()
+    a = 0
+    for g, n in enumerate(sizes):
+        pick = torch.arange(0, n, 61, device="cuda") + a           # four or five of each row tile
+        xs = x[pick].double()
+        h = torch.nn.functional.silu(xs @ w13[g][:f].double().t()) * (xs @ w13[g][f:].double().t())
+        ref = h @ w2[g].double().t()
+        rel = (y[pick].double() - ref).norm(dim=1) / ref.norm(dim=1)
+        assert float(rel.max()) < OUT_TOL["bf16"], (g, float(rel.max()))
+        a += n
