@@ -66,8 +66,7 @@ __device__ __forceinline__ void silu(float (&a)[N]) {
 // moves: within rows of 16 lanes (row_shr 1, 2, 4, 8), then each row's last lane added
 // to the row after it (row_bcast 15) and lane 31 to the upper half (row_bcast 31).  A
 // shuffle per step goes through LDS, six dependent round trips.
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-    (void)lane;
+__device__ __forceinline__ int wave_incl_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
@@ -151,15 +150,14 @@ int launch_route_topk_e4m3(const uint8_t* xq, const float* sx, const uint8_t* wq
                            const float* bias, int64_t T, int d, int E, int k, int flags,
                            float* logits, int32_t* idx, float* gate, hipStream_t s);
 
-// Tiled score kernel (score.hip): K chunks for a batch, 0 if the shape does not
-// suit it; launch with S chunks (S == 1 writes scores + bias to out[T][E],
-// S > 1 partial scores to out[S][T][E], to be summed in chunk order).
-int score_tiles_split(int64_t T, int rowbytes, int E, bool allow_split);
+// Tiled score kernel (score.hip): whether a batch takes it, and the launch over more than
+// SCORE_TOPK_MAX_E experts (scores + bias to out[T][E]).
+bool score_tiled(int64_t T, int rowbytes, int E);
 [[nodiscard]]
 int launch_score_tiles(bool fp8, const void* x, const void* w, const float* sx, const float* sw,
-                       const float* bias, int64_t T, int rowbytes, int E, int S, float* out,
+                       const float* bias, int64_t T, int rowbytes, int E, float* out,
                        hipStream_t s);
-// The tiled score kernel with one K chunk over 33 .. SCORE_TOPK_MAX_E experts
+// The tiled score kernel over 33 .. SCORE_TOPK_MAX_E experts
 // (MOE_ERR_SHAPE otherwise), finishing with the top-k and gates of its tokens
 // (logits nullable: scores + bias stored there when given).
 // Wider batches keep the top-k launch of their own (its lanes per token double and the

@@ -168,7 +168,7 @@ __device__ __forceinline__ void tile_starts(const int* s_off, int n_groups, int 
         const int g = g0 + lane;
         const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
         const int v = rows > small_rows ? (int)ceil_div(rows, BM) * n_tiles : 0;
-        const int incl = wave_incl_scan(v, lane);
+        const int incl = wave_incl_scan(v);
         if (g < n_groups) s_tstart[g + 1] = carry + incl;
         carry += __shfl(incl, 63, 64);
     }
@@ -749,7 +749,7 @@ __device__ void make_stream_plan(const StreamArgs& a, StreamPlan& P, int nthread
             const bool small = rows > 0 && rows <= lim;
             const int rs = small ? rows : 0;
             const int items = small ? (int)ceil_div(rows, ST_M) * nt : 0;
-            const int irs = wave_incl_scan(rs, lane), iit = wave_incl_scan(items, lane);
+            const int irs = wave_incl_scan(rs), iit = wave_incl_scan(items);
             if (g < a.n_groups) {
                 P.qbase[g] = rows_small + irs - rs;
                 P.istart[g] = base + iit - items;    // scaled by S below
@@ -955,7 +955,7 @@ __global__ __launch_bounds__(SP_THREADS, SP_WG_PER_CU) void strip_gemm_kernel(St
             const int g = g0 + lane;
             const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
             const int v = rows <= lim || args.zero_big ? (int)ceil_div(rows, SP_M) * nt : 0;
-            const int incl = wave_incl_scan(v, lane);
+            const int incl = wave_incl_scan(v);
             if (g < n_groups) s_tstart[g + 1] = carry + incl;
             carry += __shfl(incl, 63, 64);
         }

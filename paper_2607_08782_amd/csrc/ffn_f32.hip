@@ -99,7 +99,7 @@ __global__ __launch_bounds__(F_THREADS, KS == 4 ? 3 : 2) void ffn_f32_kernel(F32
         for (int g0 = 0; g0 < n_groups; g0 += 64) {
             const int g = g0 + lane;
             const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
-            const int incl = wave_incl_scan((rows + TM - 1) / TM * ncol, lane);
+            const int incl = wave_incl_scan((rows + TM - 1) / TM * ncol);
             if (g < n_groups) s_tstart[g + 1] = carry + incl;
             carry += __shfl(incl, 63, 64);
         }

@@ -203,6 +203,8 @@ int launch_histogram(const int32_t* idx, int64_t T, int k, int E, int32_t* count
         hipLaunchKernelGGL((histogram_kernel<false, false>), dim3((unsigned)blocks),
                            dim3(HIST_THREADS), 0, s, idx, T, k, E, counts, coact);
     } else if (E <= LDS_COACT_MAX_E) {
+        // counts and co-activation in one pass over whole tokens (coact_kernel, for callers
+        // that have the counts, takes an assignment a thread, and their number in 32 bits);
         // 64 workgroups: each flushes its non-zero E*E bins with global atomics, so
         // more workgroups add flush traffic (Qwen3-shaped prefill: 16 -> 25.1 us,
         // 32 -> 17.7, 64 -> 14.4, 128 and 256 -> 14.5, with the clearing launch)

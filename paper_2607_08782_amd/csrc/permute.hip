@@ -458,7 +458,7 @@ __global__ __launch_bounds__(SMALL_T) void perm_small_kernel(SmallArgs a, SlotTa
                 size = (int32_t)(replica_lo_small(q + 1, cnt, hosts) - lo);
                 size_s[s] = size;
             }
-            const int32_t incl = wave_incl_scan(size, lane);
+            const int32_t incl = wave_incl_scan(size);
             if (s < n_local) off_s[s + 1] = carry + incl;
             carry += __shfl(incl, 63, 64);
         }

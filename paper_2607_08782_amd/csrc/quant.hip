@@ -425,11 +425,11 @@ int launch_route_topk_e4m3(const uint8_t* xq, const float* sx, const uint8_t* wq
                            const float* bias, int64_t T, int d, int E, int k, int flags,
                            float* logits, int32_t* idx, float* gate, hipStream_t s) {
     if (T == 0) return MOE_OK;
-    if (score_tiles_split(T, d, E, false) == 1) {  // long batch over many experts
+    if (score_tiled(T, d, E)) {                    // long batch over many experts
         if (E <= SCORE_TOPK_MAX_E)
             return launch_score_tiles_topk(true, xq, wq, sx, sw, bias, T, d, E, k,
                                            (flags & MOE_RENORM) ? 1 : 0, logits, idx, gate, s);
-        const int st = launch_score_tiles(true, xq, wq, sx, sw, bias, T, d, E, 1, logits, s);
+        const int st = launch_score_tiles(true, xq, wq, sx, sw, bias, T, d, E, logits, s);
         if (st != MOE_OK) return st;
         return launch_topk_given(logits, T, E, k, flags, idx, gate, s);
     }

@@ -388,8 +388,8 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
         return launch_status();
     }
     if (!(flags & MOE_LOGITS_IN)) {
-        const int St = score_tiles_split(T, 2 * d, E, true);
-        if (St == 1 && E <= SCORE_TOPK_MAX_E)
+        const bool tiled = score_tiled(T, 2 * d, E);
+        if (tiled && E <= SCORE_TOPK_MAX_E)
             return launch_score_tiles_topk(false, x, w, nullptr, nullptr, bias, T, 2 * d, E, k,
                                            renorm, logits, idx, gate, s);
         const int chunks = route_short(T, d, E) ? route_chunks(T, d, E) : 1;
@@ -404,9 +404,8 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
         }
         float* out = logits ? logits : (float*)ws;
         given = out;
-        if (St == 1) {
-            const int st = launch_score_tiles(false, x, w, nullptr, nullptr, bias, T, 2 * d, E, 1,
-                                              out, s);
+        if (tiled) {
+            const int st = launch_score_tiles(false, x, w, nullptr, nullptr, bias, T, 2 * d, E, out, s);
             if (st != MOE_OK) return st;
         } else if (route_short(T, d, E)) {
             const int st = launch_scores_short(x, w, bias, T, d, E, out, s);
@@ -450,7 +449,7 @@ int launch_kmv(const void* x, int dtype, const void* w, const float* bias, int64
 bool route_short(int64_t T, int d, int E) {
     const int64_t et = ceil_div(E, 16), tiles = ceil_div(T, 16) * et;
     return T > 0 && ceil_div(T, route_rows(E)) < 128 && (d + 31) / 32 >= (E <= 16 ? 8 : 4) &&
-           ceil_div(tiles, 256) <= (et + (et <= 8)) / 2 && score_tiles_split(T, 2 * d, E, true) == 0;
+           ceil_div(tiles, 256) <= (et + (et <= 8)) / 2 && !score_tiled(T, 2 * d, E);
 }
 
 // K chunks of a short batch's scores: one per 2048 elements, as long as they make no more
@@ -482,7 +481,7 @@ size_t route_ws_bytes(int dtype, int64_t T, int d, int E, int flags) {
     if ((flags & MOE_LOGITS_IN) || dtype != MOE_BF16 || T <= 0) return 0;
     const size_t scores = (size_t)T * (size_t)E * sizeof(float);
     if (route_short(T, d, E)) return route_chunks(T, d, E) * scores;
-    return score_tiles_split(T, 2 * d, E, true) == 1 ? scores : 0;
+    return score_tiled(T, 2 * d, E) ? scores : 0;
 }
 
 int launch_topk_given(const float* scores, int64_t T, int E, int k, int flags, int32_t* idx,

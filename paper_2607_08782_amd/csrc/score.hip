@@ -21,9 +21,7 @@
 // (0.85 before), 0.27 in bf16 (0.39).  Routing calls, top-k included: 8192 x 64, d = 2048
 // bf16 17.5 -> 13.9 us, E4M3 17.2 -> 11.8; 16384 x 128 27.7 -> 23.0 and 25.3 -> 18.3.
 //
-// With one K chunk the workgroup stores its scores (bias added); with S > 1
-// chunks it stores fp32 partial scores part[chunk][t][e], which the caller
-// sums in chunk order.  With one chunk it can also finish with the
+// The workgroup stores its scores (bias added), and up to 128 experts finishes with the
 // top-k of its own 64 tokens (KM > 0): the scores go through LDS to the same
 // top-k as for given scores, so no second launch reads them back.
 #include "common.h"
@@ -50,13 +48,13 @@ __device__ __forceinline__ void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// KM > 0 (S == 1): top-k (k <= KM, top-k class C) of the workgroup's tokens
+// KM > 0: top-k (k <= KM, top-k class C) of the workgroup's tokens
 // into idx / gate after the scores; out (the scores) may then be null.
 template <bool FP8, int WM, int WN, int NTW, int R, int KM = 0, int C = 0>
 __global__ __launch_bounds__(64 * WM * WN) void score_tiles_kernel(
     const uint8_t* __restrict__ x, const uint8_t* __restrict__ w, const float* __restrict__ sx,
     const float* __restrict__ sw, const float* __restrict__ bias, int64_t T, int rowbytes, int E,
-    int S, float* __restrict__ out, int k = 0, int renorm = 0, int32_t* __restrict__ idx = nullptr,
+    float* __restrict__ out, int k = 0, int renorm = 0, int32_t* __restrict__ idx = nullptr,
     float* __restrict__ gate = nullptr) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     constexpr int NW = WM * WN, BM = 32 * WM;         // waves, tokens
@@ -74,10 +72,7 @@ __global__ __launch_bounds__(64 * WM * WN) void score_tiles_kernel(
     const int wm = wave % WM, wn = wave / WM;
     const int64_t t0 = (int64_t)blockIdx.x * BM;
     const int nt = (int)((T - t0) < BM ? (T - t0) : BM);
-    const int chunk = blockIdx.y;
-    const int nst_all = rowbytes / SC_BKB;
-    const int st0 = (int)((int64_t)chunk * nst_all / S);
-    const int nst = (int)((int64_t)(chunk + 1) * nst_all / S) - st0;
+    const int nst = rowbytes / SC_BKB;
 
     const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(x + t0 * rowbytes), (short)0, nt * rowbytes, SC_RSRC_WORD3);
@@ -95,7 +90,7 @@ __global__ __launch_bounds__(64 * WM * WN) void score_tiles_kernel(
     const int vstep = 8 * NW * rowbytes;
     auto dma = [&](int s) {
         char* base = lds + (s % R) * STAGE;
-        const int so = (st0 + s) * SC_BKB;
+        const int so = s * SC_BKB;
         const bool in = s < nst;
 #pragma unroll
         for (int i = 0; i < A_LOADS; ++i)
@@ -134,7 +129,7 @@ __global__ __launch_bounds__(64 * WM * WN) void score_tiles_kernel(
     for (int j = 0; j < NTW; ++j) {
         const int col = wn * 32 * NTW + j * 32 + fr;
         const int cc = col < E ? col : E - 1;
-        b_c[j] = (S == 1 && bias) ? bias[cc] : 0.0f;
+        b_c[j] = bias ? bias[cc] : 0.0f;
         s_c[j] = FP8 ? sw[cc] : 1.0f;
     }
 
@@ -205,10 +200,10 @@ __global__ __launch_bounds__(64 * WM * WN) void score_tiles_kernel(
     wait_vm<0>();                          // no load outlives the ring
 
     // accumulator element r of a 32x32 tile: row 8 (r / 4) + 4 h + r % 4, column fr;
-    // S == 1: out[t][e] = score + bias[e];  S > 1: out[chunk][t][e] = partial score.
+    // out[t][e] = score + bias[e].
     // Branch-free stores through a descriptor over the block's rows: an element past
     // the batch or past E gets an offset outside it and is dropped.
-    float* o = out ? out + (S > 1 ? (int64_t)chunk * T * E : 0) + t0 * E : nullptr;
+    float* o = out ? out + t0 * E : nullptr;
     const __amdgpu_buffer_rsrc_t orsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)o, (short)0, o ? nt * E * 4 : 0, SC_RSRC_WORD3);
     // fused top-k: the scores also go to an LDS tile [64][E_pad + 1] over the
@@ -230,7 +225,7 @@ __global__ __launch_bounds__(64 * WM * WN) void score_tiles_kernel(
             const int row = wm * 32 + (r >> 2) * 8 + 4 * h + (r & 3);
             float v = acc[j][r];
             if (FP8) v = v * sx_r[r] * s_c[j];
-            if (S == 1 && bias) v += b_c[j];
+            if (bias) v += b_c[j];
             const int off = (row < nt && col < E) ? (row * E + col) * 4 : SC_OOB;
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), orsrc, off, 0, 0);
             if constexpr (KM > 0)
@@ -241,20 +236,6 @@ __global__ __launch_bounds__(64 * WM * WN) void score_tiles_kernel(
         __syncthreads();
         topk_tokens<KM, C>(sc, ldS, nt, t0, E, k, renorm, idx, gate);
     }
-}
-
-template <bool FP8, int WM, int WN, int NTW, int R>
-int launch_tiles(const uint8_t* x, const uint8_t* w, const float* sx, const float* sw,
-                 const float* bias, int64_t T, int rowbytes, int E, int S, float* out,
-                 hipStream_t s) {
-    constexpr size_t lds = (size_t)R * 32 * (WM + WN * NTW) * SC_BKB;
-    static_assert(lds <= 160 * 1024, "ring fits the LDS of a CU");
-    if (lds > 65536 && allow_dynamic_lds<score_tiles_kernel<FP8, WM, WN, NTW, R>>(lds) != MOE_OK)
-        return MOE_ERR_DEVICE;
-    const dim3 grid((unsigned)ceil_div(T, 32 * WM), (unsigned)S);
-    hipLaunchKernelGGL((score_tiles_kernel<FP8, WM, WN, NTW, R>), grid, dim3(64 * WM * WN), lds, s, x,
-                       w, sx, sw, bias, T, rowbytes, E, S, out);
-    return launch_status();
 }
 
 template <bool FP8, int WM, int WN, int NTW, int R, int KM, int C>
@@ -270,7 +251,7 @@ int launch_tiles_topk(const uint8_t* x, const uint8_t* w, const float* sx, const
         return MOE_ERR_DEVICE;
     hipLaunchKernelGGL((score_tiles_kernel<FP8, WM, WN, NTW, R, KM, C>),
                        dim3((unsigned)ceil_div(T, 32 * WM)), dim3(64 * WM * WN), lds, s, x, w, sx, sw,
-                       bias, T, rowbytes, E, 1, logits, k, renorm, idx, gate);
+                       bias, T, rowbytes, E, logits, k, renorm, idx, gate);
     return launch_status();
 }
 
@@ -287,46 +268,51 @@ int launch_topk_by_width(const uint8_t* x, const uint8_t* w, const float* sx, co
 
 }  // namespace
 
-// K chunks for the tiled score kernel, or 0 when the shape does not suit it:
+// Whether a batch takes the tiled score kernel:
 // E > 32 (smaller E is cheap for the K-split kernel), whole 128-byte stages,
 // and at least 128 token tiles (half a tile per CU or more; the DeepSeek-V2-Lite
 // prefill batch of 8192 tokens: 22.1 -> 20.2 us against the block kernel).  One
-// chunk: summing K-chunk partials in a second pass cost more than the
+// K chunk: summing K-chunk partials in a second pass cost more than the
 // parallelism it bought (that batch split in two: 27.1 us), and with fewer tiles
 // the K-split kernel, which spreads a batch over more workgroups, measured faster
 // (Qwen1.5-shaped batches).
-int score_tiles_split(int64_t T, int rowbytes, int E, bool allow_split) {
-    (void)allow_split;
-    if (E <= 32 || E > MOE_MAX_E || rowbytes % SC_BKB != 0 || T <= 0) return 0;
-    if ((int64_t)MOE_MAX_E * rowbytes >= ((int64_t)1 << 31)) return 0;   // 32-bit buffer offsets
-    return ceil_div(T, 64) >= 128 ? 1 : 0;
+bool score_tiled(int64_t T, int rowbytes, int E) {
+    if (E <= 32 || E > MOE_MAX_E || rowbytes % SC_BKB != 0 || T <= 0) return false;
+    if ((int64_t)MOE_MAX_E * rowbytes >= ((int64_t)1 << 31)) return false;   // 32-bit buffer offsets
+    return ceil_div(T, 64) >= 128;
 }
 
 // Waves and ring by tile width.  Up to 64 experts: 4 waves, 4 stages, two workgroups a
 // CU (8 stages, one a CU: 13.8 against 15.5 us at 8192 x 64, d = 2048); up to 128: 8
-// waves (4: 22.4 against 22.7 us at 12000 x 100, even at 16384 x 128), 6 stages; wider:
-// as many stages as the LDS holds.
+// waves (4: 22.4 against 22.7 us at 12000 x 100, even at 16384 x 128), 6 stages, both with
+// the top-k (launch_score_tiles_topk); wider: as many stages as the LDS holds.
+template <bool FP8>
+static int launch_wide(const void* x, const void* w, const float* sx, const float* sw,
+                       const float* bias, int64_t T, int rowbytes, int E, float* out, hipStream_t s) {
+    constexpr int WM = 2, WN = 2, NTW = 4, R = 3;
+    constexpr size_t lds = (size_t)R * 32 * (WM + WN * NTW) * SC_BKB;
+    static_assert(lds <= 160 * 1024, "ring fits the LDS of a CU");
+    if (allow_dynamic_lds<score_tiles_kernel<FP8, WM, WN, NTW, R>>(lds) != MOE_OK)
+        return MOE_ERR_DEVICE;
+    hipLaunchKernelGGL((score_tiles_kernel<FP8, WM, WN, NTW, R>),
+                       dim3((unsigned)ceil_div(T, 32 * WM)), dim3(64 * WM * WN), lds, s,
+                       (const uint8_t*)x, (const uint8_t*)w, sx, sw, bias, T, rowbytes, E, out);
+    return launch_status();
+}
+
 int launch_score_tiles(bool fp8, const void* x, const void* w, const float* sx, const float* sw,
-                       const float* bias, int64_t T, int rowbytes, int E, int S, float* out,
+                       const float* bias, int64_t T, int rowbytes, int E, float* out,
                        hipStream_t s) {
-    const uint8_t* xb = (const uint8_t*)x;
-    const uint8_t* wb = (const uint8_t*)w;
-#define MOE_SC(F)                                                                                   \
-    if (E <= 64) return launch_tiles<F, 2, 2, 1, 4>(xb, wb, sx, sw, bias, T, rowbytes, E, S, out, s);     \
-    if (E <= 128) return launch_tiles<F, 2, 4, 1, 6>(xb, wb, sx, sw, bias, T, rowbytes, E, S, out, s);    \
-    return launch_tiles<F, 2, 2, 4, 3>(xb, wb, sx, sw, bias, T, rowbytes, E, S, out, s)
-    if (fp8) {
-        MOE_SC(true);
-    }
-    MOE_SC(false);
-#undef MOE_SC
+    if (E <= SCORE_TOPK_MAX_E) return MOE_ERR_SHAPE;
+    return fp8 ? launch_wide<true>(x, w, sx, sw, bias, T, rowbytes, E, out, s)
+               : launch_wide<false>(x, w, sx, sw, bias, T, rowbytes, E, out, s);
 }
 
 int launch_score_tiles_topk(bool fp8, const void* x, const void* w, const float* sx,
                             const float* sw, const float* bias, int64_t T, int rowbytes, int E,
                             int k, int renorm, float* logits, int32_t* idx, float* gate,
                             hipStream_t s) {
-    if (E <= 32 || E > 128) return MOE_ERR_SHAPE;
+    if (E <= 32 || E > SCORE_TOPK_MAX_E) return MOE_ERR_SHAPE;
     const uint8_t* xb = (const uint8_t*)x;
     const uint8_t* wb = (const uint8_t*)w;
 #define MOE_ST(KM)                                                                               \
