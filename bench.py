@@ -3,7 +3,8 @@
 A step is one pass of the whole share (gate scores + top-k, histograms,
 packaging, grouped SwiGLU FFN, weighted combine) over one batch of synthetic
 tokens already resident in HBM, timed as replays of one HIP graph holding the
-five C-ABI calls.  Replays cycle through copies of the local expert weights
+share's C-ABI calls (moe_route_package, the FFN call and the combine, or the two
+of them as one; LayerShare.run).  Replays cycle through copies of the local expert weights
 until at least 1 GB of weights is touched, so no shape runs out of the 256 MB
 last-level cache.
 
@@ -47,7 +48,7 @@ METRIC = "MoE-layer tokens/s on 1 GPU; grouped-GEMM % bf16 MFMA peak; decode HBM
 PEAK_BF16_FLOPS = 2.5e15        # MI355X dense bf16 MFMA
 PEAK_FP32_FLOPS = 157.3e12      # MI355X fp32 vector
 PEAK_HBM_BYTES = 8.0e12         # MI355X HBM3E
-PHASES = ("route_topk", "histogram", "permute", "grouped_ffn", "shared_ffn", "combine")
+PHASES = ("route_package", "grouped_ffn", "shared_ffn", "combine")
 ROTATE_BYTES = 1e9              # weight bytes touched per cycle of replays
 MAX_COPIES = 16
 SHAPES = [("tiny_fp32", "batch"), ("deepseek_v2_lite", "prefill"), ("deepseek_v2_lite", "decode"),
@@ -165,14 +166,8 @@ def ffn_work(share, cfg):
 
 def phase_calls(share):
     """The calls of LayerShare.run, one callable per phase (for the eager breakdown)."""
-    def route():
-        share.route()
-
-    def histogram():
-        moe.moe_expert_histogram(share.topk_idx, share.E, counts=share.counts, coact=share.coact)
-
-    def permute():
-        share.package()
+    def route_package():
+        share._route_package()
 
     def grouped_ffn():
         share.routed_ffn()
@@ -184,8 +179,8 @@ def phase_calls(share):
         if not share.fused_combine:        # else part of grouped_ffn
             share.combine()
 
-    return dict(route_topk=route, histogram=histogram, permute=permute, grouped_ffn=grouped_ffn,
-                shared_ffn=shared_ffn, combine=combine)
+    return dict(route_package=route_package, grouped_ffn=grouped_ffn, shared_ffn=shared_ffn,
+                combine=combine)
 
 
 def eager_phases(share, steps, warmup):
@@ -326,7 +321,7 @@ def shape_entry(name, regime, steps, warmup):
 
 def gathered_variant(cfg, inp, shares, steps, warmup):
     """The headline share on its other packaging path (with the row copy x_perm
-    elided -- moe_permute writes the row maps only and moe_grouped_ffn_rows reads the
+    elided -- the packaging writes the row maps only and moe_grouped_ffn_rows reads the
     token rows through row_token -- or with it, whichever the share does not use):
     step time from graph replays over the same weight copies, and whether its output
     equals the share's bit for bit."""
@@ -339,9 +334,9 @@ def gathered_variant(cfg, inp, shares, steps, warmup):
     torch.cuda.synchronize()
     equal = bool(torch.equal(shares[0].y, gs[0].y))
     ms = time_replays([capture(g.run) for g in gs], steps, warmup)
-    what = ("row copy x_perm elided: moe_permute writes the row maps only and "
+    what = ("row copy x_perm elided: the packaging writes the row maps only and "
             "moe_grouped_ffn_rows reads the token rows through row_token") if gather else \
-           "rows copied to x_perm by moe_permute and read from there by moe_grouped_ffn"
+           "rows copied to x_perm by the packaging and read from there by moe_grouped_ffn"
     return {"gather_in_ffn": gather, "ms_per_step": ms, "tokens_per_s": inp.T / (ms * 1e-3),
             "bitwise_equal_output": equal, "what": what}
 
@@ -484,8 +479,9 @@ def main():
         "warmup": args.warmup,
         "ms_per_step": ms,
         "eager_ms_per_step": m["eager_ms"],
-        "launch": "each step is one HIP graph replay of the five C-ABI calls; replays cycle "
-                  "through %d copies of the local expert weights" % m["weight_copies"],
+        "launch": "each step is one HIP graph replay of the share's C-ABI calls "
+                  "(moe_route_package, FFN, combine); replays cycle through %d copies of the "
+                  "local expert weights" % m["weight_copies"],
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,

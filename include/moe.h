@@ -88,9 +88,10 @@ const char* moe_status_string(int status);
  *           otherwise (then the scores are not stored)
  * topk_idx  device [T][k] int32 output;  topk_gate  device [T][k] float output
  * ws        device workspace of moe_route_topk_ws_bytes(dtype, T, d, E, flags)
- *           bytes, 256-byte aligned; may be NULL when that size is 0.  (Short
- *           batches split the gate GEMM over K across workgroups and keep the
- *           per-chunk fp32 partial scores here; they are summed in chunk order.)
+ *           bytes, 256-byte aligned; may be NULL when that size is 0.  (bf16 batches
+ *           whose scores run in a launch of their own keep them here: the long ones
+ *           when logits is NULL, the short ones always, past d = 2048 as fp32 partial
+ *           scores per K chunk, which are summed in chunk order.)
  * Requires 1 <= E <= MOE_MAX_E, 1 <= k <= min(E, MOE_MAX_K), T >= 0,
  * d >= 1 and, for MOE_BF16, d % 8 == 0 and E * d * 2 < 2^31 (else
  * MOE_ERR_SHAPE).  Logits must be finite.
@@ -258,13 +259,14 @@ int moe_grouped_ffn(const void* x_perm, int dtype, const int32_t* group_offsets,
  * than 256 rows (true of a batch of at most 256 tokens: a token reaches an
  * expert at most once).  Every group then takes the weight-streaming kernels
  * and the call skips the launches of the tiled kernels.  Without the flag a
- * call streams every group of at most 256 rows when its groups above 64 rows
- * make few tiles (always so when no group holds more than 64 rows), and tiles
- * every group otherwise; so a call whose groups all hold at most 64 rows gives
- * bitwise the outputs it gives without the flag, and a group that the call
- * without the flag would tile sums its products in another order (same
- * tolerance).  Rows of a group that breaks the statement are left unwritten.  It must be passed the same way to
- * the MOE_FFN_GATE_UP and the MOE_FFN_DOWN call of one pair.
+ * call streams every group when none holds more than 256 rows and its groups
+ * above 64 rows make few tiles (always so when no group holds more than 64
+ * rows), and tiles every group otherwise, each product by itself; so a call
+ * whose groups all hold at most 64 rows gives bitwise the outputs it gives
+ * without the flag, and a group that the call without the flag would tile sums
+ * its products in another order (same tolerance).  Rows of a group that breaks
+ * the statement are left unwritten.  It must be passed the same way to the
+ * MOE_FFN_GATE_UP and the MOE_FFN_DOWN call of one pair.
  * Adding MOE_FFN_LARGE_GROUPS instead states that every non-empty group holds
  * more than 256 rows (true of a shared expert's call over more than 256
  * tokens): every group then takes the tiled kernels and the call skips the

@@ -2,31 +2,26 @@
 // Director paper: each expert is an FFN sub-network; Eq. 2 prices this step
 // as the per-GPU compute latency f_comp of the rows a GPU receives).
 //
-// bf16 path, two launches of one persistent MFMA kernel:
-//   1. H = SiLU(X W1^T) * (X W3^T)   gate and up tiles side by side in one
-//                                     256-row weight tile, fused epilogue
+// bf16 path, two products, each "NT": every operand row is contiguous along K, so
+// global loads and MFMA fragment reads are all 16-byte vectors.
+//   1. H = SiLU(X W1^T) * (X W3^T)   gate and up rows side by side in one weight
+//                                     tile, fused epilogue
 //   2. Y = H W2^T
-// Both products are "NT": every operand row is contiguous along K, so global
-// loads, LDS stores and MFMA fragment reads are all 16-byte vectors.
-//
-// Kernel shape (gfx950, wave64):
-//   workgroup 512 threads = 8 waves (4 x 2, two per SIMD), macro tile 256 rows
-//   x 256 weight rows, K step 64, LDS double buffer (2 x 64 KiB, 128-byte rows
-//   with XOR-swizzled 16-byte chunks), wave tile 64 x 128 on
-//   v_mfma_f32_16x16x32_bf16 (4 x 8 accumulator tiles), fragment reads
-//   software-pipelined against the MFMAs.  Under sustained load the part runs
-//   at its board power limit, so the clock follows the energy spent per flop:
-//   16x16x32 moves half the accumulator bytes per flop of 32x32x16 and runs
-//   these loops at a higher clock.
-//   The grid is persistent (one workgroup per CU).  Tiles are ordered
-//   (group, n-tile, m-tile) and cut into eight contiguous chunks, one per XCD
-//   (workgroups are dispatched round-robin over the XCDs), so the workgroups
-//   sharing an L2 also share weight tiles.  A workgroup's tiles form one load
-//   pipeline: the next tile's first stages are loaded during the current
-//   tile's last step, so a tile starts without waiting for its operands.  The
-//   epilogue stores 8 bytes per lane (four columns of one row, gathered by a
-//   4 x 4 transpose inside each lane quad).  Group sizes are read on the
-//   device; empty groups produce no tiles, so their weights are never read.
+// Groups of many rows run as 256 x 256 tiles of a persistent grid
+// (grouped_gemm_kernel: bound by the matrix rate under the board's power limit).
+// A short call's groups of up to 256 rows stream their weights instead (bound by
+// latency and the weight reads): as strips that walk all of K (strip_gemm_kernel),
+// or, where K is long, split over workgroups (stream_gemm_kernel) and summed in
+// chunk order (split_reduce_kernel, which also sums the tiled kernel's split
+// tiles).  Which groups stream is decided on the device from the group sizes
+// (small_limits), which form streams on the host (strip_product).  All use
+// v_mfma_f32_16x16x32_bf16 but the split kernel (32x32x16): under sustained load
+// the part runs at its board power limit, so the clock follows the energy per
+// flop, and 16x16x32 moves half the accumulator bytes per flop.  Work is cut into
+// eight contiguous chunks, one per XCD (workgroups are dispatched round-robin
+// over the XCDs), so the workgroups sharing an L2 also share weights.  Group
+// sizes are read on the device; empty groups produce no tiles, so their weights
+// are never read.
 #include <type_traits>
 
 #include "common.h"
@@ -112,10 +107,10 @@ struct GemmArgs {
 constexpr int TILE_SPLIT_UNITS = 256;
 constexpr int TILE_SPLIT_MIN_STEPS = 8;
 
-// A short call (see small_limits) streams its groups of up to SMALL_ROWS_MAX rows
-// through the split-K streaming kernel and tiles the rest; any other call tiles
-// every group.  Without the row limits in the workspace (a call of at most
-// SMALL_ROWS rows in all) every group is streamed.
+// A short call none of whose groups holds more than SMALL_ROWS_MAX rows streams every
+// group (see small_limits, which decides for each product); any other call tiles every
+// group.  Without the row limits in the workspace (a call of at most SMALL_ROWS rows in
+// all) every group is streamed.
 constexpr int SMALL_ROWS = 64;
 constexpr int SMALL_ROWS_MAX = 256;
 
@@ -672,18 +667,17 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
 // Small groups (those of a short call up to SMALL_ROWS_MAX rows, see
 // small_limits; every group of a call with the MOE_FFN_SMALL_GROUPS statement or
 // of at most SMALL_ROWS rows in all): weight streaming with split-K.  Here the
-// weights dominate the traffic (each weight byte is used by
-// a handful of rows), so the aim is to read every weight byte once, from all
-// CUs at once.  Work item = (group, 128 weight rows, K chunk, 64 rows); one
-// workgroup per item, three per CU with three K steps of loads in flight
-// each (four per CU cannot hold that ring without spilling), fp32 partial sums
-// per K chunk.  HBM reads
-// reach their rate only with many independent streams in flight (a read-only
-// probe over 448 MiB: 4.3-5.1 TB/s with 224-448 workgroups, 5.4-5.7 TB/s with
-// 896 or more), so the item is narrow in weight rows and covers a whole
-// decode-sized group (a group of up to 64 rows reads its weights once).  A second kernel adds the
-// chunks in a fixed order (so results are deterministic) and, for the gate/up
-// product, applies SiLU(a) * b.
+// weights dominate the traffic (each weight byte is used by a handful of rows), so
+// the aim is to read every weight byte once, from all CUs at once.  This kernel runs
+// the products that strip_product leaves it (the long K).  Work item = (group, 128
+// weight rows, K chunk, 64 rows); one workgroup per item, three per CU with three K
+// steps of loads in flight each (four per CU cannot hold that ring without
+// spilling), fp32 partial sums per K chunk.  HBM reads reach their rate only with
+// many independent streams in flight (a read-only probe over 448 MiB: 4.3-5.1 TB/s
+// with 224-448 workgroups, 5.4-5.7 TB/s with 896 or more), so the item is narrow in
+// weight rows and covers a whole decode-sized group (a group of up to 64 rows reads
+// its weights once).  A second kernel adds the chunks in a fixed order (so results
+// are deterministic) and, for the gate/up product, applies SiLU(a) * b.
 // The split factor S is derived on the device from the group sizes; both
 // kernels derive the same plan from the same inputs.
 // ---------------------------------------------------------------------------
@@ -1259,7 +1253,7 @@ __device__ __forceinline__ void stream_reduce(const StreamArgs& args, const Stre
 }
 
 // The down product's chunk sum fused with the gate-weighted combine, for calls
-// in which every group is streamed (no group above SMALL_ROWS rows): one
+// in which every group is streamed (no group above SMALL_ROWS_MAX rows): one
 // thread per token and 4 output columns.  For each assignment r of token t, in
 // ascending r, the row's output is summed over the K chunks in chunk order and
 // rounded to bf16 (the value the chunk sum would store in y_perm), then added

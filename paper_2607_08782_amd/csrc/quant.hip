@@ -5,9 +5,11 @@
 // FP8 E4M3, which the matrix cores multiply natively
 // (v_mfma_scale_f32_32x32x64_f8f6f4).
 //
-//   quantize   one workgroup per row: |max| -> scale = max/448 (fp32), codes =
-//              E4M3 round-to-nearest-even of x/scale (fp32 division), stored
-//              as bytes; the row's largest magnitude maps to +-448
+//   quantize   one wave per row (short rows) or one workgroup per row: |max| ->
+//              scale = max/448 (fp32 division), codes = E4M3 round-to-nearest-even
+//              of the fp32 quotient x/scale (by the scale's reciprocal and one
+//              residual step, the division where that could differ), stored as
+//              bytes; the row's largest magnitude maps to +-448
 //   q-router   logits[t][e] = s_x[t] s_w[e] sum_i q_x[t][i] q_w[e][i] + b[e]:
 //              32 tokens x all experts per workgroup, eight waves split K in
 //              64-byte steps of the FP8 MFMA (unit block scales), partial

@@ -4,9 +4,10 @@
 torch) and enqueues, on the current stream:
     moe_route_package (moe_route_topk, moe_expert_histogram and moe_permute in one)
     -> moe_grouped_ffn (routed experts) -> moe_combine
-with no host synchronisation in between (decode-sized batches stream every
-expert group and skip the tiled GEMM launches; at most 64 tokens with k <= 2 the
-last two calls are one, moe_grouped_ffn_combine).  The shared experts (always
+with no host synchronisation in between (decode-sized batches, whose groups the
+host knows to hold at most 256 rows, stream every expert group and skip the tiled
+GEMM launches; at most 64 tokens with k <= 2 the last two calls are one,
+moe_grouped_ffn_combine).  The shared experts (always
 on, independent of the routing) run one of two ways.  Up to SHARED_IN_FFN_MAX_T
 tokens they are leading groups of the routed experts' FFN call
 (moe_grouped_ffn_rows_shared: each shared expert cut into blocks of the routed
@@ -203,24 +204,24 @@ class LayerShare:
         # out (a hint only: the routed groups are tiled whatever their size)
         elif self.shared_in_ffn and T > 256:
             self.ffn_products |= moe.MOE_FFN_LARGE_GROUPS
-        # when the mean group is at least 512 rows, a call short enough to stream its
-        # groups (at most a quarter of the CUs' worth of tiles in its groups above 64
-        # rows) would need this GPU's experts to get a small fraction of their share:
+        # a call streams only when none of its groups holds more than 256 rows and
+        # those above 64 rows make few tiles; when the mean group is at least 512 rows
+        # that would need this GPU's experts to get a small fraction of their share:
         # every group is tiled and the streaming launches, which would find nothing to
         # do, are left out (a hint only: any group sizes give correct results)
         elif T * k >= 512 * self.E:
             self.ffn_products |= moe.MOE_FFN_LARGE_GROUPS
-        # ... and then the combine can run inside the down product's chunk sum
-        # (moe_grouped_ffn_combine: y_perm is not written).  fuse_combine None: where
-        # it measured faster, batches of at most 64 tokens with k <= 2 (at k = 6 or 8
-        # the fused chunk sum, k x S partial loads per output element, is slower than
-        # the chunk sum plus the combine launch); True: whenever the call streams
-        # every group; False: never
         # the shared experts' call is one group of T rows: above 256 rows it is tiled
         # whole and its streaming launches are left out (MOE_FFN_LARGE_GROUPS)
         self.shared_products = self.ffn_products & ~moe.MOE_FFN_LARGE_GROUPS
         if T > 256:
             self.shared_products |= moe.MOE_FFN_LARGE_GROUPS
+        # a call that streams every group can take the combine into the down product's
+        # chunk sum (moe_grouped_ffn_combine: y_perm is not written).  fuse_combine
+        # None: where it measured faster, batches of at most 64 tokens with k <= 2 (at
+        # k = 6 or 8 the fused chunk sum, k x S partial loads per output element, is
+        # slower than the chunk sum plus the combine launch); True: whenever the call
+        # streams every group; False: never
         can_fuse = (bool(self.ffn_products & moe.MOE_FFN_SMALL_GROUPS) and dt == torch.bfloat16
                     and not gather_in_ffn and self.weights is not None
                     and not self.shared_in_ffn)

@@ -3,7 +3,7 @@
 For each shape (Mixtral-8x7B, DeepSeek-V2-Lite, Qwen1.5-MoE-A2.7B and
 Qwen3-30B-A3B-shaped shares; prefill and decode batches) and each seed 0-4:
 synthetic inputs of that shape (seeded normal hidden states and weights, Zipf
-popularity bias, the benchmark placement), the five calls captured in one HIP
+popularity bias, the benchmark placement), LayerShare's calls captured in one HIP
 graph, and the step timed over graph replays, for the share as LayerShare sets
 itself up (the row copy x_perm elided for bf16 batches of at least 16384
 token-expert assignments; shared experts inside the routed call up to 4096
@@ -152,8 +152,8 @@ def main(argv=None):
                                           res[0]["copies"]), flush=True)
     lines = ["# The layer share at every model shape and regime", "",
              "Synthetic seeded inputs of each shape (normal hidden states, N(0, 0.02) weights, Zipf",
-             "popularity bias, the benchmark placement with this GPU = device 0).  Step = the five",
-             "calls as one HIP graph replay; FFN = the routed experts' FFN call as the step makes it",
+             "popularity bias, the benchmark placement with this GPU = device 0).  Step = the",
+             "share's calls (`moe_route_package`, the FFN, the combine) as one HIP graph replay; FFN = the routed experts' FFN call as the step makes it",
              "(`moe_grouped_ffn`; `moe_grouped_ffn_combine` for batches of at most 64 tokens with",
              "k <= 2, which also writes the combined output; `moe_grouped_ffn_rows_shared` with the",
              "shared experts' blocks of width f as leading groups where the share runs them inside",
@@ -165,7 +165,7 @@ def main(argv=None):
              "active local experts' weights once, x_perm in, y_perm or the combined y out).  Weight",
              "copies: replays cycle through this many copies of the local expert weights (≥ 1 GB",
              "touched).",
-             "Step: the share as LayerShare sets itself up (the row copy x_perm elided -- moe_permute",
+             "Step: the share as LayerShare sets itself up (the row copy x_perm elided -- the packaging",
              "writes the row maps only and the FFN reads the token rows through row_token -- for bf16",
              "batches of at least 16384 token-expert assignments; shared experts as leading groups of",
              "the routed call up to 4096 tokens).  First-built path: the same share with the packaged",
