@@ -30,17 +30,22 @@ import json
 import os
 
 FFN_SOURCE = "paper_2607_08782_amd/csrc/ffn.hip"
-# kernels of one routed-expert FFN call and their launches per call (the streaming
-# kernel runs once per product; moe_grouped_ffn_combine ends with the combining
-# chunk sum in place of split_reduce_kernel<false>)
+# kernels of one routed-expert FFN call and their launches per call (a streamed
+# product runs as strips or as the split-K kernel, which is one instance for both
+# products; moe_grouped_ffn_combine ends with the combining chunk sum in place of
+# split_reduce_kernel<false>)
 FFN_CALL = {"grouped_gemm_kernel<true, false>": 1, "grouped_gemm_kernel<false, false>": 1,
+            "strip_gemm_kernel<true, false>": 1, "strip_gemm_kernel<false, false>": 1,
             "stream_gemm_kernel<false>": 2, "split_reduce_kernel<true>": 1,
             "split_reduce_kernel<false>": 1}
 FFN_CALL_PREFIX = {"stream_reduce_combine_kernel<": 1}
 
 
-def per_call(kernel):
-    """Launches of `kernel` in one routed-expert FFN call (0: not one of its kernels)."""
+def per_call(kernel, seen):
+    """Launches of `kernel` in one routed-expert FFN call (0: not one of its kernels)
+    of a run that launched the kernels `seen`."""
+    if kernel == "stream_gemm_kernel<false>":
+        return FFN_CALL[kernel] - sum(k.startswith("strip_gemm_kernel<") for k in seen)
     if kernel in FFN_CALL:
         return FFN_CALL[kernel]
     return next((n for p, n in FFN_CALL_PREFIX.items() if kernel.startswith(p)), 0)
@@ -116,9 +121,10 @@ def traffic(workload, fetch_csv, write_csv, copy_mib, out, repo="."):
         for n, v in disp:
             per[short(n)].append(v * 1024.0 * factor)
         for k, v in per.items():
-            if per_call(k):
+            n = per_call(k, per)
+            if n:
                 w["kernels"].setdefault(k, {})[key] = _mean(v)
-                w["call"][key] += _mean(v) * per_call(k)
+                w["call"][key] += _mean(v) * n
     res["workloads"][workload] = w
     res.setdefault("commands", {})[workload] = [
         "rocprofv3 --pmc %s --output-format csv -d gpurun_out/pmc -o %s -- python -u bench.py "
