@@ -153,7 +153,8 @@ def main(argv=None):
     lines = ["# The layer share at every model shape and regime", "",
              "Synthetic seeded inputs of each shape (normal hidden states, N(0, 0.02) weights, Zipf",
              "popularity bias, the benchmark placement with this GPU = device 0).  Step = the",
-             "share's calls (`moe_route_package`, the FFN, the combine) as one HIP graph replay; FFN = the routed experts' FFN call as the step makes it",
+             "share's calls (`moe_route_package`, the FFN, the combine) as one HIP graph replay; FFN =",
+             "the routed experts' FFN call as the step makes it",
              "(`moe_grouped_ffn`; `moe_grouped_ffn_combine` for batches of at most 64 tokens with",
              "k <= 2, which also writes the combined output; `moe_grouped_ffn_rows_shared` with the",
              "shared experts' blocks of width f as leading groups where the share runs them inside",
