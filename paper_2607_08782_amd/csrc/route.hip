@@ -452,14 +452,16 @@ bool route_short(int64_t T, int d, int E) {
            ceil_div(tiles, 256) <= (et + (et <= 8)) / 2 && !score_tiled(T, 2 * d, E);
 }
 
-// K chunks of a short batch's scores: one per 2048 elements, as long as they make no more
-// than a workgroup a CU (beyond that every CU is loading already, and the chunks' way
-// through memory costs more: 300 tokens, d = 4096, 128 experts 14.8 us in one chunk, 16.5 in
-// two).  moe_route_topk of 64 tokens in one chunk and in this many: d = 4096, 8 experts 10.4
-// and 8.5 us; d = 14336 24.6 and 9.1; d = 7168, 200 experts 24.4 and 16.3.
+// K chunks of a short batch's scores: past 2048 elements one per 1024 of them, as long as
+// they make no more than a workgroup a CU (beyond that every CU is loading already, and the
+// chunks' way through memory costs more: 300 tokens, d = 4096, 128 experts 14.8 us in one
+// chunk, 16.5 in two).  moe_route_topk of 64 tokens in one chunk, chunks of 2048 and of 1024:
+// d = 4096, 8 experts 10.4, 8.7 and 7.8 us; d = 14336 24.6, 9.0 and 8.9; d = 4096, 16
+// experts 9.3 and 8.0 (the K chunks of one wave each that this kernel replaced: 7.9, 8.7
+// and 8.0); chunks of 512 are even with 1024.
 int route_chunks(int64_t T, int d, int E) {
     const int64_t tiles = ceil_div(T, 16) * ceil_div(E, 16);
-    int64_t chunks = ceil_div(d, 2048);
+    int64_t chunks = d <= 2048 ? 1 : ceil_div(d, 1024);
     if (chunks > 256 / tiles) chunks = 256 / tiles;
     if (chunks > 16) chunks = 16;
     return chunks < 1 ? 1 : (int)chunks;

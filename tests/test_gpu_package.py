@@ -38,6 +38,7 @@ CASES = [
     (60, 128, 8, 4104, 9, True, "bf16", False, False),
     (7, 200, 16, 7168, 5, False, "bf16", False, False),
     (300, 60, 4, 14336, 8, False, "bf16", False, False),
+    (5, 20, 3, 24576, 4, False, "bf16", False, False),      # as many chunks as there may be
     (2000, 16, 2, 4096, 4, False, "bf16", False, False),    # long: the histogram's launches
     # long batches: the count of all experts per block (up to 32768 tokens, room for it)
     (1088, 128, 8, 256, 9, True, "bf16", False, False),
