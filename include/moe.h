@@ -261,7 +261,8 @@ int moe_grouped_ffn(const void* x_perm, int dtype, const int32_t* group_offsets,
  * and the call skips the launches of the tiled kernels.  Without the flag a
  * call streams every group when none holds more than 256 rows and its groups
  * above 64 rows make few tiles (always so when no group holds more than 64
- * rows), and tiles every group otherwise, each product by itself; so a call
+ * rows), and tiles every group otherwise, each product by itself (some calls
+ * with K past 8192 tile only the groups above 256 rows); so a call
  * whose groups all hold at most 64 rows gives bitwise the outputs it gives
  * without the flag, and a group that the call without the flag would tile sums
  * its products in another order (same tolerance).  Rows of a group that breaks

@@ -109,8 +109,9 @@ constexpr int TILE_SPLIT_MIN_STEPS = 8;
 
 // A short call none of whose groups holds more than SMALL_ROWS_MAX rows streams every
 // group (see small_limits, which decides for each product); any other call tiles every
-// group.  Without the row limits in the workspace (a call of at most SMALL_ROWS rows in
-// all) every group is streamed.
+// group, but for some with a long K, which stream those of up to SMALL_ROWS_MAX rows.
+// Without the row limits in the workspace (a call of at most SMALL_ROWS rows in all)
+// every group is streamed.
 constexpr int SMALL_ROWS = 64;
 constexpr int SMALL_ROWS_MAX = 256;
 
@@ -203,33 +204,50 @@ __device__ __forceinline__ TilePos tile_pos(int local, int mt, int n_tiles) {
 // launch is short and latency-bound: every workgroup still runs several K
 // stages of a 256 x 256 tile, on a fraction of the CUs.  Streaming every group
 // of up to SMALL_ROWS_MAX rows instead spreads the weight reads over all CUs
-// (a DeepSeek-V2-Lite-shaped decode step: 219 -> 188 us).  Only when no group is
-// larger still: a call that tiles one group anyway tiles them all, in one launch's
-// rounds instead of two launches (777 tokens of the Mixtral shape, groups of about
-// 500 and 120 rows: step 344 -> 325 us).  Otherwise the small
+// (a DeepSeek-V2-Lite-shaped decode step: 219 -> 188 us).  As a rule only when no
+// group is larger still: a call that tiles one group anyway tiles them all, in one
+// launch's rounds instead of two launches (777 tokens of the Mixtral shape, groups
+// of about 500 and 120 rows: step 344 -> 325 us).  Not where all of the groups
+// make too many tiles to split K over (more than half the units) and K is past
+// MIXED_MIN_K: whole tiles then walk all of a long K in a round or two, and the
+// streamed groups beside split tiles of the large ones are ahead (FFN, one group of
+// 500 rows and small ones, all tiled against both: 8 groups at d = 4096, f = 14336 805
+// and 700 us, 16 at d = 12288, f = 1024 446 and 361, 32 at d = 1024, f = 10240 583 and
+// 510), by less the shorter K is (the second launch and its chunk sum cost about 20 us
+// at any K): 8 groups at d = 5120, f = 8256 616 and 603, and 514 and 524 with 300 rows;
+// 16 at d = 5120, f = 1536 250 and 255, and 215 and 226.  Otherwise the small
 // groups join the tiled launch, whose rounds leave CUs free for their tiles,
 // rather than stream in a launch of their own after it (the two run one after
 // the other): DeepSeek-V2-Lite prefill FFN 364 -> 332 us, Qwen1.5 batch 137 ->
 // 129 us, Qwen3 prefill 466 -> 459 us.
+constexpr int MIXED_MIN_K = 8192;
+
 __device__ __forceinline__ void small_limits(const int* s_off, int n_groups, int tiles_up,
-                                             int tiles_down, int split_units, int lane,
-                                             int& lim_up, int& lim_down) {
+                                             int tiles_down, int k_up, int k_down,
+                                             int split_units, int lane, int& lim_up,
+                                             int& lim_down) {
     int mt = 0;                                      // 256-row tiles of the groups > SMALL_ROWS
+    int all = 0;                                     // of every group
     int most = 0;
     for (int g0 = 0; g0 < n_groups; g0 += 64) {
         const int g = g0 + lane;
         const int rows = g < n_groups ? s_off[g + 1] - s_off[g] : 0;
         mt += rows > SMALL_ROWS ? (int)ceil_div(rows, BM) : 0;
+        all += (int)ceil_div(rows, BM);
         most = max(most, rows);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         mt += __shfl_xor(mt, o, 64);
+        all += __shfl_xor(all, o, 64);
         most = max(most, __shfl_xor(most, o, 64));
     }
-    const bool fits = most <= SMALL_ROWS_MAX;
-    lim_up = fits && 4 * mt * tiles_up <= split_units ? SMALL_ROWS_MAX : 0;
-    lim_down = fits && 4 * mt * tiles_down <= split_units ? SMALL_ROWS_MAX : 0;
+    auto limit = [&](int tiles, int k) {
+        const bool mixed = k > MIXED_MIN_K && 2 * all * tiles > split_units;
+        return (most <= SMALL_ROWS_MAX || mixed) && 4 * mt * tiles <= split_units ? SMALL_ROWS_MAX : 0;
+    };
+    lim_up = limit(tiles_up, k_up);
+    lim_down = limit(tiles_down, k_down);
 }
 
 // Persistent grouped NT GEMM: 4 waves (2 x 2), one per SIMD, each a 128 x 128
@@ -299,8 +317,9 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void grouped_gemm_kernel(GemmArgs 
     if (wave == 0) {
         if (args.limits != nullptr && args.product == 0) {
             int lim_down;
-            small_limits(s_off, n_groups, args.n_tiles, args.down_tiles, args.split_units, lane, lim,
-                         lim_down);
+            // the gate/up product's N is the down product's K
+            small_limits(s_off, n_groups, args.n_tiles, args.down_tiles, args.K, args.N,
+                         args.split_units, lane, lim, lim_down);
             if (blockIdx.x == 0 && lane == 0) {
                 args.limits[0] = lim;
                 args.limits[1] = lim_down;

@@ -204,8 +204,9 @@ class LayerShare:
         # out (a hint only: the routed groups are tiled whatever their size)
         elif self.shared_in_ffn and T > 256:
             self.ffn_products |= moe.MOE_FFN_LARGE_GROUPS
-        # a call streams only when none of its groups holds more than 256 rows and
-        # those above 64 rows make few tiles; when the mean group is at least 512 rows
+        # a call streams only when none of its groups holds more than 256 rows (with a
+        # long K: the groups that don't) and those above 64 rows make few tiles; when
+        # the mean group is at least 512 rows
         # that would need this GPU's experts to get a small fraction of their share:
         # every group is tiled and the streaming launches, which would find nothing to
         # do, are left out (a hint only: any group sizes give correct results)

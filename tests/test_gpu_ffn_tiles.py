@@ -103,3 +103,52 @@ def test_more_tiles_than_a_list_holds():
         rel = (y[pick].double() - ref).norm(dim=1) / ref.norm(dim=1)
         assert float(rel.max()) < OUT_TOL["bf16"], (g, float(rel.max()))
         a += n
+
+
+@pytest.mark.parametrize("sizes,d,f,gather", [
+    ([300, 40, 1, 64, 0, 200, 7, 100, 5], 8256, 2048, True),           # the gate/up product
+    ([9, 64, 30, 1, 256, 17, 500, 3, 2, 33, 50, 6, 0, 12, 65, 8, 21, 4], 2048, 8256, False),  # down
+])
+def test_streamed_beside_tiled_groups(sizes, d, f, gather):
+    """A long K and more tiles than can be split: the groups of up to 256 rows stream
+    beside the tiles of the large one.  Against float64 on every row, the products
+    together and one by one, and not the bits of a call that tiles every group."""
+    say("[bf16 ffn] mixed", sizes, "d=%d f=%d gather=%s" % (d, f, gather))
+    N, T = sum(sizes), max(sizes) + 5
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn((T if gather else N, d), generator=gen, device="cuda").bfloat16()
+    w13 = [(torch.randn((2 * f, d), generator=gen, device="cuda") * d ** -0.5).bfloat16() for _ in sizes]
+    w2 = [(torch.randn((d, f), generator=gen, device="cuda") * f ** -0.5).bfloat16() for _ in sizes]
+    tok = torch.randint(0, T, (N + 2,), generator=gen, device="cuda", dtype=torch.int32)
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    wt, off = moe.WeightTable(w13, w2), torch.tensor(offs).cuda()
+    ws = moe.workspace(moe.moe_grouped_ffn_ws_bytes(moe.MOE_BF16, N + 2, d, f, len(sizes)), "cuda")
+
+    def call(*products):
+        y = torch.full((N + 2, d), 5.0, dtype=torch.bfloat16, device="cuda")
+        for p in products:
+            if gather:
+                moe.moe_grouped_ffn_rows(x, tok, off, wt, cap_rows=N + 2, y_perm=y, ws=ws, products=p)
+            else:
+                moe.moe_grouped_ffn(torch.cat([x, x[:2]]), off, wt, cap_rows=N + 2, y_perm=y, ws=ws,
+                                    products=p)
+        torch.cuda.synchronize()
+        return y
+
+    y = call(3)
+    assert torch.equal(y, call(moe.MOE_FFN_GATE_UP, moe.MOE_FFN_DOWN)) and torch.equal(y, call(3))
+    assert bool((y[N:] == 5.0).all())
+    tiled = call(3 | LARGE)
+    rows, small = x[tok[:N].long()] if gather else x, []
+    for g, n in enumerate(sizes):
+        if n == 0:
+            continue
+        a = int(offs[g])
+        xs = rows[a:a + n].double()
+        h = torch.nn.functional.silu(xs @ w13[g][:f].double().t()) * (xs @ w13[g][f:].double().t())
+        ref = h @ w2[g].double().t()
+        rel = (y[a:a + n].double() - ref).norm(dim=1) / ref.norm(dim=1)
+        assert float(rel.max()) < OUT_TOL["bf16"], (g, float(rel.max()))
+        small += [r for r in range(a, a + n) if n <= 256]
+    # over all of them: an order of fp32 sums changes one h in about 10^4 after rounding
+    assert not torch.equal(y[small], tiled[small])
